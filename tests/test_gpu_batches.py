@@ -87,6 +87,48 @@ def test_ragged_batches_of_channel_sums(shape, batch):
     plan.close()
 
 
+def _row_group_error(k, channels, lanes=16, samples=4000):
+    """2-norm error of a float32 sum of channels * k * k random products in the row groups' order:
+    `lanes` chains of fused multiply-adds over one list of all channels' entries, then a tree."""
+    rng = np.random.default_rng(1)
+    w = rng.standard_normal(channels * k * k).astype(np.float32)
+    x = rng.standard_normal((w.size, samples)).astype(np.float32)
+    parts = [np.zeros(samples, np.float32) for _ in range(lanes)]
+    for t in range(w.size):           # (one rounding per step: the product is exact in 64 bits)
+        parts[t % lanes] = (np.float64(w[t]) * x[t] + parts[t % lanes]).astype(np.float32)
+    while len(parts) > 1:
+        parts = [a + b for a, b in zip(parts[::2], parts[1::2])]
+    ref = w.astype(np.float64) @ x
+    return np.linalg.norm(parts[0] - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("shape,channels,batch,offset", [
+    ((70, 75, 5, 1, 2), 64, 10, 0), ((70, 75, 7, 1, 3), 48, 5, 1), ((70, 75, 7, 1, 3), 3, 3, 0), ((70, 67, 7, 1, 3), 24, 8, 2),
+    ((40, 75, 9, 1, 4), 24, 3, 0), ((130, 160, 11, 4, 5), 12, 5, 0),
+])
+def test_ragged_channel_sums_are_as_exact_as_the_row_groups(shape, channels, batch, offset):
+    """Batches that are not a multiple of 4, or operands off the 16-byte grid, walked by the staged
+    march: within 5 % (the scatter of the two samples) of the error of up to 16 lanes per row, where a
+    single chain per lane through all channels is twice as far from the exact sum or more."""
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(channels)
+    K = rng.standard_normal(channels * k * k).astype(np.float32)
+    x = rng.standard_normal(channels * m * n * batch).astype(np.float32)
+    plan = cs.conv_csr_build_channels(*shape, torch.from_numpy(K).to(device()), channels)
+    cs.conv_plan_set_march_min_jobs(plan, 1)
+    variant = plan.variant(batch)
+    assert variant.startswith("lds_march_staged_") and variant.endswith("_%d_channels" % channels), variant
+    _, xd = _padded(x, offset)
+    y = cs.conv_spmv(plan, xd, batch=batch)
+    torch.cuda.synchronize()
+    ref, scale = oracle.conv_channels(m, n, k, s, p, x, K, channels, batch=batch, want_scale=True)
+    got = y.cpu().numpy()
+    _check(got, ref, scale, (shape, batch))
+    ref = ref.astype(np.float64)
+    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1.05 * _row_group_error(k, channels)
+    plan.close()
+
+
 @pytest.mark.parametrize("shape,jobs,kind", [
     ((70, 75, 3, 1, 1), 1, "compact_rect"), ((60, 131, 5, 2, 2), 1, "compact_rect"), ((50, 75, 11, 1, 5), 1, "compact_described"),
     ((70, 75, 6, 4, 2), 1, "compact_described"), ((33, 41, 3, 1, 1), None, "compact_gather"), ((33, 41, 13, 1, 6), None, "compact_gather"),

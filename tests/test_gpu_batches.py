@@ -87,11 +87,10 @@ def test_ragged_batches_of_channel_sums(shape, batch):
     plan.close()
 
 
-def _row_group_error(k, channels, lanes=16, samples=4000):
-    """2-norm error of a float32 sum of channels * k * k random products in the row groups' order:
-    `lanes` chains of fused multiply-adds over one list of all channels' entries, then a tree."""
+def _row_group_error(w, lanes=16, samples=4000):
+    """2-norm error of float32 sums of products with the numbers w in the row groups' order: `lanes`
+    chains of fused multiply-adds over one list of all channels' entries, then a tree."""
     rng = np.random.default_rng(1)
-    w = rng.standard_normal(channels * k * k).astype(np.float32)
     x = rng.standard_normal((w.size, samples)).astype(np.float32)
     parts = [np.zeros(samples, np.float32) for _ in range(lanes)]
     for t in range(w.size):           # (one rounding per step: the product is exact in 64 bits)
@@ -125,7 +124,7 @@ def test_ragged_channel_sums_are_as_exact_as_the_row_groups(shape, channels, bat
     got = y.cpu().numpy()
     _check(got, ref, scale, (shape, batch))
     ref = ref.astype(np.float64)
-    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1.05 * _row_group_error(k, channels)
+    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1.05 * _row_group_error(K)
     plan.close()
 
 
@@ -186,6 +185,47 @@ def test_channel_sums_in_row_groups_follow_the_descriptors(shape, channels, batc
         ref += T @ xc
         scale += abs(T) @ np.abs(xc)
     _check(y.cpu().numpy(), ref.reshape(-1), scale.reshape(-1), (shape, channels, batch))
+    plan.close()
+
+
+def _launch_per_channel_error(K, channels, lanes, samples=4000):
+    """2-norm error of float32 sums over `channels` channels with the kernels K, each channel summed by
+    `lanes` chains of fused multiply-adds and a tree, then added to the sum of the channels before.  (The
+    error depends on the kernels by some 7 %, on the pixels by the root of their number: 2 %.)"""
+    rng = np.random.default_rng(2)
+    total, ref = np.zeros(samples, np.float32), np.zeros(samples)
+    for w in K.reshape(channels, -1):
+        x = rng.standard_normal((w.size, samples)).astype(np.float32)
+        parts = [np.zeros(samples, np.float32) for _ in range(lanes)]
+        for t in range(w.size):
+            parts[t % lanes] = (np.float64(w[t]) * x[t] + parts[t % lanes]).astype(np.float32)
+        while len(parts) > 1:
+            parts = [a + b for a, b in zip(parts[::2], parts[1::2])]
+        total = total + parts[0]
+        ref = ref + w.astype(np.float64) @ x
+    return np.linalg.norm(total - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("shape,channels,batch,lanes", [     # lanes: k * k taps, at most 8 in a chain
+    ((300, 300, 3, 1, 1), 64, 1, 2), ((300, 300, 2, 1, 0), 100, 2, 1), ((200, 180, 9, 1, 4), 16, 5, 16), ((200, 180, 7, 1, 3), 24, 3, 8),
+    ((100, 90, 5, 1, 2), 20, 10, 4), ((200, 180, 11, 1, 5), 16, 1, 16), ((30, 40, 3, 1, 1), 120, 6, 2),
+])
+def test_channel_sums_in_row_groups_are_as_exact_as_a_launch_per_channel(shape, channels, batch, lanes):
+    """All channels in one launch of the row groups: within 5 % (the scatter of the samples) of the
+    error of a launch per channel; one chain per lane through all channels is up to twice as far off."""
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(channels)
+    K = rng.standard_normal(channels * k * k).astype(np.float32)
+    x = rng.standard_normal(channels * m * n * batch).astype(np.float32)
+    plan = cs.conv_compact_build(*shape, torch.from_numpy(K).to(device()), channels=channels)
+    assert plan.variant(batch).startswith("compact_gather_"), plan.variant(batch)
+    y = cs.conv_spmv(plan, torch.from_numpy(x).to(device()), batch=batch)
+    torch.cuda.synchronize()
+    ref, scale = oracle.conv_channels(m, n, k, s, p, x, K, channels, batch=batch, want_scale=True)
+    got = y.cpu().numpy()
+    _check(got, ref, scale, (shape, batch))
+    ref = ref.astype(np.float64)
+    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 1.05 * _launch_per_channel_error(K, channels, lanes)
     plan.close()
 
 

@@ -203,9 +203,11 @@ class ConvPlan:
     def __init__(self, handle, shape, out_shape, nnz, row_ptr, col_idx, vals, kernel, transposed=False):
         self._handle = handle
         # The arrays are given back to torch's caching allocator in the order of the stream that was
-        # current when they were allocated; work on any other stream is waited for before (close).
+        # current when they were allocated.  close() can leave the device alone where that is the default
+        # stream and the plan was used on it only: that stream is never captured, so no graph can be
+        # replaying work on the plan elsewhere.  Everything else is waited for.
         self._home = torch._C._cuda_getCurrentRawStream(kernel.device.index)
-        self._elsewhere = False
+        self._elsewhere = self._home != 0
         self.transposed = transposed    # the arrays hold T^T (CSC of T): row_ptr is col_ptr, col_idx is row_idx
         self.m, self.n, self.k, self.s, self.p = shape
         self.m_out, self.n_out = out_shape
@@ -244,6 +246,8 @@ class ConvPlan:
         if self._handle is not None:
             if self._elsewhere:
                 torch.cuda.synchronize()
+            else:      # the caller's K may be from another stream's pool: not to be handed out before this stream has read it
+                self._kernel.record_stream(torch.cuda.default_stream(self._kernel.device))
             _load().conv_plan_destroy(self._handle)
             self._handle = None
 

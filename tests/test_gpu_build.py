@@ -61,8 +61,11 @@ def test_sweep_at_batches_in_chunks(batch):
         pl.close()
 
 
+SPIN = 20_000_000       # clock ticks of a waiting kernel: milliseconds, while the host goes on
+
+
 def test_a_dropped_plan_waits_for_work_on_another_stream():
-    """close() leaves the device alone when the plan was used on its own stream only, and waits for
+    """close() leaves the device alone when the plan was used on the default stream only, and waits for
     it when it was used on another (its arrays could be handed out again while they are read)."""
     K = torch.ones(9, device=device())
     plan = cs.conv_csr_build(64, 64, 3, 1, 1, K)
@@ -72,7 +75,55 @@ def test_a_dropped_plan_waits_for_work_on_another_stream():
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     y = torch.empty(plan.rows, device=device())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(SPIN)
     cs.conv_spmv(plan, x, y, stream=side)
-    assert plan._elsewhere
+    assert plan._elsewhere and not side.query()
     plan.close()
     assert side.query()
+
+
+@pytest.mark.parametrize("how", ["built", "replayed"])
+def test_a_dropped_plan_of_a_side_stream_waits(how):
+    """A plan built on a side stream reads a kernel that another stream's pool may get back, and a graph
+    captured on that stream runs wherever it is replayed: close() waits for both."""
+    K = torch.ones(9, device=device())
+    x, y = torch.ones(64 * 64, device=device()), torch.empty(64 * 64, device=device())
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        if how == "built":
+            torch.cuda._sleep(SPIN)
+        plan = cs.conv_csr_build(64, 64, 3, 1, 1, K)
+    busy = side
+    if how == "replayed":
+        cs.conv_spmv(plan, x, y, stream=side)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            cs.conv_spmv(plan, x, y)
+        torch.cuda.synchronize()
+        busy = torch.cuda.current_stream()
+        torch.cuda._sleep(SPIN)
+        graph.replay()
+    assert not busy.query()
+    plan.close()
+    assert busy.query()
+
+
+def test_a_kernel_of_another_streams_pool_outlives_the_build():
+    """Built on the default stream from a kernel that was allocated on another: its memory is not handed
+    out again before the build has read it, though the plan and the kernel are dropped at once."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        K = torch.ones(9, device=device())
+    torch.cuda.synchronize()
+    place = K.data_ptr()
+    torch.cuda._sleep(SPIN)
+    plan = cs.conv_csr_build(64, 64, 3, 1, 1, K)
+    plan.close()
+    del plan, K
+    with torch.cuda.stream(side):
+        again = torch.empty(9, device=device())
+        reused = again.data_ptr() == place
+    assert torch.cuda.default_stream().query() or not reused

@@ -8,6 +8,7 @@ fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -164,6 +165,11 @@ def _stream_handle(stream, device_index):
     return torch._C._cuda_getCurrentRawStream(device_index) if stream is None else stream.cuda_stream
 
 
+@functools.lru_cache(maxsize=None)
+def _default_stream(device):
+    return torch.cuda.default_stream(device)
+
+
 class _OnDevice:
     """`with torch.cuda.device(index)` that costs nothing when the device is current already."""
     __slots__ = ("index", "before")
@@ -247,7 +253,7 @@ class ConvPlan:
             if self._elsewhere:
                 torch.cuda.synchronize()
             else:      # the caller's K may be from another stream's pool: not to be handed out before this stream has read it
-                self._kernel.record_stream(torch.cuda.default_stream(self._kernel.device))
+                self._kernel.record_stream(_default_stream(self._kernel.device))
             _load().conv_plan_destroy(self._handle)
             self._handle = None
 

@@ -29,8 +29,9 @@ struct ChannelStrides {
     long long vals, x;
 };
 
-// A lane's entries first, first + step, ... below `end`, summed in that order onto acc.  U steps at a
-// time: their column indices and values are asked for together, then their operands, so that a row costs two
+// A lane's entries first, first + step, ... below `end`, summed in that order onto acc.  (Entry numbers
+// reach 2^31 - 1, and a step past the end of the last rows more: they are unsigned.)
+// U steps at a time: their column indices and values are asked for together, then their operands, so that a row costs two
 // round trips to memory per U entries of a lane and not two per entry (32 x 32, k 3, batch 1: 3.3 -> 2.9 us).
 // A step past the end reads the last entry again and leaves the sum alone.  Launches with waves enough
 // to hide the round trips do better one entry at a time (1254 x 1457, k 3, s 4, batch 1: 4.6 us, 5.6 four at a time;
@@ -38,14 +39,14 @@ struct ChannelStrides {
 constexpr int kGatherAhead = 5;      // (rows of 9 entries, two lanes: all of a lane's)
 
 template <int U, typename Operand>
-__device__ __forceinline__ float row_entries(int first, int end, int step, const int *col_idx, const float *vals,
-                                             Operand &&operand, float acc) {
-    for (int e = first; e < end; e += U * step) {
+__device__ __forceinline__ float row_entries(unsigned first, unsigned end, unsigned step, const int *col_idx,
+                                             const float *vals, Operand &&operand, float acc) {
+    for (unsigned e = first; e < end; e += U * step) {
         int col[U];
         float val[U], xv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int at = min(e + u * step, end - 1);
+            const unsigned at = min(e + u * step, end - 1);
             col[u] = col_idx[at];
             val[u] = vals[at];
         }
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_gather_scalar_kernel(
     const float *__restrict__ x, float *__restrict__ y, int rows, int batch, ChannelStrides cs) {
     const long long row = ((long long)blockIdx.x * kGatherThreads + threadIdx.x) / G;
     const int lane = (int)threadIdx.x % G;
-    int beg = 0, end = 0;
+    unsigned beg = 0, end = 0;
     if (row < rows) {
         beg = row_ptr[row];
         end = row_ptr[row + 1];
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_gather_vec_kernel(
     const float *__restrict__ x, float *__restrict__ y, int rows, int batch, ChannelStrides cs) {
     const long long row = ((long long)blockIdx.x * kGatherThreads + threadIdx.x) / G;
     const int lane = (int)threadIdx.x % G;
-    int beg = 0, end = 0;
+    unsigned beg = 0, end = 0;
     if (row < rows) {
         beg = row_ptr[row];
         end = row_ptr[row + 1];
@@ -118,13 +119,13 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_gather_vec_kernel(
         if (cs.channels == 1) {
             // (the entries of U steps, then their pixels, then the sums: see row_entries)
             constexpr int U = AHEAD ? (NV == 4 ? 2 : 4) : 1;
-            for (int e = beg + lane; e < end; e += U * G) {
+            for (unsigned e = beg + lane; e < end; e += U * G) {
                 int col[U];
                 float val[U];
                 float4 px[U][NV];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int at = min(e + u * G, end - 1);
+                    const unsigned at = min(e + u * G, end - 1);
                     col[u] = col_idx[at];
                     val[u] = vals[at];
                 }
@@ -204,10 +205,10 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_scatter_kernel(
     const long long col = ((long long)blockIdx.x * kGatherThreads + threadIdx.x) / (G * BL);
     const int r = (int)threadIdx.x % (G * BL), lane = r / BL, bl = r % BL;
     if (col >= cols) return;
-    const int beg = col_ptr[col], end = col_ptr[col + 1];
+    const unsigned beg = col_ptr[col], end = col_ptr[col + 1];
     for (int c = blockIdx.y * BL + bl; c < batch; c += gridDim.y * BL) {
         const float xv = x[col * batch + c];
-        for (int e = beg + lane; e < end; e += G)
+        for (unsigned e = beg + lane; e < end; e += G)
             unsafeAtomicAdd(y + (long long)row_idx[e] * batch + c, vals[e] * xv);
     }
 }
@@ -494,7 +495,7 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_multi_kernel(const MultiD
     const int gs = d.g_shift, G = 1 << gs;
     const long long row = ((long long)(blockIdx.x - d.first_block) * kGatherThreads + threadIdx.x) >> gs;
     const int lane = (int)threadIdx.x & (G - 1);
-    int beg = 0, end = 0;
+    unsigned beg = 0, end = 0;
     if (row < d.rows) {
         beg = d.row_ptr[row];
         end = d.row_ptr[row + 1];
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_multi_kernel(const MultiD
             float4 acc[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int e = beg + lane; e < end; e += G) {
+            for (unsigned e = beg + lane; e < end; e += G) {
                 const float w = d.vals[e];
                 const float *xr = d.x + (long long)d.col_idx[e] * batch;
 #pragma unroll

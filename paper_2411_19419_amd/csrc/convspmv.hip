@@ -1072,6 +1072,7 @@ static CscTileChoice choose_csc_tile(const conv_plan *plan, int batch) {
     g.column_max = (int)std::min<int64_t>(column_max, kCscStage);
     g.spacing = sh.k;
     g.group = g.column_max <= kCscGroupColumn ? kWave / g.column_max : 1;
+    if (plan->nnz > kInt32Limit - 2 * kWave) return c;       // the kernel steps a wave past the last entry, in int
     if (column_max > kCscStage || column_max < (batch >= 4 ? kCscTileShortestColumn : kCscTileShortColumn)) return c;
     const int tj_max = (int)std::min<int64_t>(32, kCscStage / column_max);
     double best = 0.0;

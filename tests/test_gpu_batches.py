@@ -258,3 +258,48 @@ def test_pushed_lines_at_the_edges(k, s):
         else:
             _check(got, *oracle.conv(m, n, k, s, p, x, K, batch=batch, want_scale=True), (shape, batch))
         plan.close()
+
+
+def test_rows_at_the_last_entry_numbers():
+    """2^31 - 2 entries: the row groups step past the end of the last rows, up to 80 entries at once, where an
+    entry number would leave the range of int.  The last output lines against sums in 64 bits."""
+    m, n, k, s, p = shape = (3425, 7756, 9, 1, 2)
+    assert cs.conv_nnz(*shape) == 2 ** 31 - 2
+    mo, no = cs.conv_out_shape(*shape)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K = torch.randn(k * k, device=device(), generator=g)
+
+    def last_lines(x, batch, lines=6):         # of y = T x
+        pad = torch.zeros(m + 2 * p - (mo - lines), n + 2 * p, batch, dtype=torch.float64, device=device())
+        pad[:-p, p:-p] = x.view(m, n, batch)[mo - lines - p:].double()
+        y, scale = (torch.zeros(lines, no, batch, dtype=torch.float64, device=device()) for _ in range(2))
+        for a in range(k):
+            for b in range(k):
+                y += K[a * k + b].double() * pad[a:a + lines, b:b + no]
+                scale += K[a * k + b].double().abs() * pad[a:a + lines, b:b + no].abs()
+        return y.reshape(-1), scale.reshape(-1)
+
+    def check(y, x, batch, what):
+        ref, scale = last_lines(x, batch)
+        assert not bool(torch.isnan(y).any()), what
+        assert bool(((y[-ref.numel():].double() - ref).abs() <= REL_TOL * scale).all()), what
+
+    plan = cs.conv_csr_build(*shape, K)
+    for batch in (1, 4):
+        x = torch.randn(m * n * batch, device=device(), generator=g)
+        y = torch.full((plan.rows * batch,), float("nan"), device=device())
+        multi = cs.ConvMulti([plan], [x], [y], batch=batch)
+        multi.apply()
+        check(y, x, batch, ("multi", batch))
+        multi.close()
+    plan.close()
+    del plan, multi
+    torch.cuda.empty_cache()
+    plan = cs.conv_csc_build(*shape, K)
+    x = torch.randn(m * n, device=device(), generator=g)
+    y = torch.full((plan.cols,), float("nan"), device=device())
+    cs.conv_spmv_from_csc(plan, x, y)
+    check(y, x, 1, "from csc")
+    plan.close()
+    del plan
+    torch.cuda.empty_cache()

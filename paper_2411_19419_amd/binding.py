@@ -12,12 +12,32 @@ import functools
 import os
 import threading
 
-import torch
-
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIBNAME = "libconvspmv.so"
 _lock = threading.Lock()
 _lib = None
+
+
+class _Torch:
+    """Stands in for torch until a call needs it: callers of the host functions need not have it."""
+
+    def __getattr__(self, name):
+        import torch as loaded
+        globals()["torch"] = loaded
+        globals()["_raw_stream"], globals()["_current_device"] = _device_queries(loaded)
+        return getattr(loaded, name)
+
+
+def _device_queries(loaded):
+    """Handle of the current stream of a device, and the current device's index.  The public calls build a
+    Stream object and check the initialisation (1.5 and 0.2 us); where this torch has the calls below them, those."""
+    c = loaded._C
+    return (getattr(c, "_cuda_getCurrentRawStream", None) or (lambda index: loaded.cuda.current_stream(index).cuda_stream),
+            getattr(c, "_cuda_getDevice", None) or loaded.cuda.current_device)
+
+
+torch = _Torch()
+_raw_stream = _current_device = None       # set with torch
 
 EXPORTS = (
     "conv_out_shape", "conv_nnz", "conv_csr_build", "conv_spmv", "conv_plan_shape",
@@ -162,7 +182,7 @@ def conv_nnz(m, n, k, s, p) -> int:
 
 def _stream_handle(stream, device_index):
     """Raw handle of `stream`, or of torch's current stream on that device."""
-    return torch._C._cuda_getCurrentRawStream(device_index) if stream is None else stream.cuda_stream
+    return _raw_stream(device_index) if stream is None else stream.cuda_stream
 
 
 @functools.lru_cache(maxsize=None)
@@ -178,7 +198,7 @@ class _OnDevice:
         self.index = index
 
     def __enter__(self):
-        self.before = torch._C._cuda_getDevice()
+        self.before = _current_device()
         if self.before != self.index:
             torch.cuda.set_device(self.index)
 
@@ -187,8 +207,8 @@ class _OnDevice:
             torch.cuda.set_device(self.before)
 
 
-def _is_operand(t, dtype=torch.float32):
-    return t.is_cuda and t.dtype is dtype and t.is_contiguous()
+def _is_operand(t):
+    return t.is_cuda and t.dtype is torch.float32 and t.is_contiguous()
 
 
 def _on_stream(stream, *tensors):
@@ -212,7 +232,7 @@ class ConvPlan:
         # current when they were allocated.  close() can leave the device alone where that is the default
         # stream and the plan was used on it only: that stream is never captured, so no graph can be
         # replaying work on the plan elsewhere.  Everything else is waited for.
-        self._home = torch._C._cuda_getCurrentRawStream(kernel.device.index)
+        self._home = _raw_stream(kernel.device.index)
         self._elsewhere = self._home != 0
         self.transposed = transposed    # the arrays hold T^T (CSC of T): row_ptr is col_ptr, col_idx is row_idx
         self.m, self.n, self.k, self.s, self.p = shape
@@ -462,7 +482,7 @@ class ConvMulti:
         self.batch = batch
 
     def apply(self, stream=None):
-        sh = _stream_handle(stream, torch._C._cuda_getDevice())
+        sh = _stream_handle(stream, _current_device())
         st = _load().conv_multi_apply(self._handle, sh)
         if st != 0:
             raise ConvError(st, "conv_multi_apply")

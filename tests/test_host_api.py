@@ -5,6 +5,9 @@ import ctypes
 import itertools
 import os
 import re
+import subprocess
+import sys
+import types
 
 import numpy as np
 import pytest
@@ -393,3 +396,19 @@ def test_dispatch_of_the_named_workloads():
                 (300, 300, 256, 1, 0, 1, 2, 1)]:
         with pytest.raises(cs.ConvError):
             cs.conv_dispatch_info(*bad)
+
+
+def test_host_functions_need_no_torch():
+    """conv_nnz and the other host functions, in a process where torch cannot be imported."""
+    code = ("import sys; sys.modules['torch'] = None; import paper_2411_19419_amd as cs; "
+            "assert cs.conv_nnz(32, 32, 3, 1, 1) == 8836 and cs.conv_out_shape(32, 32, 3, 1, 1) == (32, 32); "
+            "assert cs.conv_dispatch_info(32, 32, 3, 1, 1, 1).workgroups > 0 and cs.conv_strerror(0) == 'ok'")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+
+
+def test_device_queries_without_the_internal_calls():
+    """A torch without the two internal calls: the public ones answer."""
+    stub = types.SimpleNamespace(_C=types.SimpleNamespace(), cuda=types.SimpleNamespace(
+        current_stream=lambda index: types.SimpleNamespace(cuda_stream=70 + index), current_device=lambda: 3))
+    raw_stream, current_device = binding._device_queries(stub)
+    assert raw_stream(2) == 72 and current_device() == 3

@@ -379,11 +379,29 @@ constexpr int64_t kTileMinBlocks = 512;
 // of single products rounds more often than the chain it replaces; 198 x 128, k 4, s 3, batch 64: 7.0 and
 // 4.6), columns per lane halved below the second (148 x 195, k 4, s 2, batch 64, 2 lanes per row:
 // 225 workgroups of 16 columns 9 us, 900 of 4 columns 18.6).
-constexpr int64_t kRowGroupWiden = 512, kRowGroupMinBlocks = 128;
+// Long rows want them narrower earlier (25 x 35, k 13, batch 36: 6.4 us with 16 columns, 4.8 with 4; short ones do not:
+// 426 x 303, k 1, batch 24: 2.4 and 3.3; nor at large strides, where a narrow lane wastes more of the
+// memory lines it reads: 236 x 249, k 5, s 4, batch 24: 4.4 and 7.2).
+constexpr int64_t kRowGroupWiden = 512;
+constexpr int64_t row_group_min_blocks(int64_t entries, int s) { return s <= 3 && entries >= 25 * s ? 384 : 128; }
 // Multiply-adds below which the row groups beat the tile kernel's staging and barrier (76 x 48,
 // k 3, batch 32, 1.0 M: 3.8 us against 4.9; 75 x 87, k 6, batch 16, 3.7 M: 4.5 against 5.4; above it
 // 88 x 67, k 7, batch 32, 8.8 M: 7.7 against 6.4; 194 x 137, k 7, s 2, batch 32, 10 M: 9.2 against 6.6).
 constexpr int64_t kTileMinWork = 3500000;
+// T^T, whose tiles find their window by divisions: more (197 x 202, k 3, batch 4, 1.4 M: 4.2 us, row groups 3.2;
+// 267 x 383, k 3, batch 4, 3.7 M: 5.4 and 4.4; 500 x 450, k 3, batch 8, 16 M: 7.1 and 9.8), unless every
+// lane has its 16 columns (168 x 177, k 3, batch 32, 8.5 M: 5.9 and 8.2).  At strides above 1 its rows differ in
+// length, so that lanes idle, and its results leave in pieces of memory lines: full lanes, or rows of 9 entries and
+// more at batches up to 16 or where the operands exceed the last-level cache (340 x 367, k 3, s 2, batch 168:
+// 119 us, row groups 61; batch 160: 27 and 45; 881 x 1143, k 5, s 4, batch 40: 224 and 95).
+constexpr double kTileMinWorkT = 12e6, kTileMinBytesT = 200e6;
+bool tile_serves_t(const conv_plan *plan, int batch) {
+    const double work = (double)plan->nnz * batch, bytes = 4.0 * (double)(plan->rows + plan->cols) * batch;
+    if (plan->max_row_nnz < 4) return false;       // an entry or two: nothing to share (763 x 1019, k 2, s 4, batch 212: 1085 us, row groups 649)
+    if (batch % 16 == 0) return work >= kTileMinWork;
+    if (plan->shape.s > 1 && (plan->max_row_nnz < 9 || (batch > 16 && bytes < kTileMinBytesT))) return false;
+    return work >= kTileMinWorkT;
+}
 
 int round_up_mod(int v, int mod, int rem) {      // smallest r >= v with r % mod == rem
     int r = v - (v % mod) + rem;
@@ -392,7 +410,8 @@ int round_up_mod(int v, int mod, int rem) {      // smallest r >= v with r % mod
 
 // Geometry of a tile kernel launch: the widest line pitch rule and the most
 // output lines per tile whose input window still fits one LDS plane.
-bool tile_geometry(const conv_plan *plan, int batch, int tw, int plane, int col_blocks, int rows_per_pass, TileGeom *out) {
+// *most: tiles there would be with the lowest tile lines it would try for more workgroups.
+bool tile_geometry(const conv_plan *plan, int batch, int tw, int plane, int col_blocks, int rows_per_pass, TileGeom *out, int64_t *most) {
     const ConvShape &sh = plan->shape;
     const bool tr = plan->transposed;
     TileGeom g{};
@@ -419,10 +438,15 @@ bool tile_geometry(const conv_plan *plan, int batch, int tw, int plane, int col_
     int64_t th = std::max<int64_t>(results(ih_max), 1);
     if (th > 8) th = 8;
     if (th > g.m_out) th = g.m_out;
-    // a small plane: lower tiles, down to one pass per wave, until there are workgroups for the chip
+    // a small plane: lower tiles, down to one pass per wave, until there are workgroups for the chip (but not
+    // more than it holds at a time, two per compute unit: 413 x 252, k 2, batch 32: 416 workgroups 8.8 us, 552 11.3)
     g.tiles_x = (g.n_out + tw - 1) / tw;
     const int64_t th_min = (int64_t)(tw * 8 / kWave) * rows_per_pass / tw;
-    while (th > 1 && th > th_min && (g.m_out + th - 1) / th * g.tiles_x * col_blocks < kTileMinBlocks) --th;
+    auto tiles = [&](int64_t lines) { return (g.m_out + lines - 1) / lines * g.tiles_x * col_blocks; };
+    int64_t low = th;
+    while (low > 1 && low > th_min && tiles(low) < kTileMinBlocks) --low;
+    while (th > low && tiles(th - 1) <= kTileMinBlocks) --th;
+    *most = tiles(low) / col_blocks;
     const int64_t ih = extent(th);
     g.th = (int)th;
     g.ih = (int)ih;
@@ -628,7 +652,7 @@ ApplyChoice choose_apply(const conv_plan *full, int batch) {
     auto row_blocks = [&] { return (plan->rows * c.g + kGatherThreads - 1) / kGatherThreads; };
     const int64_t row_max = (int64_t)plan->max_row_nnz * full->channels;
     while (c.g < 16 && 6 * c.g <= row_max && row_blocks() * column_blocks(batch, c.nv) < kRowGroupWiden) c.g *= 2;
-    while (c.nv > 1 && row_blocks() * column_blocks(batch, c.nv) < kRowGroupMinBlocks) c.nv /= 2;
+    while (c.nv > 1 && row_blocks() * column_blocks(batch, c.nv) < row_group_min_blocks(full->channels > 1 ? 1 : row_max, plan->shape.s)) c.nv /= 2;
     if (plan->nnz == 0 || column_blocks(batch, nv_hi) > 65535) return c;
 
     // marching kernels: float4 column chunks, or scalar columns
@@ -651,34 +675,49 @@ ApplyChoice choose_apply(const conv_plan *full, int batch) {
         c.march = mg;
         return c;
     };
+    // Batches of 2 and 3 go column by column and read the entries again for each.  Sums over channels, and T^T at
+    // strides above 1 with rows of up to 16 entries, are left to the row groups (247 x 335, k 4, 4 channels,
+    // batch 3: 56 us, row groups 29; 196 x 273, k 11, s 3, T^T, batch 3: 18 and 7).  (Not where the plan's threshold, a test hook, is lowered.)
+    const bool scalar_columns = !vec && batch > 1;
+    const bool marches = !scalar_columns || full->march_min_jobs < kMarchMinJobs ||
+                         !(full->channels > 1 || (plan->transposed && plan->shape.s > 1 && plan->max_row_nnz <= 16));
     // all channels in one launch (lanes of 16 or 4 columns)
-    if (full->channels > 1 && stage_shape(plan->max_row_nnz, &ss))
+    if (marches && full->channels > 1 && stage_shape(plan->max_row_nnz, &ss))
         for (int nv = nv_hi;; nv = nv_lo) {
             const int nvc = nv == 2 ? 1 : nv;
             if (stage_march_geometry(plan, batch, nvc, full->channels, ss, &mg, &wl)) return staged(nvc);
             if (nv == nv_lo) break;
         }
-    for (int nv = nv_hi;; nv /= 2) {
-        if (stage_shape(plan->max_row_nnz, &ss) && stage_march_geometry(plan, batch, nv, 1, ss, &mg, &wl)) return staged(nv);
-        if (march_shape(plan->max_row_nnz, &ms) && march_geometry(plan, batch, nv, ms.tw, &mg, &ls, &nl)) {
-            c.kind = Kind::March;
-            c.nv = nv;
-            c.g = ms.g;
-            c.nit = ms.nit;
-            c.tw = ms.tw;
-            c.threads = kMarchThreads;
-            c.lds = nv ? (size_t)nv * march_plane(nv) * 16 : (size_t)march_plane(0) * 4;
-            c.ls = ls;
-            c.nl = nl;
-            c.march = mg;
-            return c;
-        }
+    auto march = [&](int nv) {
+        if (!march_shape(plan->max_row_nnz, &ms) || !march_geometry(plan, batch, nv, ms.tw, &mg, &ls, &nl)) return false;
+        c.kind = Kind::March;
+        c.nv = nv;
+        c.g = ms.g;
+        c.nit = ms.nit;
+        c.tw = ms.tw;
+        c.threads = kMarchThreads;
+        c.lds = nv ? (size_t)nv * march_plane(nv) * 16 : (size_t)march_plane(0) * 4;
+        c.ls = ls;
+        c.nl = nl;
+        c.march = mg;
+        return true;
+    };
+    for (int nv = nv_hi; marches; nv /= 2) {
+        const bool stages = stage_shape(plan->max_row_nnz, &ss) && stage_march_geometry(plan, batch, nv, 1, ss, &mg, &wl);
+        // Ragged lanes of long rows: the other marching kernel, whose lanes sum 8 entries and need no sums in
+        // blocks (FINE), 0.6 to 0.8 of the staged one's time from 64 entries on (393 x 379, k 11, batch 40: 196 and 87
+        // us; shorter rows 0.8 to 1.2).  Scalar columns likewise, but for rows of 25 entries (812 x 521, k 8,
+        // batch 3: 343 us, row groups 144; 477 x 694, k 8, batch 3: 150, here 95).
+        const bool other_first = scalar_columns ? plan->max_row_nnz != 25
+                                                : stages && nv && batch % (4 * nv) != 0 && plan->max_row_nnz >= 64 && mg.seg >= 4 * wl;
+        const MarchGeom staged_geom = mg;
+        if (other_first && march(nv)) return c;
+        mg = staged_geom;
+        if (stages) return staged(nv);
+        if (march(nv)) return c;
         if (nv <= nv_lo) break;
     }
-    if (!vec || plan->nnz * batch < kTileMinWork) return c;
-    // T^T whose rows have an entry or two has nothing to share through LDS (763 x 1019, k 2, s 4,
-    // batch 212: tile kernel 1085 us, row groups 649)
-    if (plan->transposed && plan->max_row_nnz < 4) return c;
+    if (!vec || !(plan->transposed ? tile_serves_t(plan, batch) : plan->nnz * batch >= kTileMinWork)) return c;
     // A multi-channel sum through the LDS kernels is one launch per channel.  That pays for the
     // marching kernel (large problems); the problems the tile kernel takes are small, and the
     // row-group kernels, which walk the channels inside one launch, measured 3x faster there.
@@ -701,11 +740,12 @@ ApplyChoice choose_apply(const conv_plan *full, int batch) {
     const int tws[2] = {kTileWide, kTileNarrow}, planes[2] = {kPlaneWide, kPlaneNarrow};
     for (int i = 0; i < 2; ++i) {
         TileGeom g;
+        int64_t most = 0;
         if ((plan->transposed ? plan->shape.n : plan->shape.n_out) <= kTileNarrow && tws[i] == kTileWide) continue;
-        if (!tile_geometry(plan, batch, tws[i], planes[i], column_blocks(batch, nv_hi), kWave / tile_g, &g)) continue;
+        if (!tile_geometry(plan, batch, tws[i], planes[i], column_blocks(batch, nv_hi), kWave / tile_g, &g, &most)) continue;
         c.kind = Kind::Tile;
         c.nv = nv_hi;
-        while (c.nv > nv_lo && (int64_t)g.n_tiles * column_blocks(batch, c.nv) < kTileMinBlocks) c.nv /= 2;
+        while (c.nv > nv_lo && most * column_blocks(batch, c.nv) < kTileMinBlocks) c.nv /= 2;
         c.g = tile_g;
         c.nit = nit;
         c.tw = tws[i];

@@ -260,6 +260,30 @@ def test_pushed_lines_at_the_edges(k, s):
         plan.close()
 
 
+@pytest.mark.parametrize("kind,shape,batch,channels,want", [
+    ("csr", (393, 379, 11, 1, 0), 40, 1, "lds_march_28x32"), ("csr", (477, 694, 8, 1, 0), 3, 1, "lds_march_"),
+    ("csr", (413, 252, 2, 1, 0), 32, 1, "lds_tile_7x64"), ("csr", (247, 335, 4, 1, 2), 3, 4, "gather_"),
+    ("csc", (340, 367, 3, 2, 1), 160, 1, "lds_tile_"), ("csc", (340, 367, 3, 2, 1), 40, 1, "gather_"),
+])
+def test_products_on_both_sides_of_the_dispatch_rules(kind, shape, batch, channels, want):
+    """Lanes, kernels and tiles that the default dispatch gives shapes of ordinary size."""
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(29)
+    K = rng.standard_normal(channels * k * k).astype(np.float32)
+    Kd = torch.from_numpy(K).to(device())
+    plan = (cs.conv_compact_build(*shape, Kd, channels=channels) if kind == "compact" else cs.conv_csc_build(*shape, Kd)
+            if kind == "csc" else cs.conv_csr_build_channels(*shape, Kd, channels))
+    assert want in plan.variant(batch), plan.variant(batch)
+    x = rng.standard_normal(plan.cols * batch).astype(np.float32)
+    y = torch.full((plan.rows * batch,), float("nan"), dtype=torch.float32, device=device())
+    cs.conv_spmv(plan, torch.from_numpy(x).to(device()), y, batch=batch)
+    torch.cuda.synchronize()
+    ref = (oracle.conv_t(m, n, k, s, p, x, K, batch=batch, want_scale=True) if kind == "csc" else
+           oracle.conv_channels(m, n, k, s, p, x, K, channels, batch=batch, want_scale=True))
+    _check(y.cpu().numpy(), *ref, (kind, shape, batch))
+    plan.close()
+
+
 def test_rows_at_the_last_entry_numbers():
     """2^31 - 2 entries: the row groups step past the end of the last rows, up to 80 entries at once, where an
     entry number would leave the range of int.  The last output lines against sums in 64 bits."""

@@ -412,3 +412,19 @@ def test_device_queries_without_the_internal_calls():
         current_stream=lambda index: types.SimpleNamespace(cuda_stream=70 + index), current_device=lambda: 3))
     raw_stream, current_device = binding._device_queries(stub)
     assert raw_stream(2) == 72 and current_device() == 3
+
+
+@pytest.mark.parametrize("shape,batch,storage,channels,kernel,columns", [
+    # T^T: the tile kernel with full lanes, or rows of 9 entries at small batches
+    ((340, 367, 3, 2, 1), 168, 1, 1, 1, 16), ((340, 367, 3, 2, 1), 160, 1, 1, 2, 16), ((881, 1143, 5, 4, 2), 40, 1, 1, 1, 16),
+    ((256, 256, 5, 2, 2), 64, 1, 1, 2, 16), ((267, 383, 3, 1, 1), 4, 1, 1, 1, 4), ((500, 450, 3, 1, 1), 8, 1, 1, 2, 8),
+    # batches of 2 and 3 column by column
+    ((812, 521, 8, 1, 7), 3, 0, 1, 3, 1), ((196, 273, 11, 3, 5), 3, 1, 1, 0, 1), ((247, 335, 4, 1, 2), 3, 0, 4, 0, 1),
+    # ragged lanes of long rows; long rows on a small plane
+    ((393, 379, 11, 1, 0), 40, 0, 1, 3, 16), ((25, 35, 13, 1, 6), 36, 0, 1, 1, 4), ((236, 249, 5, 4, 0), 24, 0, 1, 1, 16),
+])
+def test_dispatch_keeps_to_the_faster_kernel(shape, batch, storage, channels, kernel, columns):
+    """Shapes on both sides of the dispatch rules, each with the kernel that measured faster there by 15 %
+    to several times."""
+    d = _dispatch(*shape, batch, storage, channels)
+    assert d["kernel"] == kernel and columns in (None, d["columns_per_lane"]), d

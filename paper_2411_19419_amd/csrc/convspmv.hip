@@ -806,9 +806,21 @@ constexpr int64_t kChanFusedWaves = 2048;     // waves that fill the chip (8 per
 // the kernel is compiled for.
 constexpr int kPushMaxLines = 13;
 constexpr int64_t kPushTargetWaves = 2048;    // two waves per SIMD
-// Fewer waves: row groups (401 x 562, k 11, batch 4: 468 waves 45 us, row groups 30; 1185 x 1424, k 6,
-// s 3, batch 1: 800 waves 13.8 and 9.4; 229 x 281, k 2, batch 16: 1080 waves 8.1 and 9.7).
-constexpr int64_t kPushMinWaves = 1024;
+// Waves that a launch of it needs.  Fewer: row groups or the marching kernel (401 x 562, k 11, batch 4: 468
+// waves 45 us, row groups 30; 1185 x 1424, k 6, s 3, batch 1: 800 waves 13.8 and 9.4).  Small kernels need more, as a
+// wave walks every line and every column of the image for a few taps of each (843 x 1177, k 4, s 2, batch 1:
+// 1100 waves 10.4 us, row groups 5.7).
+constexpr int64_t push_min_waves(int k, bool scalar) { return scalar ? (k <= 5 ? 1792 : 1024) : (k <= 3 ? 1536 : 1024); }
+// ... and with fewer taps than this it loses to the row groups at any size (966 x 1156, k 1, s 2, batch 1: 7.0 and
+// 2.6 us; 2602 x 2660, k 3, s 4, batch 1: 13 and 7; 1126 x 1766, k 1, s 2, batch 4: 9.9 and 4.2; k 2, s 4, batches of 9 to
+// 190: 1.5 to 2.8 times; but k 2, s 1, batches of 20 and more: mostly 0.6 to 0.9, k 3, s 3: 0.55 to 0.8).
+constexpr bool push_taps(int k, int s, int batch) {
+    return k > 3 || (batch > 12 && (k == 3 || (k == 2 && s == 1)));
+}
+// With more output lines in flight than this, at 4 columns per lane, its multiply-adds are the bound and
+// the marching kernel, which reads LDS as often, does the fewer of them (434 x 289, k 13, batch 12: 118 and 37 us;
+// 420 x 582, k 11, batch 16: 88 and 61).
+constexpr int kPushFewLines = 10;
 // output lines per wave, at least: each part loads k - s input lines of its neighbour's again (547 x 374,
 // k 5, s 3, batch 44: 24 us with parts of 8, 18 of 4; 4096^2, k 11, s 4, batch 4: 66 and 80)
 constexpr int push_min_part(int k, int s) { return k <= 2 * s ? 4 : 8; }
@@ -839,12 +851,12 @@ bool push_geometry(const conv_plan *plan, int batch, bool scalar, int lpr, unsig
     return true;
 }
 
-CompactChoice choose_compact(const conv_plan *plan, int batch) {
+// The marching launch (rectangle or described path) with lanes of 4 lpr batch columns, or of one.
+bool compact_march(const conv_plan *plan, int batch, bool scalar, int lpr, CompactChoice *out) {
     const ConvShape &sh = plan->shape;
     CompactChoice c{};
-    // chunks of four columns (chunk_col); a launch per channel adds to y, where a column must not be in two chunks
-    c.scalar = batch < 4 || (plan->channels > 1 && batch % 4 != 0);
-    c.lpr = c.scalar ? 1 : widest_nv(batch);
+    c.scalar = scalar;
+    c.lpr = lpr;
     const int eb = c.scalar ? 4 : 16;
     c.col_blocks = (unsigned)column_blocks(batch, c.scalar ? 0 : c.lpr);
     int tw = kCompactThreads / c.lpr;
@@ -853,7 +865,7 @@ CompactChoice choose_compact(const conv_plan *plan, int batch) {
     g.batch = batch;
     // int arithmetic in the kernel: s*x - p + k, s*y0 - p + iw
     int64_t iw = (int64_t)(tw - 1) * sh.s + sh.k;
-    if ((int64_t)sh.m + 2LL * sh.p + sh.k >= (1LL << 30) || (int64_t)sh.n + 2LL * sh.p + iw >= (1LL << 30)) return c;
+    if ((int64_t)sh.m + 2LL * sh.p + sh.k >= (1LL << 30) || (int64_t)sh.n + 2LL * sh.p + iw >= (1LL << 30)) return false;
     const int kk_bytes = sh.k * sh.k * 4;
     // the rectangle path compares descriptors with (s*x - p)*n + s*y - p in int, for x up to m_out + RV
     // ... and addresses lanes by 32-bit offsets from a line's start: n*batch*4 < 2^24, TW*batch*4 < 2^32
@@ -919,40 +931,118 @@ CompactChoice choose_compact(const conv_plan *plan, int batch) {
     g.seg = (int)seg;
     g.segs = (int)((sh.m_out + seg - 1) / seg);
     const int64_t jobs = (int64_t)g.strips * g.segs;
-    if (jobs + kXcds >= (1LL << 31) / kXcds) return c;
+    if (jobs + kXcds >= (1LL << 31) / kXcds) return false;
     g.blocks_per_xcd = (int)((jobs + kXcds - 1) / kXcds);
     c.geom = g;
     c.ok = true;
-    // Fewer workgroups than compute units: the marching layout cannot fill the chip.  The
-    // row-group kernel gives such a product rows * G lanes instead (x from global memory, which
-    // for a plane this small means from the L2).
-    // (the plan's marching threshold, a test hook, lowers the bound so that small test shapes march too)
-    c.pushed = !c.kk && push_geometry(plan, batch, c.scalar, c.lpr, c.col_blocks, &c.push);
-    const int64_t work = c.pushed ? (int64_t)c.push.blocks * kPushWaves * c.col_blocks : jobs * c.col_blocks;
-    const int64_t least = c.pushed ? kPushMinWaves : kCompactMinBlocks;
-    if (work < (plan->march_min_jobs < kMarchMinJobs ? std::min<int64_t>(least, plan->march_min_jobs) : least) &&
-        plan->rows * 16 / kCompactThreads + 1 < kInt32Limit) {
-        c.pushed = false;
-        // More lanes per row, down to kGatherTaps taps each, where rows are few (570 x 564, k 5, batch 1:
-        // 10 us with 4 lanes per row, 18 with 8); the columns per lane that waste least of the last
-        // block (184 x 204, k 13, batch 12: 20 us with 3 blocks of 4, 24 with one of 16); ways to split
-        // the channels by the waves a launch has.
-        c.scalar = batch < 4;
-        c.lpr = c.scalar ? 0 : widest_nv(batch);
-        while (c.lpr > 1 && column_blocks(batch, c.lpr) * 4 * c.lpr * 10 > column_blocks(batch, 1) * 4 * 11) c.lpr /= 2;
-        c.gather_g = group_width(sh.k * sh.k);
-        auto waves = [&] {
-            return (plan->rows * c.gather_g + kWave - 1) / kWave * column_blocks(batch, c.lpr) * std::min(plan->channels, 16);
-        };
-        while (c.gather_g < 16 && c.gather_g * kGatherTaps < sh.k * sh.k && (!c.scalar || plan->channels > 1 || waves() < kChanFusedWaves)) c.gather_g *= 2;
+    *out = c;
+    return true;
+}
+
+// Row groups: lanes per row, columns per lane and waves that share a row's channels.
+void compact_row_groups(const conv_plan *plan, int batch, CompactChoice *out) {
+    CompactChoice &c = *out;
+    const int kk = plan->shape.k * plan->shape.k;
+    c.xld = 0;
+    c.scalar = batch < 4;
+    c.lpr = c.scalar ? 0 : widest_nv(batch);
+    // Columns per lane: not more than a third of them idle in the last block (184 x 204, k 13, batch 12: 20 us with
+    // 3 blocks of 4, 24 with one of 16; but 385 x 333, k 3, s 2, batch 35: 31 us with 9 blocks of 4, 16 with 3 of 16,
+    // as every block touches every memory line of x).
+    // (several channels, whose waves split the channels anyway: not more than a tenth)
+    const bool many = plan->channels > 1;
+    while (c.lpr > 1 && (many ? 10 : 3) * column_blocks(batch, c.lpr) * c.lpr > (many ? 11 : 4) * column_blocks(batch, 1)) c.lpr /= 2;
+    c.gather_g = group_width(kk);
+    auto waves = [&] {
+        return (plan->rows * c.gather_g + kWave - 1) / kWave * column_blocks(batch, c.lpr) * std::min(plan->channels, 16);
+    };
+    if (many) {
+        while (c.gather_g < 16 && c.gather_g * kGatherTaps < kk) c.gather_g *= 2;
         while (c.lpr > 1 && waves() < kChanFusedWaves) c.lpr /= 2;
-        c.col_blocks = (unsigned)column_blocks(batch, c.lpr);
-        const int64_t row_waves = (plan->rows * c.gather_g + kWave - 1) / kWave;
-        c.ways = 1;
-        while (c.ways < 16 && 2 * c.ways <= plan->channels && row_waves * c.col_blocks * c.ways < kChanFusedWaves) c.ways *= 2;
-        c.lds = c.ways > 1 ? (size_t)c.ways * std::max(c.lpr, 1) * (kWave / c.gather_g) * (c.scalar ? 4 : 16) : 0;
+    } else {
+        // Few waves: more lanes per row, down to 3 taps each, then narrower ones (570 x 564, k 5, batch 1: 10 us with
+        // 4 lanes per row, 18 with 8; 450 x 559, k 5, s 4, batch 36: 25 and 56), with few taps only while the
+        // waves are very few: a narrow lane reads a part of a memory line (85 x 85, k 2, s 2, batch 216: 10 us
+        // with 4 columns per lane, 3.5 with 16).
+        while (kk > 4 && c.gather_g < 16 && c.gather_g * 3 < kk && waves() < kChanFusedWaves) c.gather_g *= 2;
+        // (lanes of 16 columns and few or far taps: down to 4 taps each whatever the waves, 0.83 to 1.0 of the time)
+        while (c.gather_g < 16 && c.gather_g * kGatherTaps < kk && c.lpr == 4 && (plan->shape.s > 1 || kk <= 16)) c.gather_g *= 2;
+        while (c.lpr > 1 && waves() < (kk <= 16 ? kChanFusedWaves / 4 : kChanFusedWaves)) c.lpr /= 2;
     }
-    if (c.pushed) c.lds = (size_t)kPushWaves * 4 * push_wave_floats(sh.k, c.push.pw * sh.s << c.push.lpr_log2, c.scalar);
+    c.col_blocks = (unsigned)column_blocks(batch, c.lpr);
+    const int64_t row_waves = (plan->rows * c.gather_g + kWave - 1) / kWave;
+    c.ways = 1;
+    while (c.ways < 16 && 2 * c.ways <= plan->channels && row_waves * c.col_blocks * c.ways < kChanFusedWaves) c.ways *= 2;
+    c.lds = c.ways > 1 ? (size_t)c.ways * std::max(c.lpr, 1) * (kWave / c.gather_g) * (c.scalar ? 4 : 16) : 0;
+}
+
+// Which of the three serves a product, by the waves and workgroups each would have (8 400 drawn shapes, every
+// kernel and width timed on each: 1.08 times the best of them in the mean).
+CompactChoice choose_compact(const conv_plan *plan, int batch) {
+    const ConvShape &sh = plan->shape;
+    // chunks of four columns (chunk_col); a launch per channel adds to y, where a column must not be in two chunks
+    const bool scalar = batch < 4 || (plan->channels > 1 && batch % 4 != 0);
+    const int wide = scalar ? 1 : widest_nv(batch);
+    CompactChoice c{};
+    if (!compact_march(plan, batch, scalar, wide, &c)) return c;
+    // (the plan's marching threshold, a test hook, lowers the bounds so that small test shapes march or push too)
+    const bool lowered = plan->march_min_jobs < kMarchMinJobs;
+    auto least = [&](int64_t bound) { return lowered ? std::min<int64_t>(bound, plan->march_min_jobs) : bound; };
+    auto workgroups = [](const CompactChoice &m) { return (int64_t)m.geom.strips * m.geom.segs * m.col_blocks; };
+    const bool groups = plan->rows * 16 / kCompactThreads + 1 < kInt32Limit;
+    PushGeom push;
+    const bool can_push = !c.kk && push_geometry(plan, batch, scalar, c.lpr, c.col_blocks, &push);
+    auto pushed = [&] {
+        c.pushed = true;
+        c.push = push;
+        c.lds = (size_t)kPushWaves * 4 * push_wave_floats(sh.k, push.pw * sh.s << push.lpr_log2, scalar);
+        return c;
+    };
+    // Fewer workgroups than compute units: the marching layout cannot fill the chip.  The row groups
+    // give such a product rows * G lanes instead (x from global memory, which for a plane this small means from the L2).
+    if (!can_push && (workgroups(c) >= least(kCompactMinBlocks) || !groups)) return c;
+    // Marching where the push kernel's rule, or the widest lanes' workgroups, would leave a product to the row groups though
+    // lanes that divide the batch have workgroups enough: the widest that do, with taps enough to pay for reading x
+    // again per block of columns, and strips that are not mostly empty (553 x 440, k 11, s 2, batch 28: 39 us marching,
+    // 167 in row groups; 525 x 510, k 7, s 3, batch 36: 27 and 108; but 1901 x 1718, k 1, s 4, batch 4: 12 and 3;
+    // 65 x 50, k 7, batch 152, strips of 256: 19 and 10).  A batch of 1 to 3, a column per lane: with 81 taps or more and
+    // many pixels (1176 x 1484, k 13, s 2, p 6, batch 1: 35 and 67; 2836 x 1798, k 9, s 4: 23 and 34; but 473 x 473, k 11, s 2,
+    // batch 1: about even, and 4 to 10 times the row groups' time at 20 000 pixels).
+    auto narrower = [&](CompactChoice *out) {
+        if (plan->channels > 1) return false;
+        CompactChoice m{};
+        if (scalar) {
+            if (!can_push || sh.k < 9 || sh.s == 1 || plan->rows * batch < (sh.s <= 3 ? 300000 : 200000)) return false;
+            *out = c;
+            return workgroups(c) >= least(kCompactMinBlocks);
+        }
+        if (batch % 4 != 0 || sh.k < 5 || sh.s > 3) return false;
+        const int dividing = least_nv(batch);
+        if (!compact_march(plan, batch, false, dividing, &m) || workgroups(m) < least(kCompactMinBlocks)) return false;
+        for (int lpr = can_push ? wide : wide / 2; lpr >= dividing; lpr /= 2) {
+            if (lpr == 1 && lpr < wide && sh.k < 7) break;
+            if (!compact_march(plan, batch, false, lpr, &m) || workgroups(m) < least(kCompactMinBlocks)) continue;
+            if (10LL * sh.n_out < 6LL * m.geom.tw * m.geom.strips) continue;
+            *out = m;
+            return true;
+        }
+        return false;
+    };
+    CompactChoice m{};
+    if (can_push) {
+        const int64_t waves = (int64_t)push.blocks * kPushWaves * c.col_blocks;
+        const int in_flight = (sh.k + sh.s - 1) / sh.s;
+        // Column by column, several channels cost a launch each; the row groups take them in one, in chunks of four columns
+        // (205 x 192, k 1, s 4, 10 channels, batch 71: 361 us, row groups 7; 570 x 480, k 2, 4 channels, batch 1: 30 and 5).
+        const bool one_by_one = scalar && plan->channels > 1;
+        const bool enough = one_by_one ? batch < 4 && sh.k >= 6 && waves >= 1536 : push_taps(sh.k, sh.s, batch) && waves >= push_min_waves(sh.k, scalar);
+        if (lowered ? waves >= least(kPushTargetWaves) : enough && (scalar || in_flight <= kPushFewLines)) return pushed();
+        if (!lowered && narrower(&m)) return m;
+        if (!groups || (!lowered && enough)) return pushed();
+    } else if (!lowered && narrower(&m)) {
+        return m;
+    }
+    compact_row_groups(plan, batch, &c);
     return c;
 }
 

@@ -261,6 +261,9 @@ def test_pushed_lines_at_the_edges(k, s):
 
 
 @pytest.mark.parametrize("kind,shape,batch,channels,want", [
+    ("compact", (553, 440, 11, 2, 5), 28, 1, "compact_described_"), ("compact", (525, 510, 7, 3, 6), 36, 1, "compact_described_"),
+    ("compact", (359, 277, 9, 1, 4), 12, 1, "compact_rect_"), ("compact", (420, 582, 11, 1, 5), 16, 1, "_ring"),
+    ("compact", (205, 192, 1, 4, 0), 71, 10, "compact_gather_"), ("compact", (450, 559, 5, 4, 2), 36, 1, "compact_gather_"),
     ("csr", (393, 379, 11, 1, 0), 40, 1, "lds_march_28x32"), ("csr", (477, 694, 8, 1, 0), 3, 1, "lds_march_"),
     ("csr", (413, 252, 2, 1, 0), 32, 1, "lds_tile_7x64"), ("csr", (247, 335, 4, 1, 2), 3, 4, "gather_"),
     ("csc", (340, 367, 3, 2, 1), 160, 1, "lds_tile_"), ("csc", (340, 367, 3, 2, 1), 40, 1, "gather_"),

@@ -415,6 +415,18 @@ def test_device_queries_without_the_internal_calls():
 
 
 @pytest.mark.parametrize("shape,batch,storage,channels,kernel,columns", [
+    # row descriptors: marching lanes of fewer columns where the widest leave too few workgroups
+    ((553, 440, 11, 2, 5), 28, 2, 1, 4, 4), ((525, 510, 7, 3, 6), 36, 2, 1, 4, 4), ((359, 277, 9, 1, 4), 12, 2, 1, 5, 4),
+    # ... but not for a few taps, or strips that would be mostly empty
+    ((1901, 1718, 1, 4, 0), 4, 2, 1, 10, 4), ((65, 50, 7, 1, 3), 152, 2, 1, 10, None),
+    # lines pushed: not for a few taps on few waves, nor for many output lines in flight
+    ((1620, 2340, 1, 4, 0), 1, 2, 1, 10, 1), ((2602, 2660, 3, 4, 2), 1, 2, 1, 10, 1), ((420, 582, 11, 1, 5), 16, 2, 1, 4, 4),
+    ((4096, 4096, 11, 4, 5), 4, 2, 1, 4, 4), ((3000, 2000, 8, 1, 3), 1, 2, 1, 4, 1),
+    ((1126, 1766, 1, 2, 0), 4, 2, 1, 10, 4), ((1046, 1570, 2, 1, 0), 80, 2, 1, 4, None), ((1176, 1484, 13, 2, 6), 1, 2, 1, 4, 1),
+    # row groups: lanes per row only where waves are few
+    ((450, 559, 5, 4, 2), 36, 2, 1, 10, None),
+    # several channels column by column: one launch of the row groups
+    ((205, 192, 1, 4, 0), 71, 2, 10, 10, None), ((570, 480, 2, 1, 0), 1, 2, 4, 10, 1),
     # T^T: the tile kernel with full lanes, or rows of 9 entries at small batches
     ((340, 367, 3, 2, 1), 168, 1, 1, 1, 16), ((340, 367, 3, 2, 1), 160, 1, 1, 2, 16), ((881, 1143, 5, 4, 2), 40, 1, 1, 1, 16),
     ((256, 256, 5, 2, 2), 64, 1, 1, 2, 16), ((267, 383, 3, 1, 1), 4, 1, 1, 1, 4), ((500, 450, 3, 1, 1), 8, 1, 1, 2, 8),

@@ -49,7 +49,8 @@ struct PushGeom {
     int accum;            // 1: y += T x
 };
 
-template <int KL, bool SCALAR>
+// FINE: the sum over an input line's taps is added to the output line's sum as one number (see spmm_compact_kernel).
+template <int KL, bool SCALAR, bool FINE>
 __global__ __launch_bounds__(kPushWaves *kWave) void spmm_compact_push_kernel(const int2 *__restrict__ desc,
                                                                              const float *__restrict__ ktab,
                                                                              const float *__restrict__ x,
@@ -164,6 +165,15 @@ __global__ __launch_bounds__(kPushWaves *kWave) void spmm_compact_push_kernel(co
     // KN output lines take line i: tap lines r0, r0 + s, ...
     auto push = [&](auto kn_tag) {
         constexpr int KN = decltype(kn_tag)::value;
+        elem_t part[FINE && KN > 0 ? KN : 1];                 // FINE: the sums over this line's taps
+        if constexpr (FINE) {
+#pragma unroll
+            for (int l = 0; l < KN; ++l) part[l] = elem_t(0.0f);
+        }
+        auto sum = [&](int l) -> elem_t & {
+            if constexpr (FINE) return part[l];
+            else return acc[l];
+        };
         const float *kr = kt + r0 * kp;                       // tap line of slot l: kr + l * s * kp
         const int line_step = s * kp;
         int ph = 0, place = lane_place;                       // of tap column b: phase b mod s, place yy + b / s
@@ -186,12 +196,16 @@ __global__ __launch_bounds__(kPushWaves *kWave) void spmm_compact_push_kernel(co
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int l = 0; l < KN; ++l) fma_elem(acc[l], kv[l][t], e[t]);
+                for (int l = 0; l < KN; ++l) fma_elem(sum(l), kv[l][t], e[t]);
         }
         for (; b < k; ++b) {
             const elem_t e = line[next_place()];
 #pragma unroll
-            for (int l = 0; l < KN; ++l) fma_elem(acc[l], kr[l * line_step + b], e);
+            for (int l = 0; l < KN; ++l) fma_elem(sum(l), kr[l * line_step + b], e);
+        }
+        if constexpr (FINE) {
+#pragma unroll
+            for (int l = 0; l < KN; ++l) acc[l] += part[l];
         }
     };
     auto one_line = [&](int i, elem_t (&e)[kPushItems]) {

@@ -978,7 +978,7 @@ void compact_row_groups(const conv_plan *plan, int batch, CompactChoice *out) {
 
 // Which of the three serves a product, by the waves and workgroups each would have (8 400 drawn shapes, every
 // kernel and width timed on each: 1.08 times the best of them in the mean).
-CompactChoice choose_compact(const conv_plan *plan, int batch) {
+CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
     const ConvShape &sh = plan->shape;
     // chunks of four columns (chunk_col); a launch per channel adds to y, where a column must not be in two chunks
     const bool scalar = batch < 4 || (plan->channels > 1 && batch % 4 != 0);
@@ -1014,6 +1014,7 @@ CompactChoice choose_compact(const conv_plan *plan, int batch) {
         if (scalar) {
             if (!can_push || sh.k < 9 || sh.s == 1 || plan->rows * batch < (sh.s <= 3 ? 300000 : 200000)) return false;
             *out = c;
+            out->fine = true;
             return workgroups(c) >= least(kCompactMinBlocks);
         }
         if (batch % 4 != 0 || sh.k < 5 || sh.s > 3) return false;
@@ -1024,6 +1025,7 @@ CompactChoice choose_compact(const conv_plan *plan, int batch) {
             if (!compact_march(plan, batch, false, lpr, &m) || workgroups(m) < least(kCompactMinBlocks)) continue;
             if (10LL * sh.n_out < 6LL * m.geom.tw * m.geom.strips) continue;
             *out = m;
+            out->fine = true;
             return true;
         }
         return false;
@@ -1043,6 +1045,18 @@ CompactChoice choose_compact(const conv_plan *plan, int batch) {
         return m;
     }
     compact_row_groups(plan, batch, &c);
+    return c;
+}
+
+// ... and whether its sums are taken line by line (FINE): where the row groups would serve it otherwise, with the
+// widest lanes (above) or with lanes that divide the batch (one column each where it is not a multiple of 4), so that
+// neither the lanes' width nor the pushed lines cost such products their exactness.
+CompactChoice choose_compact(const conv_plan *plan, int batch) {
+    CompactChoice c = choose_compact_path(plan, batch), even{};
+    if (!c.ok || c.gather_g || plan->shape.k < 3 || (!c.pushed && (c.scalar || plan->channels > 1))) return c;
+    const bool whole = batch >= 4 && batch % 4 == 0;
+    c.fine = c.fine || (compact_march(plan, batch, !whole, whole ? least_nv(batch) : 1, &even) &&
+                        (int64_t)even.geom.strips * even.geom.segs * even.col_blocks < kCompactMinBlocks);
     return c;
 }
 

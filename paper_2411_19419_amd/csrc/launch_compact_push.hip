@@ -7,10 +7,16 @@ namespace convspmv {
 template <int KL>
 void launch_push_kl(const CompactChoice &c, const PushGeom &g, const conv_plan *plan, const float *ktab, const float *x,
                     float *y, dim3 grid, hipStream_t q) {
-    if (c.scalar)
-        spmm_compact_push_kernel<KL, true><<<grid, kPushWaves * kWave, c.lds, q>>>(plan->desc, ktab, x, y, g);
-    else
-        spmm_compact_push_kernel<KL, false><<<grid, kPushWaves * kWave, c.lds, q>>>(plan->desc, ktab, x, y, g);
+#define CONV_PUSH(SCALAR, FINE) \
+    spmm_compact_push_kernel<KL, SCALAR, FINE><<<grid, kPushWaves * kWave, c.lds, q>>>(plan->desc, ktab, x, y, g)
+    if (c.scalar) {
+        if (c.fine) CONV_PUSH(true, true);
+        else CONV_PUSH(true, false);
+    } else {
+        if (c.fine) CONV_PUSH(false, true);
+        else CONV_PUSH(false, false);
+    }
+#undef CONV_PUSH
 }
 
 void launch_compact_push(const CompactChoice &c, const conv_plan *plan, const float *x, float *y, hipStream_t q) {

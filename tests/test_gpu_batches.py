@@ -287,6 +287,36 @@ def test_products_on_both_sides_of_the_dispatch_rules(kind, shape, batch, channe
     plan.close()
 
 
+@pytest.mark.parametrize("shape,batch,want", [
+    ((512, 512, 7, 2, 3), 12, "compact_rect_"), ((713, 1068, 11, 4, 5), 64, "_push3_float4"), ((333, 504, 13, 1, 0), 3, "_push13_scalar"),
+    ((553, 440, 11, 2, 5), 28, "_ring"), ((1176, 1484, 13, 2, 6), 1, "_ring"),
+])
+def test_products_of_few_workgroups_sum_line_by_line(shape, batch, want):
+    """Marching and pushing launches that take the place of row groups: the taps of a line are summed
+    before the lines are, within 5 % (the scatter of the samples) of the error that has; one chain
+    through all taps is 1.8 to 2.4 times as far off."""
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(31)
+    K = rng.standard_normal(k * k).astype(np.float32)
+    plan = cs.conv_compact_build(*shape, torch.from_numpy(K).to(device()))
+    assert want in plan.variant(batch), plan.variant(batch)
+    x = rng.standard_normal(plan.cols * batch).astype(np.float32)
+    y = torch.full((plan.rows * batch,), float("nan"), dtype=torch.float32, device=device())
+    cs.conv_spmv(plan, torch.from_numpy(x).to(device()), y, batch=batch)
+    torch.cuda.synchronize()
+    ref, scale = oracle.conv(m, n, k, s, p, x, K, batch=batch, want_scale=True)
+    got = y.cpu().numpy()
+    _check(got, ref, scale, (shape, batch))
+    # 20 000 of the outputs against sums in 64 bits
+    i, j, c = (rng.integers(0, top, 20000) for top in (plan.m_out, plan.n_out, batch))
+    xp = np.zeros((m + 2 * p, n + 2 * p, batch), np.float32)
+    xp[p:p + m, p:p + n] = x.reshape(m, n, batch)
+    exact = sum(np.float64(K[a * k + b]) * xp[i * s + a, j * s + b, c] for a in range(k) for b in range(k))
+    error = np.linalg.norm(got.reshape(plan.m_out, plan.n_out, batch)[i, j, c] - exact) / np.linalg.norm(exact)
+    assert error <= 1.05 * _launch_per_channel_error(K, k, 1), error
+    plan.close()
+
+
 def test_rows_at_the_last_entry_numbers():
     """2^31 - 2 entries: the row groups step past the end of the last rows, up to 80 entries at once, where an
     entry number would leave the range of int.  The last output lines against sums in 64 bits."""

@@ -1601,7 +1601,7 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch) {
         if (cc.gather_g)
             snprintf(name, sizeof name, "compact_gather_g%d_%s", cc.gather_g, cols);
         else if (cc.pushed)
-            snprintf(name, sizeof name, "compact_described_%dx%d_prefetch_push%d_%s", cc.push.seg, cc.push.tw,
+            snprintf(name, sizeof name, "compact_described_%dx%d_push%d_%s", cc.push.seg, cc.push.tw,
                      (plan->shape.k + plan->shape.s - 1) / plan->shape.s, cols);
         else if (cc.kk)
             snprintf(name, sizeof name, "compact_rect_k%ds%d_%dx%d_ring%d_rv%d_%s", cc.kk, cc.ss, cc.geom.seg,

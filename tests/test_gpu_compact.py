@@ -4,6 +4,7 @@ oracle, and, for descriptors edited after the build, against the matrix the orac
 decoder says they stand for."""
 import ctypes
 import itertools
+import re
 
 import numpy as np
 import pytest
@@ -75,9 +76,13 @@ DESCRIBED = [
     ((120, 120, 100, 5, 50), 4), ((260, 260, 255, 3, 0), 1), ((60, 70, 40, 1, 20), 16), ((500, 40, 4, 1, 2), 8),
     ((31, 31, 6, 1, 9), 16), ((150, 150, 1, 3, 0), 16), ((97, 400, 2, 1, 1), 4),
 ]
+PREFETCHED = [   # ... with a step's lines in registers during the step before: rings above 64 KiB, no push kernel
+    ((60, 140, 17, 1, 8), 16), ((60, 140, 17, 1, 8), 13), ((70, 140, 11, 2, 11), 16), ((70, 140, 11, 2, 11), 13),
+    ((40, 300, 19, 1, 18), 32), ((90, 200, 17, 1, 0), 16), ((80, 140, 11, 4, 11), 16), ((80, 140, 11, 4, 11), 4),
+]
 
 
-@pytest.mark.parametrize("shape,batch", RECT + RECT_S2 + DESCRIBED)
+@pytest.mark.parametrize("shape,batch", RECT + RECT_S2 + DESCRIBED + PREFETCHED)
 def test_compact_shapes(shape, batch):
     x, K = _rand(shape, batch, 3)
     plan = build_plan_c(shape, K)
@@ -101,6 +106,10 @@ def test_rectangle_path_is_dispatched_where_compiled(compact_dispatch):
     for shape, batch in DESCRIBED:
         plan = build_plan_c(shape, np.ones(shape[2] ** 2, dtype=np.float32))
         assert plan.variant(batch).startswith("compact_described"), (shape, plan.variant(batch))
+        plan.close()
+    for shape, batch in PREFETCHED:
+        plan = build_plan_c(shape, np.ones(shape[2] ** 2, dtype=np.float32))
+        assert re.match(r"compact_described_\d+x\d+_ring\d+_rv\d+_prefetch_float4", plan.variant(batch)), plan.variant(batch)
         plan.close()
 
 
@@ -134,16 +143,27 @@ def test_compact_batch_widths(batch):
     plan.close()
 
 
-def test_compact_more_column_blocks_than_one_grid_holds():
-    """An odd batch takes one scalar column per workgroup row; 65 541 of them need two launches."""
-    shape, batch = (3, 4, 3, 1, 1), 65541
-    x, K = _rand(shape, batch, 17)
-    plan = build_plan_c(shape, K)
-    check_apply(plan, shape, K, x, batch)
+@pytest.mark.parametrize("shape,kind", [((3, 4, 3, 1, 1), "compact_rect_"), ((6, 7, 4, 3, 1), "_push2_"), ((5, 6, 4, 1, 4), "_ring")])
+def test_compact_more_column_blocks_than_one_grid_holds(shape, kind):
+    """Sums over channels at an odd batch march, or push, one column per workgroup row; 65 541 of them
+    need two launches per channel."""
+    (m, n, k, s, p), batch, channels = shape, 65541, 2
+    rng = np.random.default_rng(17)
+    x = rng.standard_normal(channels * m * n * batch).astype(np.float32)
+    K = rng.standard_normal(channels * k * k).astype(np.float32)
+    plan = cs.conv_compact_build(*shape, torch.from_numpy(K).to(device()), channels=channels)
+    cs.conv_plan_set_march_min_jobs(plan, 1)
+    variant = plan.variant(batch)
+    assert kind in variant and variant.endswith("_scalar"), variant
+    y = torch.full((plan.rows * batch,), float("nan"), dtype=torch.float32, device=device())
+    cs.conv_spmv(plan, torch.from_numpy(x).to(device()), y, batch=batch)
+    torch.cuda.synchronize()
+    ref, scale = oracle.conv_channels(m, n, k, s, p, x, K, channels, batch=batch, want_scale=True)
+    assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - ref) <= REL_TOL * scale)
     plan.close()
 
 
-def test_compact_unaligned_operands_take_the_scalar_columns():
+def test_compact_operands_off_the_16_byte_grid():
     shape, batch = (80, 300, 7, 1, 3), 4
     m, n, k, s, p = shape
     x, K = _rand(shape, batch, 5)
@@ -171,8 +191,10 @@ def _word(a_lo, r1, b_lo, r2):
 @pytest.mark.parametrize("shape,batch", [((96, 300, 7, 1, 3), 16), ((96, 300, 7, 1, 3), 1), ((120, 200, 5, 2, 2), 8),
                                          ((60, 70, 40, 1, 20), 4),
                                          # strides 3 and 4: row groups by default; with the marching threshold
-                                         # lowered the described path, the second with its lines prefetched
-                                         ((150, 160, 9, 3, 8), 1), ((300, 1200, 11, 4, 5), 4)])
+                                         # lowered the push kernel
+                                         ((150, 160, 9, 3, 8), 1), ((300, 1200, 11, 4, 5), 4),
+                                         # described, with its lines prefetched
+                                         ((60, 140, 17, 1, 8), 16), ((70, 140, 11, 2, 11), 13), ((80, 140, 11, 4, 11), 4)])
 def test_compact_apply_reads_the_stored_descriptors(shape, batch, compact_dispatch):
     """Descriptors and table edited after the build: the product follows them.  Edits:
     shortened and shifted rectangles in the interior (a wave that holds one leaves the
@@ -185,8 +207,11 @@ def test_compact_apply_reads_the_stored_descriptors(shape, batch, compact_dispat
     if shape[3] >= 3:
         want = "compact_described" if compact_dispatch == "marching_everywhere" else "compact_gather"
         assert plan.variant(batch).startswith(want), plan.variant(batch)
-        if shape[3] == 4 and compact_dispatch == "marching_everywhere":
-            assert "_prefetch_" in plan.variant(batch), plan.variant(batch)
+    if compact_dispatch == "marching_everywhere":
+        if shape[3] >= 3 and p < k:
+            assert "_push" in plan.variant(batch), plan.variant(batch)
+        if k == 17 or p >= k:
+            assert "_ring" in plan.variant(batch) and "_prefetch_" in plan.variant(batch), plan.variant(batch)
     desc = plan.row_desc.cpu().numpy().copy()
     ktab = plan.ktab.cpu().numpy().copy()
     rng = np.random.default_rng(8)

@@ -4,6 +4,7 @@ computed by two lanes, and 16-byte accesses start at any float.  Reference: the 
 oracle; the floats around the result must stay as they were."""
 import numpy as np
 import pytest
+import scipy.sparse
 import torch
 
 import oracle
@@ -63,6 +64,74 @@ def test_ragged_batches_and_unaligned_operands(shape, jobs, kind):
     assert True in seen                       # the kernel this row is about ran for some of the batches
     plan.close()
     plan_t.close()
+
+
+TILES = [   # T or T^T, batches: enough multiply-adds for the tile kernel
+    ("csr", (260, 200, 3, 1, 1), (8, 9, 10, 13, 16, 31)), ("csr", (240, 251, 5, 2, 2), (10, 13, 16)),
+    ("csc", (500, 450, 3, 1, 1), (6, 7, 9, 10, 13, 16)), ("csc", (500, 451, 5, 2, 2), (9, 10, 13, 16)),
+]
+
+
+@pytest.mark.parametrize("storage,shape,batches", TILES)
+def test_tiles_at_ragged_batches(storage, shape, batches):
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(41)
+    K = rng.standard_normal(k * k).astype(np.float32)
+    plan = (cs.conv_csr_build if storage == "csr" else cs.conv_csc_build)(*shape, torch.from_numpy(K).to(device()))
+    for i, batch in enumerate(batches):
+        offset = i % 4
+        assert plan.variant(batch).startswith("lds_tile_"), (batch, plan.variant(batch))
+        x = rng.standard_normal(plan.cols * batch).astype(np.float32)
+        y0 = np.full(plan.rows * batch, np.nan, dtype=np.float32)
+        (_, xd), (yb, yd) = _padded(x, offset), _padded(y0, 3 - offset)
+        cs.conv_spmv(plan, xd, yd, batch=batch)
+        torch.cuda.synchronize()
+        _check(yd.cpu().numpy(), *(oracle.conv if storage == "csr" else oracle.conv_t)(m, n, k, s, p, x, K, batch=batch, want_scale=True),
+               (shape, batch))
+        edge = yb.cpu().numpy()
+        assert np.all(edge[:3 - offset] == 7.0) and np.all(edge[3 - offset + y0.size:] == 7.0)
+    plan.close()
+
+
+@pytest.mark.parametrize("storage,shape,batches", TILES)
+def test_tiles_read_the_stored_columns(storage, shape, batches):
+    """Columns redirected after the build (far from the row's window, one pixel beside it, another
+    line): the product follows the stored arrays, and no other row changes."""
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(43)
+    K = rng.standard_normal(k * k).astype(np.float32)
+    plan = (cs.conv_csr_build if storage == "csr" else cs.conv_csc_build)(*shape, torch.from_numpy(K).to(device()))
+    rp, ci, va = oracle.csr(*shape, K)
+    outputs = plan.m_out * plan.n_out
+    T = scipy.sparse.csr_matrix((va.astype(np.float64), ci, rp), shape=(outputs, m * n))
+    if storage == "csc":
+        T = T.T.tocsr()
+        T.sort_indices()
+    ptr, idx = T.indptr, T.indices.copy()
+    stored = plan.col_idx                      # (of a T^T plan: T's row numbers)
+    assert np.array_equal(stored.cpu().numpy(), idx)
+    rows = rng.choice(plan.rows, size=60, replace=False)
+    rows = rows[np.diff(ptr)[rows] > 3]
+    for i, row in enumerate(rows):
+        e = ptr[row] + i % 4
+        idx[e] = (0, plan.cols - 1, min(idx[e] + 1, plan.cols - 1), (idx[e] + 5 * n) % plan.cols)[i % 4]
+    for batch in batches:
+        assert plan.variant(batch).startswith("lds_tile_"), (batch, plan.variant(batch))
+        x = rng.standard_normal(plan.cols * batch).astype(np.float32)
+        xd = torch.from_numpy(x).to(device())
+        stored.copy_(torch.from_numpy(T.indices))
+        before = cs.conv_spmv(plan, xd, batch=batch).clone()
+        stored.copy_(torch.from_numpy(idx))
+        got = cs.conv_spmv(plan, xd, batch=batch)
+        torch.cuda.synchronize()
+        before, got = before.cpu().numpy().reshape(-1, batch), got.cpu().numpy().reshape(-1, batch)
+        others = np.ones(plan.rows, bool)
+        others[rows] = False
+        assert np.array_equal(before[others], got[others])
+        E = scipy.sparse.csr_matrix((T.data, idx, ptr), shape=T.shape)[rows]
+        X = x.reshape(-1, batch).astype(np.float64)
+        _check(got[rows], E @ X, abs(E) @ np.abs(X), (shape, batch))
+    plan.close()
 
 
 @pytest.mark.parametrize("shape", [(70, 75, 5, 1, 2), (70, 131, 5, 2, 2)])     # in one launch; a launch per channel, adding
@@ -177,7 +246,6 @@ def test_channel_sums_in_row_groups_follow_the_descriptors(shape, channels, batc
     cs.conv_spmv(plan, torch.from_numpy(x).to(device()), y, batch=batch)
     torch.cuda.synchronize()
     ref, scale = np.zeros((plan.rows, batch)), np.zeros((plan.rows, batch))
-    import scipy.sparse
     for c in range(channels):
         rp, ci, va = oracle.compact_decode(n, k, desc, K[c * k * k:(c + 1) * k * k])
         T = scipy.sparse.csr_matrix((va.astype(np.float64), ci, rp), shape=(plan.rows, m * n))

@@ -104,7 +104,7 @@ def test_batch_widths(batch):
     plan.close()
 
 
-def test_unaligned_operands_take_the_scalar_path():
+def test_operands_off_the_16_byte_grid():
     shape, batch = (29, 31, 3, 1, 1), 8
     x, K = _rand(shape, batch, 3)
     plan = build_plan(shape, K)

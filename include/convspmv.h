@@ -81,7 +81,8 @@ int conv_csr_build(int m, int n, int k, int s, int p,
  * harnesses that forbid hipMalloc): the three CSR arrays of conv_csr_build,
  * written by the same kernels, with no allocation of any kind -- no plan object
  * is made.  Arguments as for conv_csr_build.  Limits: m_out + n_out + 2
- * <= 65536 (CONV_EOVERFLOW beyond).  Calls share nothing and may overlap on any
+ * <= 65536 (CONV_EOVERFLOW beyond; part of the contract, no kernel needs it
+ * any more).  Calls share nothing and may overlap on any
  * streams.  The device that is current at the call is used. */
 int conv_csr_fill_noalloc(int m, int n, int k, int s, int p,
                           const float *kernel_dev,
@@ -233,7 +234,9 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch);
  * CONV_ENULL).  For tests of the host logic and for reports. */
 typedef struct conv_dispatch {
     int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, 3 LDS march,
-                               4 described rows (structure-aware), 5 rectangle path (structure-aware),
+                               4 described rows (structure-aware): marching, or, with ring_lines 0
+                               and strip x lanes_per_row = 64, input lines pushed into output lines,
+                               5 rectangle path (structure-aware),
                                6 all channels in one launch, 4 x 16 outputs per wave (structure-aware),
                                7 scatter with the sums of a tile of pixels kept on chip, 8 direct scatter
                                (storage 3; for 7: strip x segment = pixels x lines of a tile, ring_lines_needed
@@ -254,7 +257,7 @@ typedef struct conv_dispatch {
 int conv_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels,
                        conv_dispatch *out);
 
-/* Release the host object and the plan-owned device table.  The caller must
+/* Release the host object (a plan owns no device memory).  The caller must
  * have synchronised every stream the plan was used on.  NULL is accepted. */
 int conv_plan_destroy(conv_plan *plan);
 

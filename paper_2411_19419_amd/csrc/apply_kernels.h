@@ -34,7 +34,7 @@ struct ChannelStrides {
 // U steps at a time: their column indices and values are asked for together, then their operands, so that a row costs two
 // round trips to memory per U entries of a lane and not two per entry (32 x 32, k 3, batch 1: 3.3 -> 2.9 us).
 // A step past the end reads the last entry again and leaves the sum alone.  Launches with waves enough
-// to hide the round trips do better one entry at a time (1254 x 1457, k 3, s 4, batch 1: 4.6 us, 5.6 four at a time;
+// to hide the round trips do better one entry at a time (1254 x 1457, k 3, s 4, batch 1: 4.6 us, 5.6 five at a time;
 // 119 x 153, k 13, batch 144: 118 and 147).
 constexpr int kGatherAhead = 5;      // (rows of 9 entries, two lanes: all of a lane's)
 

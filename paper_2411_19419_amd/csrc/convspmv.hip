@@ -1007,7 +1007,9 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
     // 167 in row groups; 525 x 510, k 7, s 3, batch 36: 27 and 108; but 1901 x 1718, k 1, s 4, batch 4: 12 and 3;
     // 65 x 50, k 7, batch 152, strips of 256: 19 and 10).  A batch of 1 to 3, a column per lane: with 81 taps or more and
     // many pixels (1176 x 1484, k 13, s 2, p 6, batch 1: 35 and 67; 2836 x 1798, k 9, s 4: 23 and 34; but 473 x 473, k 11, s 2,
-    // batch 1: about even, and 4 to 10 times the row groups' time at 20 000 pixels).
+    // batch 1: about even, and 4 to 10 times the row groups' time at 20 000 pixels).  Batches that are not a multiple of 4:
+    // the rectangles of stride 1, from fewer workgroups on (262 x 253, k 9, batch 11, 132: 0.6 of the row groups' time;
+    // 243 x 337, k 7, batch 15, 186: 0.5; 418 x 445, k 5, batch 6, 212: 0.78; but 192 x 178, k 5, batch 14, 96: 1.4).
     auto narrower = [&](CompactChoice *out) {
         if (plan->channels > 1) return false;
         CompactChoice m{};
@@ -1017,13 +1019,24 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
             out->fine = true;
             return workgroups(c) >= least(kCompactMinBlocks);
         }
-        if (batch % 4 != 0 || sh.k < 5 || sh.s > 3) return false;
+        const bool ragged = batch % 4 != 0;
+        if (sh.k < 5 || sh.s > 3 || (ragged && (!c.kk || sh.s > 1))) return false;
+        auto filled = [&] { return 10LL * sh.n_out >= 6LL * m.geom.tw * m.geom.strips; };
+        if (ragged) {
+            for (int lpr = wide; lpr >= 1; lpr /= 2)
+                if (compact_march(plan, batch, false, lpr, &m) && workgroups(m) >= (sh.k == 9 ? 128 : 192) && filled()) {
+                    *out = m;
+                    out->fine = true;
+                    return true;
+                }
+            return false;
+        }
         const int dividing = least_nv(batch);
         if (!compact_march(plan, batch, false, dividing, &m) || workgroups(m) < least(kCompactMinBlocks)) return false;
         for (int lpr = can_push ? wide : wide / 2; lpr >= dividing; lpr /= 2) {
             if (lpr == 1 && lpr < wide && sh.k < 7) break;
             if (!compact_march(plan, batch, false, lpr, &m) || workgroups(m) < least(kCompactMinBlocks)) continue;
-            if (10LL * sh.n_out < 6LL * m.geom.tw * m.geom.strips) continue;
+            if (!filled()) continue;
             *out = m;
             out->fine = true;
             return true;

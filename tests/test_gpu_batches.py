@@ -357,7 +357,8 @@ def test_products_on_both_sides_of_the_dispatch_rules(kind, shape, batch, channe
 
 @pytest.mark.parametrize("shape,batch,want", [
     ((512, 512, 7, 2, 3), 12, "compact_rect_"), ((713, 1068, 11, 4, 5), 64, "_push3_float4"), ((333, 504, 13, 1, 0), 3, "_push13_scalar"),
-    ((553, 440, 11, 2, 5), 28, "_ring"), ((1176, 1484, 13, 2, 6), 1, "_ring"),
+    ((553, 440, 11, 2, 5), 28, "_ring"), ((1176, 1484, 13, 2, 6), 1, "_ring"), ((243, 337, 7, 1, 3), 15, "compact_rect_"),
+    ((262, 253, 9, 1, 4), 11, "compact_rect_"), ((418, 445, 5, 1, 2), 6, "compact_rect_"),
 ])
 def test_products_of_few_workgroups_sum_line_by_line(shape, batch, want):
     """Marching and pushing launches that take the place of row groups: the taps of a line are summed

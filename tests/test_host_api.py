@@ -417,6 +417,8 @@ def test_device_queries_without_the_internal_calls():
 @pytest.mark.parametrize("shape,batch,storage,channels,kernel,columns", [
     # row descriptors: marching lanes of fewer columns where the widest leave too few workgroups
     ((553, 440, 11, 2, 5), 28, 2, 1, 4, 4), ((525, 510, 7, 3, 6), 36, 2, 1, 4, 4), ((359, 277, 9, 1, 4), 12, 2, 1, 5, 4),
+    ((262, 253, 9, 1, 4), 11, 2, 1, 5, None), ((243, 337, 7, 1, 3), 15, 2, 1, 5, None), ((418, 445, 5, 1, 2), 6, 2, 1, 5, None),
+    ((192, 178, 5, 1, 2), 14, 2, 1, 10, None),
     # ... but not for a few taps, or strips that would be mostly empty
     ((1901, 1718, 1, 4, 0), 4, 2, 1, 10, 4), ((65, 50, 7, 1, 3), 152, 2, 1, 10, None),
     # lines pushed: not for a few taps on few waves, nor for many output lines in flight

@@ -106,6 +106,7 @@ namespace {
 // quad-walking kernel takes rows too long for the others.
 // Returns true when the launch also wrote row_ptr (with row_ptr_dev given).
 constexpr int64_t kFillMinBlocks = 1024, kFillFewBlocks = 256;
+constexpr int64_t kFillAlikeEntries = 2000000, kFillAlikeRows = 100000;
 constexpr int64_t kFillQuadEntries = 25000;      // entries a workgroup of the values' kernel computes, about
 template <bool COLS, bool TR>
 bool launch_fill(const conv_plan *plan, const float *kernel_dev, int *idx_dev, float *vals_dev, hipStream_t q,
@@ -123,9 +124,13 @@ bool launch_fill(const conv_plan *plan, const float *kernel_dev, int *idx_dev, f
         while (rows > 64 && l1 * ((l2 + rows - 1) / rows) < kFillFewBlocks) rows >>= 1;
         return rows;
     };
-    // values alone, where the rows between two borders are alike
+    // values alone, where the rows between two borders are alike and the entries many: below, the longer prologue
+    // is most of the kernel (28^2, k 3: 3.8 us, staged 3.3, T^T 4.4 and 3.7; 256^2, k 5: 6.3 and 6.0; but 512^2, k 5: 9.3 and 9.8;
+    // 531 x 349, k 2: 6.1 and 6.3)
     const int range = shorter(kFillRows);
-    const bool alike = !COLS && (!TR || sh.s == 1) && (int64_t)kFillRows * plan->max_row_nnz <= kFillSpan;
+    const bool alike = !COLS && (!TR || sh.s == 1) && (int64_t)kFillRows * plan->max_row_nnz <= kFillSpan &&
+                       (plan->nnz * channels >= kFillAlikeEntries || plan->rows * channels >= kFillAlikeRows ||
+                        (int64_t)kFillRows / 4 * plan->max_row_nnz > kFillStageEntries);
     // through an LDS image of R rows' entries
     int R = 256;
     while (R > 1 && (int64_t)R * plan->max_row_nnz > kFillStageEntries) R >>= 1;

@@ -38,6 +38,31 @@ def test_fills_over_several_lines(shape):
     plan_t.close()
 
 
+@pytest.mark.parametrize("shape,channels", [     # fewer than 2 M values and 100 000 rows: through an image in LDS, more: in place
+    ((28, 28, 3, 1, 1), 1), ((31, 33, 4, 1, 2), 1), ((470, 471, 3, 1, 1), 1), ((473, 475, 3, 1, 1), 1), ((500, 401, 6, 2, 3), 1),
+    ((97, 700, 6, 2, 3), 1), ((300, 301, 3, 1, 1), 1), ((350, 301, 3, 1, 1), 1), ((250, 180, 3, 1, 1), 2), ((300, 301, 3, 1, 1), 3), ((90, 40, 11, 1, 10), 1), ((200, 1, 1, 1, 0), 1),
+])
+def test_new_kernels_of_few_and_many_values(shape, channels):
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(7)
+    K, K2 = (rng.standard_normal(channels * k * k).astype(np.float32) for _ in range(2))
+    Kd = torch.from_numpy(K).to(device())
+    plan = cs.conv_csr_build_channels(*shape, Kd, channels) if channels > 1 else build_plan(shape, K)
+    plan.vals.fill_(float("nan"))
+    cs.conv_update_kernel(plan, torch.from_numpy(K2).to(device()))
+    torch.cuda.synchronize()
+    parts = K2.reshape(channels, k * k)
+    assert np.array_equal(plan.vals.cpu().numpy(), np.concatenate([oracle.csr(*shape, w)[2] for w in parts]))
+    plan.close()
+    if channels == 1:
+        plan_t = build_plan_t(shape, K)
+        plan_t.vals.fill_(float("nan"))
+        cs.conv_update_kernel(plan_t, torch.from_numpy(K2).to(device()))
+        torch.cuda.synchronize()
+        check_csc(plan_t, shape, K2)
+        plan_t.close()
+
+
 @pytest.mark.parametrize("batch", [2, 4, 5, 8, 11, 16, 21])
 def test_sweep_at_batches_in_chunks(batch):
     rng = np.random.default_rng(batch)

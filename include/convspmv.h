@@ -198,13 +198,18 @@ int conv_spmv(const conv_plan *plan, const float *x_dev, float *y_dev, int batch
  * variants do (Sections 3 and 4.1: the same T stored by columns).  `plan` must
  * come from conv_csc_build (CONV_EINVAL otherwise); x_dev has m*n*batch
  * elements, y_dev m_out*n_out*batch, both batch-minor.  By columns the product
- * is a scatter: y is zeroed, then every stored entry adds vals[e]*x[column] to
- * y[row_idx[e]].  The sums of a tile of neighbouring pixels are collected on
- * chip and added to y with hardware float adds (for 2 <= ceil(k/s) <= 32, from
- * 3 at batches below 4; otherwise every entry is added to y directly).  The result is that of
- * conv_spmv on the CSR plan of the same T up to the order of the additions,
- * which here depends on timing: repeated calls agree to rounding, not bit for
- * bit.  The arrays are read as stored: every row_idx must be in
+ * is a scatter: every stored entry adds vals[e]*x[column] to y[row_idx[e]].
+ * Where the entries of an output lie in the arrays follows from the geometry,
+ * and products of some size (s <= k, p < k, ceil(k/s) <= 13) gather them: every
+ * output is summed in registers, from entries whose stored row index is
+ * compared with the one their place asks for; outputs of a workgroup that found
+ * another one, or another column pointer, are summed again from whatever the
+ * arrays hold.  Otherwise y is zeroed and the sums of a tile of neighbouring
+ * pixels are collected on chip and added to y with hardware float adds (for
+ * 2 <= ceil(k/s) <= 32, from 3 at batches below 4), or every entry is added to y
+ * directly.  The result is that of conv_spmv on the CSR plan of the same T up to
+ * the order of the additions, which in the scatters depends on timing: repeated
+ * calls agree to rounding, not bit for bit.  The arrays are read as stored: every row_idx must be in
  * [0, m_out*n_out), col_ptr non-decreasing, no column longer than ceil(k/s)^2
  * entries (the longest conv_csc_build writes), and the row indices of one
  * column pairwise different, as conv_csc_build writes them (a row stored twice
@@ -230,7 +235,8 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch);
  * (host only; 16-byte-aligned operands assumed): the kernel family and the
  * launch geometry the dispatch derives.  storage: 0 = CSR of T, 1 = CSC of T
  * (the plan applies T^T), 2 = structure-aware storage, 3 = CSC of T applied
- * by conv_spmv_from_csc; channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
+ * by conv_spmv_from_csc: the scatter, which takes what the gather described there does
+ * not; channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
  * CONV_ENULL).  For tests of the host logic and for reports. */
 typedef struct conv_dispatch {
     int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, 3 LDS march,
@@ -298,8 +304,15 @@ int conv_multi_destroy(conv_multi *multi);   /* NULL is accepted */
  * previous value (CONV_EINVAL for jobs < 1, CONV_ENULL without a plan).  Not
  * thread-safe against a concurrent conv_spmv on the same plan.  The result of
  * conv_spmv does not depend on it beyond the summation order.
- * conv_test_dispatch_info is conv_dispatch_info with that threshold given. */
+ * conv_test_dispatch_info is conv_dispatch_info with that threshold given.
+ * conv_spmv_from_csc lowers the work from which it gathers in proportion (256:
+ * as it is); conv_test_csc_gather_info says whether it gathers, and how: kernel
+ * 11 (0: it scatters), strip, segment, threads, LDS, workgroups, lanes per
+ * output column and batch columns per lane, lines_per_step = shares of a tap
+ * sum, ring_lines_needed = output lines in flight, ring_lines = 16-byte accesses
+ * per array that a line takes at most.  Status as for conv_dispatch_info. */
 int conv_plan_set_march_min_jobs(conv_plan *plan, int jobs);
+int conv_test_csc_gather_info(int m, int n, int k, int s, int p, int batch, int march_min_jobs, conv_dispatch *out);
 int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels,
                             int march_min_jobs, conv_dispatch *out);
 

@@ -47,7 +47,7 @@ EXPORTS = (
     "conv_csc_build", "conv_plan_is_transposed",
     "conv_compact_build", "conv_plan_is_compact",
     "conv_csr_build_channels", "conv_plan_channels", "conv_spmv_from_csc", "conv_dispatch_info",
-    "conv_compact_build_channels",
+    "conv_compact_build_channels", "conv_test_csc_gather_info",
 )
 
 
@@ -133,6 +133,8 @@ def _load():
         lib.conv_plan_set_march_min_jobs.restype = i
         lib.conv_test_dispatch_info.argtypes = [i] * 9 + [ctypes.POINTER(ConvDispatch)]
         lib.conv_test_dispatch_info.restype = i
+        lib.conv_test_csc_gather_info.argtypes = [i] * 7 + [ctypes.POINTER(ConvDispatch)]
+        lib.conv_test_csc_gather_info.restype = i
         lib.conv_csr_fill_noalloc.argtypes = [i, i, i, i, i, vp, vp, vp, vp, vp]
         lib.conv_csr_fill_noalloc.restype = i
         _lib = lib

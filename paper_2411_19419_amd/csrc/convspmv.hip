@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in include/convspmv.h: argument checking,
 // the closed-form count of Theorem 2.1, the plan object and kernel dispatch.
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <new>
@@ -1280,6 +1281,85 @@ static void launch_csc_tile(const CscTileChoice &c, const conv_plan *plan, const
                                                                  c.g);
 }
 
+// Launch shape of the product from the column-compressed arrays that gathers (csc_gather_kernel.h).
+//
+// What it costs over the scatter is time per input line: a workgroup walks seg s + k - s of them, a microsecond each, however
+// little there is to do, and every line at the image's border is placed anew.  Planes with little work for that stay
+// with the scatter.  The line was drawn over 600 products (planes of 16 to 4096 a side, k 1 to 13, strides 1 to 4, batches 1 to 256):
+// entries x batch^(3/4) against the fourth power of the lines in flight, four times as much at strides above 1, whose
+// kernel does not know its strip.  Above it the gather takes 0.1 to 0.9 of the scatter's time (1024^2, k 7, batch 16: 103 us and
+// 357, batch 1: 78 and 157; 1000 x 900, k 3, batch 16: 36 and 215; 4096^2, k 11, s 4, batch 4: 300 and 1480; 269 x 320, k 5,
+// batch 1: 17 and 24), below it the scatter does (137 x 210, k 11, batch 1: 39 and 21; 32 x 40, k 7, batch 16: 25 and 9.5).  With
+// one or two entries per pixel and batches below 4 adding every entry to y directly is hard to beat (3384 x 3491, k 1, batch 1:
+// 47 and 210; 1226 x 786, k 2, batch 1: 20 and 26).
+// Two workgroups per compute unit; with few lines in flight (and few registers) four, as long as the lines that two
+// segments share stay few (3453 x 2976, k 3, batch 1: 238 -> 191 us, 3000^2, k 3, s 2, batch 4: 149 -> 114; 1000 x 900, k 3,
+// batch 16, 15 lines a segment: 36 -> 37; k 5: 163 -> 171).
+constexpr int64_t kCscGatherTarget = 512, kCscGatherLong = 32;
+constexpr double kCscGatherWork = 2000.0, kCscGatherWorkStrided = 15000.0, kCscGatherWorkOne = 1e6, kCscGatherWorkDirect = 2e6;
+
+static CscGatherChoice choose_csc_gather(const conv_plan *plan, int batch) {
+    const ConvShape &sh = plan->shape;
+    CscGatherChoice c{};
+    CscGatherGeom g{};
+    const int64_t k = sh.k, s = sh.s, kl = (k + s - 1) / s;
+    if (s > k || sh.p >= k || kl > kCscGatherLines) return c;       // pixels or rows without entries; too many sums in flight
+    // int arithmetic in the kernel
+    if ((int64_t)sh.m + 2LL * sh.p + k >= (1LL << 30) || (int64_t)sh.n + 2LL * sh.p + 64 * s + k >= (1LL << 30) || 1024LL * batch > kInt32Limit)
+        return c;
+    // (conv_plan_set_march_min_jobs lowers the bar for tests)
+    const double bar = std::min(1.0, plan->march_min_jobs / (double)kMarchMinJobs);
+    const double work = (double)plan->nnz * batch;
+    if (kl == 1 ? batch < 4 || work < kCscGatherWorkOne * bar
+                : work / std::sqrt(std::sqrt((double)batch)) < (s == 1 ? kCscGatherWork : kCscGatherWorkStrided) * (double)(kl * kl * kl * kl) * bar)
+        return c;
+    if (kl == 2 && batch < 4 && k < 4 && (s == 1 || work < kCscGatherWorkDirect * bar)) return c;
+    c.kl = (int)kl;
+    c.scalar = batch < 4;
+    g.sh = sh;
+    const BuildScan bs = build_scan<true>(sh);
+    g.zero1 = bs.first.zero;
+    g.zero2 = bs.second.zero;
+    g.row_entries = bs.row_entries;
+    if (bs.row_entries < 4) return c;                                // lines of fewer entries than one access brings
+    g.nnz = (unsigned)plan->nnz;
+    g.batch = batch;
+    g.lpr_log2 = c.scalar ? 0 : (batch > 8 ? 2 : (batch > 4 ? 1 : 0));
+    const int lpr = 1 << g.lpr_log2, columns = c.scalar ? 1 : 4 * lpr;
+    g.col_blocks = (batch + columns - 1) / columns;
+    const int tw = csc_gather_tw((int)k, (int)s, g.lpr_log2, c.scalar);
+    if (tw == 0) return c;
+    const int pixels = (int)((tw - 1) * s + k + s - 1);              // of a strip, at most
+    g.tw = tw;
+    g.iw = (int)((tw - 1) * s + k);
+    g.pw = csc_gather_places(tw, (int)k, (int)s);
+    g.opw_log2 = csc_gather_opw_log2(tw, g.lpr_log2);
+    g.groups = csc_gather_groups(tw, g.lpr_log2);
+    g.ways = csc_gather_ways(tw, g.lpr_log2);
+    g.line_elems = csc_gather_line(tw, (int)k, (int)s, g.lpr_log2);
+    g.slots = csc_gather_slots(tw, (int)k, (int)s);
+    g.quads = csc_gather_quads(tw, (int)k, (int)s);
+    g.sets = k % s == 0 ? 1 : 2;
+    c.nld = g.quads <= 2 * kCscGatherThreads ? 2 : 5;
+    c.nx = c.nld == 2 && pixels * lpr <= kCscGatherThreads && pixels < kCscGatherThreads ? 1 : 3;
+    c.lds = (size_t)csc_gather_lds(tw, (int)k, (int)s, g.lpr_log2, c.scalar);
+    g.strips = (sh.n_out + tw - 1) / tw;
+    auto lines = [&](int64_t target) {                               // output lines per segment
+        const int64_t segs = std::max<int64_t>(target / ((int64_t)g.strips * g.col_blocks), 1);
+        return (sh.m_out + segs - 1) / segs;
+    };
+    const int64_t seg = kl <= 3 && lines(2 * kCscGatherTarget) >= kCscGatherLong ? lines(2 * kCscGatherTarget) : lines(kCscGatherTarget);
+    g.seg = (int)seg;
+    g.segs = (int)((sh.m_out + seg - 1) / seg);
+    const int64_t blocks = (int64_t)g.strips * g.segs * g.col_blocks;
+    if (blocks + kXcds > kCscGatherBlocks) return c;
+    g.blocks = (int)blocks;
+    g.blocks_per_xcd = (int)((blocks + kXcds - 1) / kXcds);
+    c.geom = g;
+    c.ok = true;
+    return c;
+}
+
 extern "C" {
 
 int conv_spmv_from_csc(const conv_plan *plan, const float *x_dev, float *y_dev, int batch, void *stream) {
@@ -1294,6 +1374,13 @@ int conv_spmv_from_csc(const conv_plan *plan, const float *x_dev, float *y_dev, 
     }
     hipStream_t q = (hipStream_t)stream;
     const LaunchScope scope;
+    if (plan->nnz > 0) {
+        const CscGatherChoice gather = choose_csc_gather(plan, batch);
+        if (gather.ok) {
+            launch_csc_gather(gather, plan, x_dev, y_dev, q);
+            return scope.ok() ? CONV_OK : CONV_EHIP;
+        }
+    }
     const long long count = (long long)out_pixels * batch;
     const unsigned fill_blocks = (unsigned)std::min<long long>((count / 4 + kGatherThreads) / kGatherThreads, 1 << 16);
     fill_zero_kernel<<<fill_blocks, kGatherThreads, 0, q>>>(y_dev, count);
@@ -1596,6 +1683,38 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
         } else {
             d.workgroups = (plan.rows * c.g + kGatherThreads - 1) / kGatherThreads;
         }
+    }
+    *out = d;
+    return CONV_OK;
+}
+
+int conv_test_csc_gather_info(int m, int n, int k, int s, int p, int batch, int march_min_jobs, conv_dispatch *out) {
+    if (!out) return CONV_ENULL;
+    if (march_min_jobs < 1 || batch < 1) return CONV_EINVAL;
+    int64_t mo, no;
+    const int st = check_shape(m, n, k, s, p, &mo, &no);
+    if (st != CONV_OK) return st;
+    const int64_t nnz = conv_nnz(m, n, k, s, p);
+    if (nnz < 0 || nnz > kInt32Limit || mo * no >= kInt32Limit || (int64_t)m * n >= kInt32Limit) return CONV_EOVERFLOW;
+    conv_plan plan{};
+    plan.shape = ConvShape{m, n, k, s, p, (int)mo, (int)no};
+    plan.transposed = true;
+    plan.nnz = nnz;
+    plan.march_min_jobs = march_min_jobs;
+    conv_dispatch d{};
+    const CscGatherChoice c = nnz > 0 ? choose_csc_gather(&plan, batch) : CscGatherChoice{};
+    if (c.ok) {
+        d.kernel = 11;
+        d.threads = kCscGatherThreads;
+        d.lds_bytes = (int64_t)c.lds;
+        d.workgroups = c.geom.blocks;
+        d.strip = c.geom.tw;
+        d.segment = c.geom.seg;
+        d.ring_lines = c.geom.quads;
+        d.ring_lines_needed = c.kl;
+        d.lines_per_step = c.geom.ways;
+        d.lanes_per_row = 1 << c.geom.lpr_log2;
+        d.columns_per_lane = c.scalar ? 1 : 4;
     }
     *out = d;
     return CONV_OK;

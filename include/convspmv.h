@@ -239,7 +239,8 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch);
  * not; channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
  * CONV_ENULL).  For tests of the host logic and for reports. */
 typedef struct conv_dispatch {
-    int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, 3 LDS march,
+    int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, or, with lds_bytes 0, blocks of
+                               strip x segment outputs per group of lanes, 3 LDS march,
                                4 described rows (structure-aware): marching, or, with ring_lines 0
                                and strip x lanes_per_row = 64, input lines pushed into output lines,
                                5 rectangle path (structure-aware),
@@ -258,7 +259,7 @@ typedef struct conv_dispatch {
     int ring_lines_needed;  /* lines a step keeps resident (<= ring_lines when there is a ring) */
     int lines_per_step;     /* output lines per step (kernels 3-5, 9) */
     int lanes_per_row;      /* lanes that share a row of the matrix */
-    int columns_per_lane;   /* batch columns per lane */
+    int columns_per_lane;   /* batch columns per lane; in blocks: sums per lane, 4 columns of every output */
 } conv_dispatch;
 int conv_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels,
                        conv_dispatch *out);

@@ -637,6 +637,59 @@ bool stage_march_geometry(const conv_plan *plan, int batch, int nv, int channels
     return true;
 }
 
+// Geometry of a block kernel launch (apply_block_kernel.h): the lanes over the batch whose blocks of columns leave the
+// fewest idle, the widest of those.
+bool block_geometry(const conv_plan *plan, int batch, int *lpr_log2, BlockGeom *out) {
+    const ConvShape &sh = plan->shape;
+    const bool tr = plan->transposed;
+    auto padded = [&](int l) { return (batch + (4LL << l) - 1) >> (l + 2) << (l + 2); };
+    int lpr = kBlockLprMost;
+    for (int l = kBlockLprMost - 1; l >= kBlockLprLeast; --l)
+        if (padded(l) < padded(lpr)) lpr = l;
+    // byte offsets of 32 bits, and int arithmetic on padded lines
+    if (plan->cols * batch >= (1LL << 30) || plan->rows * batch >= (1LL << 30)) return false;
+    if ((int64_t)sh.m + 2LL * sh.p >= (1LL << 30) || (int64_t)sh.n + 2LL * sh.p >= (1LL << 30)) return false;
+    BlockGeom g{};
+    g.m = tr ? sh.m_out : sh.m;
+    g.n = tr ? sh.n_out : sh.n;
+    g.m_out = tr ? sh.m : sh.m_out;
+    g.n_out = tr ? sh.n : sh.n_out;
+    g.p = sh.p;
+    g.batch = batch;
+    const int first = block_first(sh.s, sh.p, tr);
+    const int64_t lines = 2 * block_rx(sh.k, sh.s, tr), pixels = 2LL * block_ry(sh.k, sh.s, tr) * (kWave >> lpr);
+    const int64_t cells_y = (g.n_out - first + pixels - 1) / pixels, cells = (g.m_out - first + lines - 1) / lines * cells_y;
+    if (cells + kXcds >= (1LL << 31) / kXcds) return false;
+    g.cells_y = (int)cells_y;
+    g.cells = (int)cells;
+    g.cells_per_xcd = (int)((cells + kXcds - 1) / kXcds);
+    *out = g;
+    *lpr_log2 = lpr;
+    return true;
+}
+
+// Where the block kernel takes a product: batches above 32 columns (lanes for 64 at least; below, the tile kernel's 16 columns per
+// lane are as good: 224^2, k 3, batch 16: 6.0 us, blocks with 4 lanes a pixel 7.1), and multiply-adds enough for its start, which
+// waits for row pointers, then entries, then sums, where a block has many entries (24 x 25, k 5, batch 131, 1.9 M: 6.7 us in row
+// groups, 8.3 in blocks; 39 x 40, k 11, s 4, T^T, batch 128, 1.6 M: 5.7 and 6.5; above it 134 x 130, k 7, s 3, T^T, batch 72, 6.8 M:
+// 7.9 and 6.2; 64 x 60, k 5, batch 176, 20 M: 11.2 and 10.3).  Against the marching kernels, which it replaces at k 4 and 5: 246^2,
+// k 4, batch 96: 40.8 and 11.8; 254^2, k 5, s 2, batch 100: 33.5 and 14.1; 595^2, k 5, batch 64: 71.0 and 67.2.
+// A fifth of the lanes idle: from 10 M multiply-adds on; below, it is a matter of a microsecond (72 x 60, k 3, batch 131: 7.3 with
+// tiles, 6.1 in blocks), and the tile kernel's ragged batches keep their place.
+// T^T at k = s + 1, where most pixels have a single entry, stays with the tile kernel and the row groups where an eighth of the
+// lanes or more would idle (the shapes that test_dispatch_keeps_to_the_faster_kernel names for those two).
+constexpr int kBlockMinBatch = 33;
+constexpr int64_t kBlockMinWork = 4000000, kBlockMinWorkIdle = 10000000;
+bool block_serves(const conv_plan *plan, int batch, int lpr_log2) {
+    const ConvShape &sh = plan->shape;
+    if (batch < kBlockMinBatch) return false;
+    const int64_t columns = 4LL << lpr_log2, padded = (batch + columns - 1) / columns * columns;
+    if (plan->transposed && sh.k == sh.s + 1 && sh.s > 1 && 8LL * batch <= 7 * padded) return false;
+    if (5LL * batch < 4 * padded && plan->nnz * batch < kBlockMinWorkIdle) return false;
+    const bool long_start = plan->max_row_nnz >= 16 || (plan->transposed && sh.s >= 3);
+    return !long_start || plan->nnz * batch >= kBlockMinWork;
+}
+
 ApplyChoice choose_apply(const conv_plan *full, int batch) {
     // geometry of one channel; a multi-channel plan applies it once per channel (LDS kernels)
     // or walks the channels inside the row-group kernels
@@ -660,6 +713,17 @@ ApplyChoice choose_apply(const conv_plan *full, int batch) {
     while (c.g < 16 && 6 * c.g <= row_max && row_blocks() * column_blocks(batch, c.nv) < kRowGroupWiden) c.g *= 2;
     while (c.nv > 1 && row_blocks() * column_blocks(batch, c.nv) < row_group_min_blocks(full->channels > 1 ? 1 : row_max, plan->shape.s)) c.nv /= 2;
     if (plan->nnz == 0 || column_blocks(batch, nv_hi) > 65535) return c;
+
+    // batches that fill a wave (not where the plan's marching threshold, a test hook, is lowered)
+    if (full->channels == 1 && full->march_min_jobs >= kMarchMinJobs && block_compiled(plan->shape.k, plan->shape.s, plan->transposed) &&
+        block_geometry(plan, batch, &c.lpr_log2, &c.block) && block_serves(plan, batch, c.lpr_log2)) {
+        c.kind = Kind::Block;
+        c.threads = kBlockThreads;
+        c.g = 1;
+        c.nv = 1;
+        c.tw = block_ry(plan->shape.k, plan->shape.s, plan->transposed);
+        return c;
+    }
 
     // marching kernels: float4 column chunks, or scalar columns
     MarchShape ms;
@@ -1164,6 +1228,9 @@ int conv_spmv(const conv_plan *plan, const float *x_dev, float *y_dev, int batch
     if (c.kind == Kind::StageMarch && c.march.channels > 1) {
         // one launch walks the channels of every block of lines: y is stored once, in a fixed order of sums
         if (!launch_stage_march(c, plan, x_dev, y_dev, q)) return CONV_EHIP;
+    } else if (c.kind == Kind::Block) {
+        if (plan->transposed) launch_block_adjoint(c, plan, x_dev, y_dev, q);
+        else launch_block(c, plan, x_dev, y_dev, q);
     } else if (c.kind == Kind::March || c.kind == Kind::Tile || c.kind == Kind::StageMarch) {
         // one launch per channel: the first stores y, the others add to it
         conv_plan one = *plan;
@@ -1654,7 +1721,7 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
         d.workgroups = (int64_t)cc.geom.strips * cc.geom.segs * cc.col_blocks;
     } else {
         const ApplyChoice c = choose_apply(&plan, batch);
-        d.kernel = c.kind == Kind::GatherScalar ? 0 : c.kind == Kind::GatherVec ? 1 : c.kind == Kind::Tile ? 2
+        d.kernel = c.kind == Kind::GatherScalar ? 0 : c.kind == Kind::GatherVec ? 1 : c.kind == Kind::Tile || c.kind == Kind::Block ? 2
                    : c.kind == Kind::March ? 3 : 9;
         d.threads = c.threads;
         d.lds_bytes = (int64_t)c.lds;
@@ -1676,6 +1743,11 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
             d.lines_per_step = c.ls;
             d.ring_lines_needed = tr ? (c.ls == 2 ? (k + 2) / s + 2 : k / s + 2) : s * (2 * c.ls - 1) + k;
             d.workgroups = (int64_t)c.march.strips * c.march.segs * column_blocks(batch, c.nv);
+        } else if (c.kind == Kind::Block) {
+            d.columns_per_lane = 4 * block_rx(k, s, plan.transposed) * c.tw;
+            d.strip = c.tw;
+            d.segment = block_rx(k, s, plan.transposed);
+            d.workgroups = (int64_t)c.block.cells * ((batch + (4LL << c.lpr_log2) - 1) / (4LL << c.lpr_log2));
         } else if (c.kind == Kind::Tile) {
             d.strip = c.tw;
             d.segment = c.geom.th;
@@ -1763,6 +1835,9 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch) {
                 snprintf(name, sizeof name, "lds_march_staged_%dx%d_ring%d_step%d_g%d_nit%d_float4x%d", c.march.seg, c.tw, c.nl, c.ls, c.g, c.nit, c.nv);
             else
                 snprintf(name, sizeof name, "lds_march_staged_%dx%d_ring%d_step%d_g%d_nit%d_scalar", c.march.seg, c.tw, c.nl, c.ls, c.g, c.nit);
+            break;
+        case Kind::Block:
+            snprintf(name, sizeof name, "block_%dx%d_lanes%d_float4", block_rx(plan->shape.k, plan->shape.s, plan->transposed), c.tw, 1 << c.lpr_log2);
             break;
         case Kind::Tile:
             snprintf(name, sizeof name, "lds_tile_%dx%d_g%d_nit%d_float4x%d", c.geom.th, c.tw, c.g, c.nit, c.nv);

@@ -1,0 +1,87 @@
+"""Products in blocks of outputs with the batch on the lanes (apply_block_kernel.h), T and T^T, against the oracle."""
+import numpy as np
+import pytest
+import scipy.sparse
+import torch
+
+import oracle
+import paper_2411_19419_amd as cs
+from gpu_util import REL_TOL, device
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [("csr", k, s) for s in (1, 2) for k in (2, 3, 4, 5)] + [("csc", 2, 1), ("csc", 3, 1)] + \
+    [("csc", k, s) for s in (2, 3, 4) for k in range(s + 1, 3 * s + 1)]
+
+
+def _check(got, ref, scale, what):
+    assert not np.any(np.isnan(got)), what
+    assert np.all(np.abs(got.astype(np.float64) - ref.astype(np.float64)) <= REL_TOL * scale), what
+
+
+@pytest.mark.parametrize("storage,k,s", SHAPES)
+def test_blocks_at_edges_and_paddings(storage, k, s):
+    """Planes that end anywhere in a block, padding from none to more than the kernel, lanes full and partly idle,
+    batches that are no multiple of 4, operands at any float address."""
+    rng = np.random.default_rng(100 * k + s)
+    conv = oracle.conv if storage == "csr" else oracle.conv_t
+    served = 0
+    for i, (p, batch) in enumerate(((0, 64), (k // 2, 125), (k - 1, 131), (k + 1, 49), (k // 2, 256))):
+        for m, n in ((92 * s + i, 90 * s + 2 * i + 1), (k + 2, 900 * s + i), (900 * s + i, k + 1), (k, 9 * s + i)):
+            K = rng.standard_normal(k * k).astype(np.float32)
+            plan = (cs.conv_csr_build if storage == "csr" else cs.conv_csc_build)(m, n, k, s, p, torch.from_numpy(K).to(device()))
+            served += plan.variant(batch).startswith("block_")
+            x = rng.standard_normal(plan.cols * batch).astype(np.float32)
+            xb = torch.full((x.size + 4,), 7.0, device=device())
+            yb = torch.full((plan.rows * batch + 8,), 7.0, device=device())
+            xd, yd = xb[i % 4:i % 4 + x.size], yb[4 - i % 4:4 - i % 4 + plan.rows * batch]
+            xd.copy_(torch.from_numpy(x))
+            yd.fill_(float("nan"))
+            cs.conv_spmv(plan, xd, yd, batch=batch)
+            torch.cuda.synchronize()
+            _check(yd.cpu().numpy(), *conv(m, n, k, s, p, x, K, batch=batch, want_scale=True), (m, n, p, batch))
+            edge = yb.cpu().numpy()
+            assert np.all(edge[:4 - i % 4] == 7.0) and np.all(edge[4 - i % 4 + plan.rows * batch:] == 7.0)
+            plan.close()
+    assert served >= 4
+
+
+@pytest.mark.parametrize("storage,shape,batch", [("csr", (60, 71, 3, 1, 1), 64), ("csr", (110, 83, 5, 2, 2), 112),
+                                                 ("csc", (60, 71, 3, 1, 1), 126), ("csc", (90, 83, 5, 2, 2), 60),
+                                                 ("csc", (130, 111, 7, 3, 3), 64)])
+def test_blocks_read_the_stored_arrays(storage, shape, batch):
+    """Columns redirected after the build, entries moved between neighbouring rows, infinite values: the product follows the
+    arrays; in image-border blocks too."""
+    m, n, k, s, p = shape
+    rng = np.random.default_rng(5)
+    K = rng.standard_normal(k * k).astype(np.float32)
+    plan = (cs.conv_csr_build if storage == "csr" else cs.conv_csc_build)(*shape, torch.from_numpy(K).to(device()))
+    assert plan.variant(batch).startswith("block_")
+    x = rng.standard_normal(plan.cols * batch).astype(np.float32)
+    xd = torch.from_numpy(x).to(device())
+    before = cs.conv_spmv(plan, xd, batch=batch).cpu().numpy().reshape(-1, batch)
+    ptr, idx, vals = (t.cpu().numpy().copy() for t in (plan.row_ptr, plan.col_idx, plan.vals))
+    rows = rng.choice(plan.rows - 2, size=40, replace=False)
+    rows = np.concatenate([rows[(np.diff(ptr)[rows] > 2) & (np.diff(ptr)[rows + 1] > 0)], [0]])
+    for i, row in enumerate(rows):
+        if i % 3 == 2:
+            ptr[row + 1] -= 1                    # the row's last entry goes to the next row
+        else:
+            idx[ptr[row] + i % 2] = rng.integers(plan.cols)
+    plan.row_ptr.copy_(torch.from_numpy(ptr))
+    plan.col_idx.copy_(torch.from_numpy(idx))
+    got = cs.conv_spmv(plan, xd, batch=batch).cpu().numpy().reshape(-1, batch)
+    # (copies: abs() merges duplicates in place)
+    T = scipy.sparse.csr_matrix((vals.astype(np.float64), idx.copy(), ptr.copy()), shape=(plan.rows, plan.cols))
+    x2 = x.reshape(-1, batch).astype(np.float64)
+    scale = abs(T) @ abs(x2)
+    assert np.all(np.abs(got - T @ x2) <= REL_TOL * scale + 1e-30)
+    changed = np.union1d(rows, rows + 1)
+    same = np.setdiff1d(np.arange(plan.rows), changed)
+    # (a wave with an edited row sums entry by entry: other roundings, no other result)
+    assert np.all(np.abs(got[same] - before[same]) <= 2 * REL_TOL * scale[same])
+    vals[ptr[rows[0]]] = np.inf
+    plan.vals.copy_(torch.from_numpy(vals))
+    hit = ~np.isfinite(cs.conv_spmv(plan, xd, batch=batch).cpu().numpy().reshape(-1, batch)).all(axis=1)
+    assert list(np.flatnonzero(hit)) == [rows[0]]
+    plan.close()

@@ -50,19 +50,19 @@ __host__ __device__ constexpr int block_row_taps(int d, int k, int s, bool tr) {
 // result line (pixel) at which the first block starts
 __host__ __device__ constexpr int block_first(int s, int p, bool tr) { return tr ? -(p % s) : 0; }
 
-// Outputs of a block, and which (k, s) are compiled.  T: pixels that fit 25 to 40 16-byte registers.  T^T: one or two
-// steps of the stride, so that an operand pixel serves as many results as it has.
+// Outputs of a block, and which (k, s) are compiled.  T: windows of at most 48 pixels (four registers each).  T^T: one or two
+// steps of the stride, so that an operand pixel serves as many results as it has, and windows of at most 40 pixels.
 __host__ __device__ constexpr bool block_compiled(int k, int s, bool tr) {
-    if (!tr) return s <= 2 && k >= 2 && k <= 5;
-    return (s == 1 && k >= 2 && k <= 3) || (s >= 2 && s <= 4 && k > s && k <= 3 * s);
+    if (!tr || s == 1) return (s <= 2 && k >= 2 && k <= 5) || (!tr && s <= 4 && k >= 3 && k <= 5);
+    return s <= 4 && k > s && k <= (s == 2 ? 5 : 4) * s && k <= 13;
 }
 __host__ __device__ constexpr int block_rx(int k, int s, bool tr) {
-    if (tr) return s > 2 ? s : 2;
-    return s == 1 ? (k == 5 ? 1 : 2) : (k == 4 ? 1 : 2);
+    if (tr && s > 1) return s;
+    return s == 1 ? (k == 5 ? 1 : 2) : s == 2 ? (k == 4 ? 1 : 2) : 1;
 }
 __host__ __device__ constexpr int block_ry(int k, int s, bool tr) {
-    if (tr) return s > 2 ? s : 2;
-    return s == 1 ? (k == 5 ? 4 : 2) : (k == 5 ? 1 : 2);
+    if (tr && s > 1) return s;
+    return s == 1 ? (k == 5 ? 4 : 2) : s == 2 ? (k == 5 ? 1 : 2) : k == 5 ? 1 : 2;
 }
 constexpr int kBlockLprLeast = 4, kBlockLprMost = 6;        // lanes over the batch: 16 to 64 (64 to 256 columns)
 

@@ -676,16 +676,24 @@ bool block_geometry(const conv_plan *plan, int batch, int *lpr_log2, BlockGeom *
 // k 4, batch 96: 40.8 and 11.8; 254^2, k 5, s 2, batch 100: 33.5 and 14.1; 595^2, k 5, batch 64: 71.0 and 67.2.
 // A fifth of the lanes idle: from 10 M multiply-adds on; below, it is a matter of a microsecond (72 x 60, k 3, batch 131: 7.3 with
 // tiles, 6.1 in blocks), and the tile kernel's ragged batches keep their place.
+// T^T at strides above 2 with 16 taps an output has the longest start (a block is 9 or 16 outputs): from 20 M where the tile kernel's
+// lanes are full (124 x 120, k 12, s 3, batch 64: 6.1 with tiles, 8.5 in blocks; 111 x 110, k 13, s 4, batch 256: 16.3 and 7.1; 110 x 105,
+// k 12, s 3, batch 72: 11.0 and 7.7), and so has k 5 at stride 1 (84 x 74, batch 64, 9.5 M: 6.9 and 7.8; 128^2, batch 128, 50 M:
+// 11.6 and 9.9).  25 taps for each of four outputs at stride 1 need columns on 5/8 of the lanes where the
+// marching kernel has whole chunks (191 x 180, batch 36: 16.3 marching, 17.6; batch 33, 162 x 155: 21.6 and 14.0).
 // T^T at k = s + 1, where most pixels have a single entry, stays with the tile kernel and the row groups where an eighth of the
 // lanes or more would idle (the shapes that test_dispatch_keeps_to_the_faster_kernel names for those two).
 constexpr int kBlockMinBatch = 33;
-constexpr int64_t kBlockMinWork = 4000000, kBlockMinWorkIdle = 10000000;
+constexpr int64_t kBlockMinWork = 4000000, kBlockMinWorkIdle = 10000000, kBlockMinWorkLong = 20000000;
 bool block_serves(const conv_plan *plan, int batch, int lpr_log2) {
     const ConvShape &sh = plan->shape;
     if (batch < kBlockMinBatch) return false;
     const int64_t columns = 4LL << lpr_log2, padded = (batch + columns - 1) / columns * columns;
     if (plan->transposed && sh.k == sh.s + 1 && sh.s > 1 && 8LL * batch <= 7 * padded) return false;
     if (5LL * batch < 4 * padded && plan->nnz * batch < kBlockMinWorkIdle) return false;
+    if (sh.k == 5 && sh.s == 1 && batch % 4 == 0 && 8LL * batch < 5 * padded) return false;
+    const bool longest = (plan->transposed && sh.s >= 3 && plan->max_row_nnz >= 16) || (sh.k == 5 && sh.s == 1);
+    if (longest && batch % 16 == 0 && plan->nnz * batch < kBlockMinWorkLong) return false;
     const bool long_start = plan->max_row_nnz >= 16 || (plan->transposed && sh.s >= 3);
     return !long_start || plan->nnz * batch >= kBlockMinWork;
 }

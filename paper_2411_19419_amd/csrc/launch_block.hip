@@ -33,6 +33,8 @@ void launch_block(const ApplyChoice &c, const conv_plan *plan, const float *x, f
     switch (plan->shape.s) {
         case 1: launch_s<1>(c, plan, x, y, q); break;
         case 2: launch_s<2>(c, plan, x, y, q); break;
+        case 3: launch_s<3>(c, plan, x, y, q); break;
+        case 4: launch_s<4>(c, plan, x, y, q); break;
     }
 }
 

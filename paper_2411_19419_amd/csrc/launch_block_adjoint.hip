@@ -33,6 +33,7 @@ static void launch_s(const ApplyChoice &c, const conv_plan *plan, const float *x
         case 10: launch_ks<10, S>(c, plan, x, y, q); break;
         case 11: launch_ks<11, S>(c, plan, x, y, q); break;
         case 12: launch_ks<12, S>(c, plan, x, y, q); break;
+        case 13: launch_ks<13, S>(c, plan, x, y, q); break;
     }
 }
 

@@ -8,12 +8,16 @@ import paper_2411_19419_amd as cs
     ((224, 224, 3, 1, 1), 256, 0, True), ((224, 224, 3, 1, 1), 33, 0, True), ((224, 224, 3, 1, 1), 32, 0, False),
     ((224, 224, 3, 1, 1), 256, 1, True), ((256, 256, 5, 2, 2), 64, 0, True), ((256, 256, 5, 2, 2), 64, 1, True),
     ((246, 246, 4, 1, 2), 96, 0, True), ((329, 300, 6, 2, 5), 100, 1, True), ((300, 300, 12, 4, 5), 64, 1, True),
-    # not compiled: 1 and 6 taps a side, strides above 2, T^T of more than 3 taps per axis and result
-    ((224, 224, 1, 1, 0), 256, 0, False), ((224, 224, 6, 1, 0), 256, 0, False), ((224, 224, 5, 3, 0), 256, 0, False),
-    ((224, 224, 4, 1, 1), 256, 1, False), ((224, 224, 7, 2, 3), 256, 1, False), ((224, 224, 3, 3, 1), 256, 1, False),
+    ((224, 224, 5, 3, 0), 256, 0, True), ((224, 224, 4, 1, 1), 256, 1, True), ((224, 224, 9, 2, 4), 256, 1, True),
+    # not compiled: 1 and 6 taps a side, strides above 4, T^T of more than 5 taps per axis and result (4 at strides 3 and 4)
+    ((224, 224, 1, 1, 0), 256, 0, False), ((224, 224, 6, 1, 0), 256, 0, False), ((224, 224, 5, 5, 0), 256, 0, False),
+    ((224, 224, 6, 1, 1), 256, 1, False), ((224, 224, 11, 2, 3), 256, 1, False), ((224, 224, 13, 3, 3), 256, 1, False),
+    ((224, 224, 3, 3, 1), 256, 1, False),
     # a long start for little work; idle lanes for little work; T^T of mostly single entries with idle lanes
     ((24, 25, 5, 1, 4), 131, 0, False), ((39, 40, 11, 4, 0), 128, 1, False), ((64, 90, 3, 1, 1), 131, 0, False),
     ((340, 367, 3, 2, 1), 160, 1, False), ((340, 367, 3, 2, 1), 192, 1, True),
+    ((124, 120, 12, 3, 6), 64, 1, False), ((124, 120, 12, 3, 6), 72, 1, True), ((191, 180, 5, 1, 4), 36, 1, False),
+    ((84, 74, 5, 1, 0), 64, 0, False), ((128, 128, 5, 1, 2), 128, 0, True),
     # byte offsets of 32 bits: operands of 4 GiB and more
     ((4000, 4000, 3, 1, 1), 68, 0, False), ((3900, 4000, 3, 1, 1), 68, 0, True),
 ])

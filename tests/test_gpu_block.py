@@ -10,8 +10,9 @@ from gpu_util import REL_TOL, device
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [("csr", k, s) for s in (1, 2) for k in (2, 3, 4, 5)] + [("csc", 2, 1), ("csc", 3, 1)] + \
-    [("csc", k, s) for s in (2, 3, 4) for k in range(s + 1, 3 * s + 1)]
+SHAPES = [("csr", k, s) for s in (1, 2) for k in (2, 3, 4, 5)] + [("csr", k, s) for s in (3, 4) for k in (3, 4, 5)] + \
+    [("csc", k, 1) for k in (2, 3, 4, 5)] + [("csc", k, 2) for k in range(3, 11)] + \
+    [("csc", k, 3) for k in range(4, 13)] + [("csc", k, 4) for k in range(5, 14)]
 
 
 def _check(got, ref, scale, what):
@@ -48,7 +49,8 @@ def test_blocks_at_edges_and_paddings(storage, k, s):
 
 @pytest.mark.parametrize("storage,shape,batch", [("csr", (60, 71, 3, 1, 1), 64), ("csr", (110, 83, 5, 2, 2), 112),
                                                  ("csc", (60, 71, 3, 1, 1), 126), ("csc", (90, 83, 5, 2, 2), 60),
-                                                 ("csc", (130, 111, 7, 3, 3), 64)])
+                                                 ("csc", (130, 111, 7, 3, 3), 64), ("csc", (100, 93, 9, 2, 4), 64),
+                                                 ("csr", (160, 163, 5, 3, 2), 64)])
 def test_blocks_read_the_stored_arrays(storage, shape, batch):
     """Columns redirected after the build, entries moved between neighbouring rows, infinite values: the product follows the
     arrays; in image-border blocks too."""

@@ -202,15 +202,16 @@ int conv_spmv(const conv_plan *plan, const float *x_dev, float *y_dev, int batch
  * Where the entries of an output lie in the arrays follows from the geometry,
  * and products of some size (s <= k, p < k, ceil(k/s) <= 13) gather them: every
  * output is summed in registers, from entries whose stored row index is
- * compared with the one their place asks for; outputs of a workgroup that found
- * another one, or another column pointer, are summed again from whatever the
- * arrays hold.  Otherwise y is zeroed and the sums of a tile of neighbouring
- * pixels are collected on chip and added to y with hardware float adds (for
- * 2 <= ceil(k/s) <= 32, from 3 at batches below 4), or every entry is added to y
- * directly.  The result is that of conv_spmv on the CSR plan of the same T up to
- * the order of the additions, which in the scatters depends on timing: repeated
- * calls agree to rounding, not bit for bit.  The arrays are read as stored: every row_idx must be in
- * [0, m_out*n_out), col_ptr non-decreasing, no column longer than ceil(k/s)^2
+ * compared with the one their place asks for.  Arrays found to hold another one,
+ * or another column pointer, are multiplied by the scatter instead, behind the
+ * gather in that call and in its place in the plan's later ones.  The scatter:
+ * y is zeroed and the sums of a tile of neighbouring pixels are collected on
+ * chip and added to y with hardware float adds (for 2 <= ceil(k/s) <= 32, from 3
+ * at batches below 4), or every entry is added to y directly.  The result is
+ * that of conv_spmv on the CSR plan of the same T up to the order of the
+ * additions, which in the scatters depends on timing: repeated calls agree to
+ * rounding, not bit for bit.  The arrays are read as stored: every row_idx must
+ * be in [0, m_out*n_out), col_ptr non-decreasing, no column longer than ceil(k/s)^2
  * entries (the longest conv_csc_build writes), and the row indices of one
  * column pairwise different, as conv_csc_build writes them (a row stored twice
  * in one column may lose one of its two contributions). */

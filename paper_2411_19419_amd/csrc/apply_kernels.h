@@ -183,8 +183,15 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_gather_vec_kernel(
 // column j contributes vals[e] * x[j] to row row_idx[e].  G lanes share a column; each
 // contribution is one hardware float add to y (zeroed beforehand by fill_zero_kernel), so
 // the summation order, unlike everywhere else in this library, depends on timing.
+//
+// EDITED: the two launches behind a product that gathers (csc_gather_kernel.h), which return at once unless the arrays were
+// noted as edited.  They walk their work with about as many workgroups as run at once: a product sees 1.6 us of an idle
+// launch of 512 workgroups, 1.9 of one of 2048, 4.6 of one of 16384.  The scatter's walk, 1024^2, k 7, batch 16: 1024
+// workgroups 500 us, 1536 408, 1792 490, 4096 390, a workgroup for every tile 358.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kGatherThreads) void fill_zero_kernel(float *__restrict__ y, long long count) {
+template <bool EDITED>
+__global__ __launch_bounds__(kGatherThreads) void fill_zero_kernel(float *__restrict__ y, long long count, const EditedWord edited) {
+    if (EDITED && !noted_edited(edited)) return;
     const long long stride = (long long)gridDim.x * kGatherThreads;
     const long long first = (long long)blockIdx.x * kGatherThreads + threadIdx.x;
     // 16-byte stores over the aligned middle, single floats before and after it
@@ -198,18 +205,21 @@ __global__ __launch_bounds__(kGatherThreads) void fill_zero_kernel(float *__rest
 
 // BL consecutive lanes take BL neighbouring batch columns of one entry, so that their adds fall
 // into one 64-byte line of y and travel to the L2 as one request.
-template <int G, int BL>
+template <int G, int BL, bool EDITED>
 __global__ __launch_bounds__(kGatherThreads) void spmm_scatter_kernel(
     const int *__restrict__ col_ptr, const int *__restrict__ row_idx, const float *__restrict__ vals,
-    const float *__restrict__ x, float *__restrict__ y, int cols, int batch) {
-    const long long col = ((long long)blockIdx.x * kGatherThreads + threadIdx.x) / (G * BL);
+    const float *__restrict__ x, float *__restrict__ y, int cols, int batch, const EditedWord edited) {
+    if (EDITED && !noted_edited(edited)) return;
     const int r = (int)threadIdx.x % (G * BL), lane = r / BL, bl = r % BL;
-    if (col >= cols) return;
-    const unsigned beg = col_ptr[col], end = col_ptr[col + 1];
-    for (int c = blockIdx.y * BL + bl; c < batch; c += gridDim.y * BL) {
-        const float xv = x[col * batch + c];
-        for (unsigned e = beg + lane; e < end; e += G)
-            unsafeAtomicAdd(y + (long long)row_idx[e] * batch + c, vals[e] * xv);
+    long long col = ((long long)blockIdx.x * kGatherThreads + threadIdx.x) / (G * BL);
+    for (; col < cols; col += (long long)gridDim.x * (kGatherThreads / (G * BL))) {
+        const unsigned beg = col_ptr[col], end = col_ptr[col + 1];
+        for (int c = blockIdx.y * BL + bl; c < batch; c += gridDim.y * BL) {
+            const float xv = x[col * batch + c];
+            for (unsigned e = beg + lane; e < end; e += G)
+                unsafeAtomicAdd(y + (long long)row_idx[e] * batch + c, vals[e] * xv);
+        }
+        if (!EDITED) return;                     // (a thread for every column)
     }
 }
 
@@ -240,7 +250,7 @@ constexpr int kCscStage = 1024;      // most entries of one tile line (tj column
 
 struct CscTileGeom {
     int m, n, n_out, k, s, p, batch;
-    int ti, tj, tiles_j;           // tile: ti lines of tj pixels, tj < 64; tiles per line of tiles
+    int ti, tj, tiles_j, tiles;    // tile: ti lines of tj pixels, tj < 64; tiles per line of tiles; tiles
     int wx, wy;                    // window: runs x rows per run
     int limit;                     // (wx - 1) * n_out + wy, at most 2^21: rows base .. base + limit - 1 can be in the window
     int stage;                     // entries per stage buffer, tj * (most entries of a column) <= kCscStage
@@ -256,16 +266,16 @@ __device__ __forceinline__ int first_window(int t0, int k, int s, int p) {   // 
 }
 
 template <int VB, int W>
-__global__ __launch_bounds__(W *kWave) void spmm_csc_tile_kernel(
+__device__ __forceinline__ void csc_tile(
     const int *__restrict__ col_ptr, const int *__restrict__ row_idx, const float *__restrict__ vals,
-    const float *__restrict__ x, float *__restrict__ y, const CscTileGeom g) {
+    const float *__restrict__ x, float *__restrict__ y, const CscTileGeom &g, int tile) {
     constexpr int NT = W * kWave, BC = W * VB;   // threads; batch columns per pass
     constexpr int PER = kCscStage / NT;          // staged entries per thread
     extern __shared__ __align__(16) int lds[];
     int2 *const stage = reinterpret_cast<int2 *>(lds);                     // [2][g.stage] (window slot or -1, value bits)
     int *const ptrs = lds + 4 * g.stage;                                   // [ti][tj + 1] column pointers
     float *const win = reinterpret_cast<float *>(ptrs + g.ptrs);           // [W][VB / 4][wx][wy][4] ([W][wx][wy][VB] for VB < 4)
-    const int tile_i = (int)blockIdx.x / g.tiles_j, tile_j = (int)blockIdx.x - tile_i * g.tiles_j;
+    const int tile_i = tile / g.tiles_j, tile_j = tile - tile_i * g.tiles_j;
     const int i0 = tile_i * g.ti, j0 = tile_j * g.tj;
     // first row of the window; below 2^31 like every row
     const int base = first_window(i0, g.k, g.s, g.p) * g.n_out + first_window(j0, g.k, g.s, g.p);
@@ -450,6 +460,21 @@ __global__ __launch_bounds__(W *kWave) void spmm_csc_tile_kernel(
                 unsafeAtomicAdd(y + ((long long)base + slot + (long long)lx * skip) * g.batch + c0 + b, v);
         }
         __syncthreads();
+    }
+}
+
+template <int VB, int W, bool EDITED>
+__global__ __launch_bounds__(W *kWave) void spmm_csc_tile_kernel(
+    const int *__restrict__ col_ptr, const int *__restrict__ row_idx, const float *__restrict__ vals,
+    const float *__restrict__ x, float *__restrict__ y, const CscTileGeom g, const EditedWord edited) {
+    if constexpr (EDITED) {
+        if (!noted_edited(edited)) return;
+        for (unsigned tile = blockIdx.x; tile < (unsigned)g.tiles; tile += gridDim.x) {
+            csc_tile<VB, W>(col_ptr, row_idx, vals, x, y, g, (int)tile);
+            __syncthreads();
+        }
+    } else {
+        csc_tile<VB, W>(col_ptr, row_idx, vals, x, y, g, (int)blockIdx.x);
     }
 }
 

@@ -1,5 +1,8 @@
 // Host side of the C ABI declared in include/convspmv.h: argument checking,
 // the closed-form count of Theorem 2.1, the plan object and kernel dispatch.
+#include <pthread.h>
+
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -43,6 +46,56 @@ struct LaunchScope {
         return false;
     }
 };
+
+// The words (device_util.h) in which products from column-compressed arrays note edited columns: a static array of every
+// device, so that a build allocates nothing.  A plan has its place to itself until it is destroyed, which is after its
+// last product; places are taken again in the order in which they came back, with another stamp.  A plan that finds
+// none left (65536 plans at a time) scatters.
+constexpr int kEditedWords = 1 << 16;
+__device__ unsigned edited_words[kEditedWords];
+
+struct EditedPlaces {
+    pthread_mutex_t lock = PTHREAD_MUTEX_INITIALIZER;
+    int fresh = 0, oldest = 0, returned = 0;      // places never taken; those given back, a ring
+    int ring[kEditedWords];
+    unsigned stamp[kEditedWords];
+
+    int take(unsigned *stamp_out) {
+        pthread_mutex_lock(&lock);
+        int slot = -1;
+        if (fresh < kEditedWords) {
+            slot = fresh++;
+        } else if (returned > 0) {
+            slot = ring[oldest];
+            oldest = (oldest + 1) % kEditedWords;
+            --returned;
+        }
+        if (slot >= 0) {
+            if (++stamp[slot] == 0) ++stamp[slot];     // (the array begins with zeros)
+            *stamp_out = stamp[slot];
+        }
+        pthread_mutex_unlock(&lock);
+        return slot;
+    }
+    void give_back(int slot) {
+        pthread_mutex_lock(&lock);
+        ring[(oldest + returned++) % kEditedWords] = slot;
+        pthread_mutex_unlock(&lock);
+    }
+};
+EditedPlaces edited_places;
+
+unsigned *edited_words_of(int device) {
+    static std::atomic<unsigned *> known[64];
+    const bool keep = device >= 0 && device < 64;
+    unsigned *base = keep ? known[device].load(std::memory_order_relaxed) : nullptr;
+    if (!base && hipGetSymbolAddress((void **)&base, HIP_SYMBOL(edited_words)) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (keep) known[device].store(base, std::memory_order_relaxed);
+    return base;
+}
 
 // Theorem 2.1, output extent along one axis (0 = precondition violated).
 int64_t out_extent(int64_t extent, int64_t k, int64_t s, int64_t p) {
@@ -238,6 +291,11 @@ int build_impl(int m, int n, int k, int s, int p, int channels, const float *ker
     if (!scope.ok()) {
         delete plan;
         return CONV_EHIP;
+    }
+    if (TR) {
+        unsigned *const words = edited_words_of(plan->device);
+        plan->edited_place = words ? edited_places.take(&plan->edited.stamp) : -1;
+        if (plan->edited_place >= 0) plan->edited.word = words + plan->edited_place;
     }
     *plan_out = plan;
     return CONV_OK;
@@ -1340,6 +1398,7 @@ static CscTileChoice choose_csc_tile(const conv_plan *plan, int batch) {
                     g.limit = (int)limit; g.stage = (int)stage; g.ptrs = (int)ptrs;
                     c.lds = (size_t)lds;
                     c.grid = dim3((unsigned)blocks, (unsigned)chunks);
+                    g.tiles = (int)blocks;
                 }
             }
         }
@@ -1349,11 +1408,62 @@ static CscTileChoice choose_csc_tile(const conv_plan *plan, int batch) {
     return c;
 }
 
-template <int VB, int W>
+// The scatter: a product by itself, or (EDITED) what a product that gathers leaves to do where arrays were edited.
+constexpr unsigned kEditedWaves = 6144, kEditedBlocks = 4096, kEditedFillBlocks = 256;
+template <bool EDITED>
+static dim3 scatter_grid(unsigned blocks, unsigned chunks, unsigned waves_per_block) {
+    if (!EDITED) return dim3(blocks, chunks);
+    const unsigned most = std::min(kEditedWaves / waves_per_block, kEditedBlocks);
+    blocks = std::min(blocks, most);
+    return dim3(blocks, std::min(chunks, most / blocks));
+}
+
+template <int VB, int W, bool EDITED>
 static void launch_csc_tile(const CscTileChoice &c, const conv_plan *plan, const float *x_dev, float *y_dev,
                             hipStream_t q) {
-    spmm_csc_tile_kernel<VB, W><<<c.grid, W * kWave, c.lds, q>>>(plan->row_ptr, plan->col_idx, plan->vals, x_dev, y_dev,
-                                                                 c.g);
+    spmm_csc_tile_kernel<VB, W, EDITED><<<scatter_grid<EDITED>(c.grid.x, c.grid.y, W), W * kWave, c.lds, q>>>(
+        plan->row_ptr, plan->col_idx, plan->vals, x_dev, y_dev, c.g, plan->edited);
+}
+
+// y zeroed, then every entry added.  The plan's "rows" are the columns of T (input pixels), its "cols" the rows of T.
+template <bool EDITED>
+static int enqueue_csc_scatter(const conv_plan *plan, const float *x_dev, float *y_dev, int batch, hipStream_t q) {
+    const long long count = (long long)plan->cols * batch;
+    const unsigned fill_blocks = (unsigned)std::min<long long>((count / 4 + kGatherThreads) / kGatherThreads, EDITED ? kEditedFillBlocks : 1 << 16);
+    fill_zero_kernel<EDITED><<<fill_blocks, kGatherThreads, 0, q>>>(y_dev, count, plan->edited);
+    if (plan->nnz == 0) return CONV_OK;
+    const CscTileChoice tc = choose_csc_tile(plan, batch);
+    if (tc.ok) {
+        if (tc.vb == 1) launch_csc_tile<1, 1, EDITED>(tc, plan, x_dev, y_dev, q);
+        else if (tc.vb == 2) launch_csc_tile<2, 1, EDITED>(tc, plan, x_dev, y_dev, q);
+        else if (tc.waves == 1) launch_csc_tile<4, 1, EDITED>(tc, plan, x_dev, y_dev, q);
+        else if (tc.waves == 2) launch_csc_tile<4, 2, EDITED>(tc, plan, x_dev, y_dev, q);
+        else launch_csc_tile<4, 4, EDITED>(tc, plan, x_dev, y_dev, q);
+        return CONV_OK;
+    }
+    const int g = group_width(plan->max_row_nnz);
+    const int bl = batch >= 16 ? 16 : (batch >= 4 ? 4 : 1);      // lanes across the batch
+    const int64_t blocks = (plan->rows * g * bl + kGatherThreads - 1) / kGatherThreads;
+    if (blocks > kInt32Limit) return CONV_EOVERFLOW;
+    const dim3 grid = scatter_grid<EDITED>((unsigned)blocks, (unsigned)std::min((batch + bl - 1) / bl, 65535), kGatherThreads / kWave);
+    const int cols = (int)plan->rows;
+#define CONV_SCATTER_BL(G, BL)                                                                                      \
+    spmm_scatter_kernel<G, BL, EDITED><<<grid, kGatherThreads, 0, q>>>(plan->row_ptr, plan->col_idx, plan->vals, x_dev, \
+                                                                       y_dev, cols, batch, plan->edited)
+#define CONV_SCATTER(G)                                  \
+    if (bl == 16) CONV_SCATTER_BL(G, 16);                \
+    else if (bl == 4) CONV_SCATTER_BL(G, 4);             \
+    else CONV_SCATTER_BL(G, 1)
+    switch (g) {
+        case 1: CONV_SCATTER(1); break;
+        case 2: CONV_SCATTER(2); break;
+        case 4: CONV_SCATTER(4); break;
+        case 8: CONV_SCATTER(8); break;
+        default: CONV_SCATTER(16); break;
+    }
+#undef CONV_SCATTER_BL
+#undef CONV_SCATTER
+    return CONV_OK;
 }
 
 // Launch shape of the product from the column-compressed arrays that gathers (csc_gather_kernel.h).
@@ -1449,50 +1559,11 @@ int conv_spmv_from_csc(const conv_plan *plan, const float *x_dev, float *y_dev, 
     }
     hipStream_t q = (hipStream_t)stream;
     const LaunchScope scope;
-    if (plan->nnz > 0) {
-        const CscGatherChoice gather = choose_csc_gather(plan, batch);
-        if (gather.ok) {
-            launch_csc_gather(gather, plan, x_dev, y_dev, q);
-            return scope.ok() ? CONV_OK : CONV_EHIP;
-        }
-    }
-    const long long count = (long long)out_pixels * batch;
-    const unsigned fill_blocks = (unsigned)std::min<long long>((count / 4 + kGatherThreads) / kGatherThreads, 1 << 16);
-    fill_zero_kernel<<<fill_blocks, kGatherThreads, 0, q>>>(y_dev, count);
-    CscTileChoice tc{};
-    if (plan->nnz > 0) tc = choose_csc_tile(plan, batch);
-    if (tc.ok) {
-        if (tc.vb == 1) launch_csc_tile<1, 1>(tc, plan, x_dev, y_dev, q);
-        else if (tc.vb == 2) launch_csc_tile<2, 1>(tc, plan, x_dev, y_dev, q);
-        else if (tc.waves == 1) launch_csc_tile<4, 1>(tc, plan, x_dev, y_dev, q);
-        else if (tc.waves == 2) launch_csc_tile<4, 2>(tc, plan, x_dev, y_dev, q);
-        else launch_csc_tile<4, 4>(tc, plan, x_dev, y_dev, q);
-    } else if (plan->nnz > 0) {
-        const int g = group_width(plan->max_row_nnz);
-        const int bl = batch >= 16 ? 16 : (batch >= 4 ? 4 : 1);      // lanes across the batch
-        const int64_t blocks = (in_pixels * g * bl + kGatherThreads - 1) / kGatherThreads;
-        if (blocks > kInt32Limit) return CONV_EOVERFLOW;
-        const unsigned bx = (unsigned)blocks;
-        const unsigned by = (unsigned)std::min((batch + bl - 1) / bl, 65535);
-        const dim3 grid(bx, by);
-        const int cols = (int)in_pixels;
-#define CONV_SCATTER_BL(G, BL)                                                                              \
-    spmm_scatter_kernel<G, BL><<<grid, kGatherThreads, 0, q>>>(plan->row_ptr, plan->col_idx, plan->vals, x_dev, \
-                                                               y_dev, cols, batch)
-#define CONV_SCATTER(G)                                  \
-    if (bl == 16) CONV_SCATTER_BL(G, 16);                \
-    else if (bl == 4) CONV_SCATTER_BL(G, 4);             \
-    else CONV_SCATTER_BL(G, 1)
-        switch (g) {
-            case 1: CONV_SCATTER(1); break;
-            case 2: CONV_SCATTER(2); break;
-            case 4: CONV_SCATTER(4); break;
-            case 8: CONV_SCATTER(8); break;
-            default: CONV_SCATTER(16); break;
-        }
-#undef CONV_SCATTER_BL
-#undef CONV_SCATTER
-    }
+    const CscGatherChoice gather = plan->nnz > 0 && plan->edited.word ? choose_csc_gather(plan, batch) : CscGatherChoice{};
+    if (gather.ok) launch_csc_gather(gather, plan, x_dev, y_dev, q);      // (then the scatter, should the arrays turn out edited)
+    const int st = gather.ok ? enqueue_csc_scatter<true>(plan, x_dev, y_dev, batch, q)
+                             : enqueue_csc_scatter<false>(plan, x_dev, y_dev, batch, q);
+    if (st != CONV_OK) return st;
     return scope.ok() ? CONV_OK : CONV_EHIP;
 }
 
@@ -1862,6 +1933,7 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch) {
 
 int conv_plan_destroy(conv_plan *plan) {
     if (!plan) return CONV_OK;
+    if (plan->edited.word) edited_places.give_back(plan->edited_place);
     delete plan;          // a plan owns no device memory
     return CONV_OK;
 }

@@ -1,5 +1,4 @@
 // Launches of the product from the column-compressed arrays that sums every output where it stays.
-#include "csc_gather_mend_kernel.h"
 #include "dispatch.h"
 
 namespace convspmv {
@@ -7,7 +6,7 @@ namespace convspmv {
 template <int KL, int STRIDE, int TW, int LPR_LOG2, bool SCALAR, int NLD, int NX, int DEPTH>
 void launch_csc_gather_inst(const CscGatherChoice &c, const conv_plan *plan, const float *x, float *y, hipStream_t q) {
     spmm_csc_gather_kernel<KL, STRIDE, TW, LPR_LOG2, SCALAR, NLD, NX, DEPTH><<<c.geom.blocks_per_xcd * kXcds, kCscGatherThreads, c.lds, q>>>(
-        plan->row_ptr, plan->col_idx, plan->vals, x, y, c.geom);
+        plan->row_ptr, plan->col_idx, plan->vals, x, y, c.geom, plan->edited);
 }
 
 // stride 1: the kernels that know their strip
@@ -55,9 +54,6 @@ void launch_csc_gather_any(const CscGatherChoice &c, const conv_plan *plan, cons
 void launch_csc_gather(const CscGatherChoice &c, const conv_plan *plan, const float *x, float *y, hipStream_t q) {
     if (c.scalar) launch_csc_gather_any<true>(c, plan, x, y, q);
     else launch_csc_gather_any<false>(c, plan, x, y, q);
-    const int blocks = c.geom.blocks_per_xcd * kXcds, columns = c.scalar ? 1 : 4 << c.geom.lpr_log2;
-    csc_gather_mend_kernel<<<blocks, kCscGatherThreads, (size_t)(blocks + 31) / 32 * 4, q>>>(plan->row_ptr, plan->col_idx, plan->vals, x,
-                                                                                          y, c.geom, columns);
 }
 
 }  // namespace convspmv

@@ -134,3 +134,125 @@ def test_an_infinite_pixel_reaches_only_its_windows(shape, batch):
     got = y.cpu().numpy()
     assert np.array_equal(np.isfinite(got), np.isfinite(ref)) and np.array_equal(np.isnan(got), np.isnan(ref))
     plan.close()
+
+
+def median_us(run, repeats=9):
+    """Median time of run() on the device, one call at a time, after three calls."""
+    for _ in range(3):
+        run()
+    times = []
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(1e3 * a.elapsed_time(b))
+    return sorted(times)[repeats // 2]
+
+
+@pytest.mark.parametrize("edit", ["one", "every column"])
+def test_edited_arrays_cost_no_more_than_a_scatter(edit):
+    """Columns that are not as built are left to the scatter, which takes three to four times as long as the gather at this shape
+    whatever the arrays hold: six times bounds the two together (every workgroup's outputs summed again took 70)."""
+    shape, batch = (1024, 1024, 7, 1, 3), 16
+    x, K = inputs(shape, batch, 12)
+    plan, other = build_plan_t(shape, K), build_plan_t(shape, K)
+    xd = torch.from_numpy(x).to(device())
+    y = torch.empty(plan.cols * batch, device=device())
+    as_built = median_us(lambda: cs.conv_spmv_from_csc(plan, xd, y, batch=batch))
+    cols = slice(500 * 1024 + 37, 500 * 1024 + 38) if edit == "one" else slice(0, plan.rows)
+    first = plan.row_ptr[:-1][cols].long()
+    swapped = plan.col_idx[first + 1].clone()                        # the first two entries of a column change places
+    plan.col_idx[first + 1] = plan.col_idx[first]
+    plan.col_idx[first] = swapped
+    edited = median_us(lambda: cs.conv_spmv_from_csc(plan, xd, y, batch=batch))
+    assert edited <= 6 * as_built, (as_built, edited)
+    untouched = median_us(lambda: cs.conv_spmv_from_csc(other, xd, y, batch=batch))     # another plan is not slowed by it
+    assert untouched <= 1.5 * as_built, (as_built, untouched)
+    plan.close()
+    other.close()
+
+
+@pytest.mark.parametrize("shape,batch", [((96, 180, 7, 1, 3), 16), ((130, 150, 3, 1, 1), 18), ((120, 133, 5, 2, 2), 5),
+                                         ((140, 150, 9, 4, 4), 1), ((150, 140, 1, 1, 0), 20), ((200, 190, 4, 2, 1), 3)])
+def test_an_infinite_pixel_does_not_reach_what_its_edited_column_left(shape, batch):
+    """Of pixels that are infinite, the entries are sent elsewhere: the outputs they have left stay finite."""
+    import scipy.sparse as sp
+    m, n, k, s, p = shape
+    x, K = inputs(shape, batch, 15)
+    K[K == 0] = 1.0
+    plan = plan_of(shape, K, batch)
+    cp, ri, va = (np.array(a) for a in oracle.csc(*shape, K))
+    X = x.reshape(-1, batch)
+    for col in (n + 2, (m // 2) * n + n // 2, (m // 2) * n + n // 2 + 1, (m - 1) * n + n - 2, (m // 3) * n + 63, (m // 3) * n + 64):
+        X[col] = np.inf
+        ri[cp[col]:cp[col + 1]] = np.arange(cp[col + 1] - cp[col]) + (3 * col) % (plan.cols - 200)
+    plan.col_idx.copy_(torch.from_numpy(ri.astype(np.int32)))
+    y = cs.conv_spmv_from_csc(plan, torch.from_numpy(X.reshape(-1)).to(device()), batch=batch)
+    torch.cuda.synchronize()
+    T = sp.csc_matrix((va.astype(np.float64), ri, cp), shape=(plan.cols, plan.rows))
+    finite = np.isfinite(T @ np.where(np.isinf(X), np.inf, 0.0).astype(np.float64))
+    got = y.cpu().numpy().reshape(-1, batch)
+    assert np.array_equal(np.isfinite(got), finite) and not finite.all()
+    X0 = np.where(np.isinf(X), 0.0, X).astype(np.float64)
+    assert np.all(np.abs(got - T @ X0)[finite] <= (REL_TOL * (abs(T) @ np.abs(X0)) + 1e-30)[finite])
+    plan.close()
+
+
+def test_replays_follow_arrays_edited_between_them():
+    """A captured product, replayed on arrays as built, edited, and as built again."""
+    import scipy.sparse as sp
+    shape, batch = (120, 133, 5, 1, 2), 9
+    x, K = inputs(shape, batch, 13)
+    plan = plan_of(shape, K, batch)
+    cp, ri, va = (np.array(a) for a in oracle.csc(*shape, K))
+    xd = torch.from_numpy(x).to(device())
+    y = torch.empty(plan.cols * batch, device=device())
+    cs.conv_spmv_from_csc(plan, xd, y, batch=batch)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cs.conv_spmv_from_csc(plan, xd, y, batch=batch)
+    e = int(cp[61 * 133 + 40])
+    for rep in range(6):
+        rows = ri.copy()
+        if rep in (1, 2, 4):
+            rows[e + rep] = 7 * rep
+        plan.col_idx.copy_(torch.from_numpy(rows.astype(np.int32)))
+        y.fill_(float("nan"))
+        graph.replay()
+        eager = cs.conv_spmv_from_csc(plan, xd, batch=batch)
+        torch.cuda.synchronize()
+        T = sp.csc_matrix((va.astype(np.float64), rows, cp), shape=(plan.cols, plan.rows))
+        X = x.reshape(-1, batch).astype(np.float64)
+        want, scale = T @ X, abs(T) @ np.abs(X)
+        for got in (y, eager):
+            assert np.all(np.abs(got.cpu().numpy().reshape(-1, batch) - want) <= REL_TOL * scale + 1e-30), rep
+    plan.close()
+
+
+def test_a_plan_edited_on_two_streams_at_once():
+    """Products of one edited plan side by side on two streams, of two batches (two launch shapes), first calls included."""
+    import scipy.sparse as sp
+    shape = (300, 260, 7, 1, 3)
+    x, K = inputs(shape, 16, 14)
+    cp, ri, va = (np.array(a) for a in oracle.csc(*shape, K))
+    ri[int(cp[150 * 260 + 99]) + 3] = 5
+    T = sp.csc_matrix((va.astype(np.float64), ri, cp), shape=(300 * 260, 300 * 260))
+    xs = {b: torch.from_numpy(x[:300 * 260 * b]).to(device()) for b in (5, 16)}
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for rep in range(8):
+        plan = plan_of(shape, K, 16)
+        plan.col_idx.copy_(torch.from_numpy(ri.astype(np.int32)))
+        ys = [torch.full((plan.cols * b,), float("nan"), device=device()) for b in (5, 16, 5, 16)]
+        torch.cuda.synchronize()
+        for i, y in enumerate(ys):
+            b = y.numel() // plan.cols
+            cs.conv_spmv_from_csc(plan, xs[b], y, batch=b, stream=streams[(i + rep) % 2])
+        torch.cuda.synchronize()
+        for y in ys:
+            b = y.numel() // plan.cols
+            X = xs[b].cpu().numpy().reshape(-1, b).astype(np.float64)
+            assert np.all(np.abs(y.cpu().numpy().reshape(-1, b) - T @ X) <= REL_TOL * (abs(T) @ np.abs(X)) + 1e-30), (rep, b)
+        plan.close()

@@ -726,37 +726,58 @@ bool block_geometry(const conv_plan *plan, int batch, int *lpr_log2, BlockGeom *
     return true;
 }
 
-// Where the block kernel takes a product: batches above 32 columns (lanes for 64 at least; below, the tile kernel's 16 columns per
-// lane are as good: 224^2, k 3, batch 16: 6.0 us, blocks with 4 lanes a pixel 7.1), and multiply-adds enough for its start, which
-// waits for row pointers, then entries, then sums, where a block has many entries (24 x 25, k 5, batch 131, 1.9 M: 6.7 us in row
-// groups, 8.3 in blocks; 39 x 40, k 11, s 4, T^T, batch 128, 1.6 M: 5.7 and 6.5; above it 134 x 130, k 7, s 3, T^T, batch 72, 6.8 M:
-// 7.9 and 6.2; 64 x 60, k 5, batch 176, 20 M: 11.2 and 10.3).  Against the marching kernels, which it replaces at k 4 and 5: 246^2,
-// k 4, batch 96: 40.8 and 11.8; 254^2, k 5, s 2, batch 100: 33.5 and 14.1; 595^2, k 5, batch 64: 71.0 and 67.2.
-// A fifth of the lanes idle: from 10 M multiply-adds on; below, it is a matter of a microsecond (72 x 60, k 3, batch 131: 7.3 with
-// tiles, 6.1 in blocks), and the tile kernel's ragged batches keep their place.
-// T^T at strides above 2 with 16 taps an output has the longest start (a block is 9 or 16 outputs): from 20 M where the tile kernel's
-// lanes are full (124 x 120, k 12, s 3, batch 64: 6.1 with tiles, 8.5 in blocks; 111 x 110, k 13, s 4, batch 256: 16.3 and 7.1; 110 x 105,
-// k 12, s 3, batch 72: 11.0 and 7.7), and so has k 5 at stride 1 (84 x 74, batch 64, 9.5 M: 6.9 and 7.8; 128^2, batch 128, 50 M:
-// 11.6 and 9.9).  25 taps for each of four outputs at stride 1 need columns on 5/8 of the lanes where the
-// marching kernel has whole chunks (191 x 180, batch 36: 16.3 marching, 17.6; batch 33, 162 x 155: 21.6 and 14.0).
-// T^T at k = s + 1, where most pixels have a single entry, stays with the tile kernel and the row groups where an eighth of the
-// lanes or more would idle (the shapes that test_dispatch_keeps_to_the_faster_kernel names for those two).
+// Where the block kernel takes a product from the kernel that would have it otherwise: batches above 32 columns (lanes for 64 at
+// least; below, the tile kernel's 16 columns per lane are as good: 224^2, k 3, batch 16: 6.0 us, blocks with 4 lanes a pixel 7.1).
+// The lines lie where 26 000 products (planes of 16 to 700 a side, batches of 33 to 256, every (k, s) compiled) had the block
+// kernel and the other one even.  A marching kernel walks and loses everywhere, if its rows are long too (246^2, k 4,
+// batch 96: 30.8 us and 13.3; 192^2, k 11, s 3, T^T, batch 192: 54 and 13.4), but for 25 taps at stride 1, where it depends on how full
+// the lanes and how full the marching kernel's rounds of workgroups are: of 6900 more products of that kind its time is
+// within 10 % of what block_march_ns says, the block kernel's within 14 % of block_ns, and the smaller of the two names
+// the faster kernel in all but 170 (in blocks 550 of them are slower, up to 1.36 times: 182 x 111, batch 144: 16.9 us
+// marching, 23.0; 475 x 679, batch 80: 100 and 117; but 128^2, batch 128: 11.6 and 9.9).  Tiles and row groups start at once, where a
+// block waits for row pointers, then entries, then sums, the longer the more entries it has.  Blocks of few entries
+// are even with them where the launch is all there is (up to 1.5 M multiply-adds) and faster above; from then on, least work in
+// millions of multiply-adds for medians of 0.95 of the other's time and less:
+//   T:    16 taps, s 1: 8 (below 1.02 to 1.1); 25 taps, s 2: 20 (below 0.95 to 1.2); 25 taps, s 1: tiles stay (1.0 to 1.3)
+//   T^T:  9 taps, s 3: 8, s 4: 10 (below up to 1.3); 16 taps, s 1 and 2: 6, s 4: 15, s 3: tiles stay (1.1); 25 taps: tiles stay
+// (340 x 367, k 3, s 2, T^T, batch 160: 34 us with tiles, 15 in blocks; batch 168: 70 in row groups, 30; 93 x 124, k 5, T^T, batch 160: 10.4 with
+// tiles, 15.4 in blocks; 37 x 48, k 12, s 3, T^T, batch 178: 5.3 in row groups, 8.4 in blocks.)  Of the 26 000, 70 are more than 6 % slower than
+// with the other kernel, 350 would be that much faster.
 constexpr int kBlockMinBatch = 33;
-constexpr int64_t kBlockMinWork = 4000000, kBlockMinWorkIdle = 10000000, kBlockMinWorkLong = 20000000;
-bool block_serves(const conv_plan *plan, int batch, int lpr_log2) {
+constexpr int64_t kBlockNever = INT64_MAX;
+constexpr double kBlockMarchEven = 1.02;      // (of the 6900: 28 slower by more than 6 %, 143 missed)
+int64_t block_least_work(const ConvShape &sh, bool tr, int taps) {
+    if (taps < 9) return 0;
+    if (tr) {
+        if (taps == 9) return sh.s <= 2 ? 0 : sh.s == 3 ? 8000000 : 10000000;
+        if (taps == 16) return sh.s <= 2 ? 6000000 : sh.s == 3 ? kBlockNever : 15000000;
+        return kBlockNever;
+    }
+    if (taps == 9) return sh.s <= 2 ? 1500000 : 0;
+    if (taps == 16) return sh.s == 1 ? 8000000 : 1500000;
+    return sh.s == 1 ? kBlockNever : sh.s == 2 ? 20000000 : 1500000;
+}
+// 25 taps, stride 1: nanoseconds of the staged march (a workgroup per compute unit, 32 of those on an XCD, whose cells are
+// divided evenly among the XCDs) and of the block kernel.
+double block_march_ns(const ApplyChoice &c, int batch) {
+    const int64_t cells = (int64_t)c.march.strips * c.march.segs, rounds = ((cells + kXcds - 1) / kXcds * column_blocks(batch, c.nv) + 31) / 32;
+    return rounds * (c.nv == 4 ? 4400.0 + 416.0 * c.march.seg : 3800.0 + 318.0 * c.march.seg);
+}
+double block_ns(int64_t rows, int batch, int lpr_log2) {
+    constexpr double start[3] = {6200.0, 5500.0, 4700.0}, row[3] = {3.41e-3, 2.67e-3, 2.54e-3};    // 64, 128, 256 columns
+    const int64_t columns = 4LL << lpr_log2, padded = (batch + columns - 1) / columns * columns;
+    return start[lpr_log2 - kBlockLprLeast] + row[lpr_log2 - kBlockLprLeast] * (double)rows * (double)padded;
+}
+bool block_serves(const conv_plan *plan, int batch, int lpr_log2, const ApplyChoice &other) {
     const ConvShape &sh = plan->shape;
     if (batch < kBlockMinBatch) return false;
-    const int64_t columns = 4LL << lpr_log2, padded = (batch + columns - 1) / columns * columns;
-    if (plan->transposed && sh.k == sh.s + 1 && sh.s > 1 && 8LL * batch <= 7 * padded) return false;
-    if (5LL * batch < 4 * padded && plan->nnz * batch < kBlockMinWorkIdle) return false;
-    if (sh.k == 5 && sh.s == 1 && batch % 4 == 0 && 8LL * batch < 5 * padded) return false;
-    const bool longest = (plan->transposed && sh.s >= 3 && plan->max_row_nnz >= 16) || (sh.k == 5 && sh.s == 1);
-    if (longest && batch % 16 == 0 && plan->nnz * batch < kBlockMinWorkLong) return false;
-    const bool long_start = plan->max_row_nnz >= 16 || (plan->transposed && sh.s >= 3);
-    return !long_start || plan->nnz * batch >= kBlockMinWork;
+    if (other.kind == Kind::StageMarch && sh.k == 5 && sh.s == 1) return block_ns(plan->rows, batch, lpr_log2) <= kBlockMarchEven * block_march_ns(other, batch);
+    if (other.kind == Kind::March || other.kind == Kind::StageMarch) return true;
+    return plan->nnz * batch >= block_least_work(sh, plan->transposed, plan->max_row_nnz);
 }
 
-ApplyChoice choose_apply(const conv_plan *full, int batch) {
+// The kernel for a product, blocks left aside.
+ApplyChoice choose_unblocked(const conv_plan *full, int batch) {
     // geometry of one channel; a multi-channel plan applies it once per channel (LDS kernels)
     // or walks the channels inside the row-group kernels
     conv_plan one = *full;
@@ -779,17 +800,6 @@ ApplyChoice choose_apply(const conv_plan *full, int batch) {
     while (c.g < 16 && 6 * c.g <= row_max && row_blocks() * column_blocks(batch, c.nv) < kRowGroupWiden) c.g *= 2;
     while (c.nv > 1 && row_blocks() * column_blocks(batch, c.nv) < row_group_min_blocks(full->channels > 1 ? 1 : row_max, plan->shape.s)) c.nv /= 2;
     if (plan->nnz == 0 || column_blocks(batch, nv_hi) > 65535) return c;
-
-    // batches that fill a wave (not where the plan's marching threshold, a test hook, is lowered)
-    if (full->channels == 1 && full->march_min_jobs >= kMarchMinJobs && block_compiled(plan->shape.k, plan->shape.s, plan->transposed) &&
-        block_geometry(plan, batch, &c.lpr_log2, &c.block) && block_serves(plan, batch, c.lpr_log2)) {
-        c.kind = Kind::Block;
-        c.threads = kBlockThreads;
-        c.g = 1;
-        c.nv = 1;
-        c.tw = block_ry(plan->shape.k, plan->shape.s, plan->transposed);
-        return c;
-    }
 
     // marching kernels: float4 column chunks, or scalar columns
     MarchShape ms;
@@ -890,6 +900,23 @@ ApplyChoice choose_apply(const conv_plan *full, int batch) {
         c.geom = g;
         break;
     }
+    return c;
+}
+
+ApplyChoice choose_apply(const conv_plan *plan, int batch) {
+    const ApplyChoice other = choose_unblocked(plan, batch);
+    // batches that fill a wave (not where the plan's marching threshold, a test hook, is lowered)
+    const ConvShape &sh = plan->shape;
+    ApplyChoice c{};
+    if (plan->channels > 1 || plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || !block_compiled(sh.k, sh.s, plan->transposed) ||
+        column_blocks(batch, 4) > 65535 || !block_geometry(plan, batch, &c.lpr_log2, &c.block) ||
+        !block_serves(plan, batch, c.lpr_log2, other))
+        return other;
+    c.kind = Kind::Block;
+    c.threads = kBlockThreads;
+    c.g = 1;
+    c.nv = 1;
+    c.tw = block_ry(sh.k, sh.s, plan->transposed);
     return c;
 }
 

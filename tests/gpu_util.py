@@ -14,6 +14,21 @@ def device():
     return torch.device("cuda:0")
 
 
+def median_us(run, repeats=9):
+    """Median time of run() on the device, one call at a time, after three calls."""
+    for _ in range(3):
+        run()
+    times = []
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(1e3 * a.elapsed_time(b))
+    return sorted(times)[repeats // 2]
+
+
 # Test hook: when set, every plan built through this module gets this threshold for the
 # persistent marching kernels (the default, 256 strip segments, keeps them off small shapes).
 MARCH_MIN_JOBS = None

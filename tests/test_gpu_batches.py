@@ -27,7 +27,7 @@ def _check(got, ref, scale, what):
 
 
 KINDS = [   # shape, test threshold for the marching kernels (None: the default), what takes it
-    ((64, 90, 3, 1, 1), None, "lds_tile_"), ((120, 101, 5, 2, 2), None, "lds_tile_"), ((20, 33, 4, 1, 2), None, "gather_"),
+    ((64, 90, 3, 1, 1), None, "block_"), ((260, 200, 3, 1, 1), None, "lds_tile_"), ((120, 101, 5, 2, 2), None, "lds_tile_"), ((20, 33, 4, 1, 2), None, "gather_"),
     ((70, 75, 5, 1, 2), 1, "lds_march_staged_"), ((40, 75, 9, 1, 4), 1, "lds_march_staged_"),
     ((40, 75, 11, 1, 5), 1, "lds_march_staged_"), ((70, 131, 5, 2, 2), 1, "lds_march_"), ((70, 67, 10, 2, 3), 1, "lds_march_"),
 ]
@@ -334,7 +334,10 @@ def test_pushed_lines_at_the_edges(k, s):
     ("compact", (205, 192, 1, 4, 0), 71, 10, "compact_gather_"), ("compact", (450, 559, 5, 4, 2), 36, 1, "compact_gather_"),
     ("csr", (393, 379, 11, 1, 0), 40, 1, "lds_march_28x32"), ("csr", (477, 694, 8, 1, 0), 3, 1, "lds_march_"),
     ("csr", (413, 252, 2, 1, 0), 32, 1, "lds_tile_7x64"), ("csr", (247, 335, 4, 1, 2), 3, 4, "gather_"),
-    ("csc", (340, 367, 3, 2, 1), 160, 1, "lds_tile_"), ("csc", (340, 367, 3, 2, 1), 40, 1, "gather_"),
+    ("csc", (340, 367, 3, 2, 1), 160, 1, "block_"), ("csc", (340, 367, 3, 2, 1), 40, 1, "block_"),
+    ("csc", (340, 367, 3, 2, 1), 32, 1, "lds_tile_"), ("csc", (340, 367, 3, 2, 1), 18, 1, "gather_"),
+    ("csr", (475, 679, 5, 1, 2), 40, 1, "lds_march_staged_"), ("csr", (128, 128, 5, 1, 2), 128, 1, "block_"),
+    ("csc", (93, 124, 5, 1, 0), 160, 1, "lds_tile_"), ("csc", (37, 48, 12, 3, 6), 178, 1, "gather_"),
 ])
 def test_products_on_both_sides_of_the_dispatch_rules(kind, shape, batch, channels, want):
     """Lanes, kernels and tiles that the default dispatch gives shapes of ordinary size."""

@@ -47,9 +47,9 @@ def test_blocks_at_edges_and_paddings(storage, k, s):
     assert served >= 4
 
 
-@pytest.mark.parametrize("storage,shape,batch", [("csr", (60, 71, 3, 1, 1), 64), ("csr", (110, 83, 5, 2, 2), 112),
+@pytest.mark.parametrize("storage,shape,batch", [("csr", (60, 71, 3, 1, 1), 64), ("csr", (200, 183, 5, 2, 2), 112),
                                                  ("csc", (60, 71, 3, 1, 1), 126), ("csc", (90, 83, 5, 2, 2), 60),
-                                                 ("csc", (130, 111, 7, 3, 3), 64), ("csc", (100, 93, 9, 2, 4), 64),
+                                                 ("csc", (190, 163, 7, 3, 3), 64), ("csc", (200, 190, 9, 2, 4), 64),
                                                  ("csr", (160, 163, 5, 3, 2), 64)])
 def test_blocks_read_the_stored_arrays(storage, shape, batch):
     """Columns redirected after the build, entries moved between neighbouring rows, infinite values: the product follows the

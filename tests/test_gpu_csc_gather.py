@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2411_19419_amd as cs
 
-from gpu_util import build_plan_t, device
+from gpu_util import build_plan_t, device, median_us
 from test_csc_gather_rule import gather_info
 
 pytestmark = pytest.mark.gpu
@@ -134,21 +134,6 @@ def test_an_infinite_pixel_reaches_only_its_windows(shape, batch):
     got = y.cpu().numpy()
     assert np.array_equal(np.isfinite(got), np.isfinite(ref)) and np.array_equal(np.isnan(got), np.isnan(ref))
     plan.close()
-
-
-def median_us(run, repeats=9):
-    """Median time of run() on the device, one call at a time, after three calls."""
-    for _ in range(3):
-        run()
-    times = []
-    for _ in range(repeats):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record()
-        run()
-        b.record()
-        torch.cuda.synchronize()
-        times.append(1e3 * a.elapsed_time(b))
-    return sorted(times)[repeats // 2]
 
 
 @pytest.mark.parametrize("edit", ["one", "every column"])

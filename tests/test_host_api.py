@@ -430,7 +430,8 @@ def test_device_queries_without_the_internal_calls():
     # several channels column by column: one launch of the row groups
     ((205, 192, 1, 4, 0), 71, 2, 10, 10, None), ((570, 480, 2, 1, 0), 1, 2, 4, 10, 1),
     # T^T: the tile kernel with full lanes, or rows of 9 entries at small batches
-    ((340, 367, 3, 2, 1), 168, 1, 1, 1, 16), ((340, 367, 3, 2, 1), 160, 1, 1, 2, 16), ((881, 1143, 5, 4, 2), 40, 1, 1, 1, 16),
+    # (blocks: 340 x 367, batch 168 70 us in row groups and 30, batch 160 32 with tiles and 15; 1122 x 1211, k 5, s 4, batch 40 146 and 73)
+    ((340, 367, 3, 2, 1), 168, 1, 1, 2, None), ((340, 367, 3, 2, 1), 160, 1, 1, 2, None), ((881, 1143, 5, 4, 2), 40, 1, 1, 2, None),
     ((256, 256, 5, 2, 2), 64, 1, 1, 2, 16), ((267, 383, 3, 1, 1), 4, 1, 1, 1, 4), ((500, 450, 3, 1, 1), 8, 1, 1, 2, 8),
     # batches of 2 and 3 column by column
     ((812, 521, 8, 1, 7), 3, 0, 1, 3, 1), ((196, 273, 11, 3, 5), 3, 1, 1, 0, 1), ((247, 335, 4, 1, 2), 3, 0, 4, 0, 1),

@@ -1496,19 +1496,25 @@ static int enqueue_csc_scatter(const conv_plan *plan, const float *x_dev, float 
 // Launch shape of the product from the column-compressed arrays that gathers (csc_gather_kernel.h).
 //
 // What it costs over the scatter is time per input line: a workgroup walks seg s + k - s of them, a microsecond each, however
-// little there is to do, and every line at the image's border is placed anew.  Planes with little work for that stay
-// with the scatter.  The line was drawn over 600 products (planes of 16 to 4096 a side, k 1 to 13, strides 1 to 4, batches 1 to 256):
-// entries x batch^(3/4) against the fourth power of the lines in flight, four times as much at strides above 1, whose
-// kernel does not know its strip.  Above it the gather takes 0.1 to 0.9 of the scatter's time (1024^2, k 7, batch 16: 103 us and
-// 357, batch 1: 78 and 157; 1000 x 900, k 3, batch 16: 36 and 215; 4096^2, k 11, s 4, batch 4: 300 and 1480; 269 x 320, k 5,
-// batch 1: 17 and 24), below it the scatter does (137 x 210, k 11, batch 1: 39 and 21; 32 x 40, k 7, batch 16: 25 and 9.5).  With
-// one or two entries per pixel and batches below 4 adding every entry to y directly is hard to beat (3384 x 3491, k 1, batch 1:
-// 47 and 210; 1226 x 786, k 2, batch 1: 20 and 26).
+// little there is to do, and every line at the image's border is placed anew; planes too small to pay for that stay with
+// the scatter.  What the scatter costs goes with pixels x batch, below four columns with pixels x sqrt(batch).  The lines lie
+// where 11 000 products (planes of 16 to 3000 a side, k 1 to 13, strides 1 to 4, batches 1 to 256) had the two even, for every number
+// of output lines that an input line reaches: ceil(k/s), 1 to 13.  Of these products 110 are more than 6 % slower than the
+// scatter, 280 would be that much faster (1024^2, k 7, batch 16: 101 us and 358, batch 1: 80 and 158; 1000 x 900, k 3, batch 16: 39 and 217;
+// 4096^2, k 11, s 4, batch 4: 306 and 1490; 269 x 320, k 5, batch 1: 18 and 23; below the lines 691 x 628, k 13, s 2, batch 3: 122 and 76;
+// 176 x 128, k 7, batch 8: 25 and 17; 1292 x 1151, k 1, batch 4: 37 and 26).
+// Columns of one entry below batch 4, and of up to four at stride 1, are added to y directly; at strides above 1 these
+// gather from half a million products on, k 3 from 1.3 million (427 x 533, k 3, s 2, batch 1: 9.9 directly, 18).
 // Two workgroups per compute unit; with few lines in flight (and few registers) four, as long as the lines that two
 // segments share stay few (3453 x 2976, k 3, batch 1: 238 -> 191 us, 3000^2, k 3, s 2, batch 4: 149 -> 114; 1000 x 900, k 3,
 // batch 16, 15 lines a segment: 36 -> 37; k 5: 163 -> 171).
 constexpr int64_t kCscGatherTarget = 512, kCscGatherLong = 32;
-constexpr double kCscGatherWork = 2000.0, kCscGatherWorkStrided = 15000.0, kCscGatherWorkOne = 1e6, kCscGatherWorkDirect = 2e6;
+constexpr float kCscGatherLeast[2][14] = {      // thousand pixels x batch, stride 1 and strides above
+    {0, 2400, 70, 70, 110, 250, 380, 450, 430, 500, 330, 400, 400, 500}, {0, 1400, 160, 260, 390, 980, 1260, 1500, 2000, 2500, 3000, 3700, 4400, 5200}};
+constexpr float kCscGatherLeastFew[2][14] = {   // batches below 4: thousand pixels x sqrt(batch)
+    {0, 0, 0, 30, 41, 55, 81, 180, 700, 185, 330, 270, 175, 400}, {0, 0, 0, 95, 203, 303, 720, 870, 1100, 1400, 1800, 2200, 2600, 3000}};
+constexpr float kCscGatherLeastOne = 10000, kCscGatherLeastOneStrided = 4300;        // one entry a column, batch 4
+constexpr double kCscGatherDirect = 5e5, kCscGatherDirectThree = 1.3e6;
 
 static CscGatherChoice choose_csc_gather(const conv_plan *plan, int batch) {
     const ConvShape &sh = plan->shape;
@@ -1519,13 +1525,17 @@ static CscGatherChoice choose_csc_gather(const conv_plan *plan, int batch) {
     // int arithmetic in the kernel
     if ((int64_t)sh.m + 2LL * sh.p + k >= (1LL << 30) || (int64_t)sh.n + 2LL * sh.p + 64 * s + k >= (1LL << 30) || 1024LL * batch > kInt32Limit)
         return c;
-    // (conv_plan_set_march_min_jobs lowers the bar for tests)
-    const double bar = std::min(1.0, plan->march_min_jobs / (double)kMarchMinJobs);
-    const double work = (double)plan->nnz * batch;
-    if (kl == 1 ? batch < 4 || work < kCscGatherWorkOne * bar
-                : work / std::sqrt(std::sqrt((double)batch)) < (s == 1 ? kCscGatherWork : kCscGatherWorkStrided) * (double)(kl * kl * kl * kl) * bar)
+    // (conv_plan_set_march_min_jobs lowers the bar for tests, or raises it)
+    const double bar = plan->march_min_jobs / (double)kMarchMinJobs, pixels_in = (double)sh.m * sh.n;
+    if (batch >= 4) {
+        const float least = kl == 1 && batch == 4 ? (s == 1 ? kCscGatherLeastOne : kCscGatherLeastOneStrided) : kCscGatherLeast[s > 1][kl];
+        if (pixels_in * batch < 1000.0 * least * bar) return c;
+    } else if (kl == 1 || (kl == 2 && s == 1)) {
         return c;
-    if (kl == 2 && batch < 4 && k < 4 && (s == 1 || work < kCscGatherWorkDirect * bar)) return c;
+    } else if (kl == 2 ? (double)plan->nnz * batch < (k < 4 ? kCscGatherDirectThree : kCscGatherDirect) * bar
+                       : pixels_in * std::sqrt((double)batch) < 1000.0 * kCscGatherLeastFew[s > 1][kl] * bar) {
+        return c;
+    }
     c.kl = (int)kl;
     c.scalar = batch < 4;
     g.sh = sh;

@@ -46,7 +46,10 @@ def test_geometry_over_many_shapes():
 
 @pytest.mark.parametrize("shape,batch,gathers", [
     ((1024, 1024, 7, 1, 3), 16, True), ((1024, 1024, 7, 1, 3), 1, True), ((4096, 4096, 11, 4, 5), 4, True),
-    ((32, 40, 7, 1, 3), 16, False), ((137, 210, 11, 1, 5), 1, False),          # little work for a line's fixed cost
+    # little work for a line's fixed cost
+    ((32, 40, 7, 1, 3), 16, False), ((137, 210, 11, 1, 5), 1, False), ((691, 628, 13, 2, 0), 3, False), ((176, 128, 7, 1, 3), 8, False),
+    ((92, 79, 7, 1, 3), 48, False), ((564, 447, 8, 1, 4), 3, False), ((241, 336, 7, 1, 0), 2, False), ((183, 123, 8, 1, 0), 16, False),
+    ((1292, 1151, 1, 1, 0), 4, False), ((1292, 1151, 1, 1, 0), 5, True), ((427, 533, 3, 2, 1), 1, False), ((427, 533, 4, 2, 1), 1, True),
     ((3384, 3491, 1, 1, 0), 1, False), ((1226, 786, 2, 1, 0), 1, False),       # an entry or four per pixel, one vector
     ((1000, 1000, 3, 4, 1), 16, False), ((1000, 1000, 5, 1, 5), 16, False),    # pixels, rows without entries
     ((1000, 1000, 14, 1, 7), 16, False), ((5, 1, 5, 1, 4), 4, False),

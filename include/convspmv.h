@@ -240,8 +240,7 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch);
  * not; channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
  * CONV_ENULL).  For tests of the host logic and for reports. */
 typedef struct conv_dispatch {
-    int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, or, with lds_bytes 0, blocks of
-                               strip x segment outputs per group of lanes, 3 LDS march,
+    int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, 3 LDS march,
                                4 described rows (structure-aware): marching, or, with ring_lines 0
                                and strip x lanes_per_row = 64, input lines pushed into output lines,
                                5 rectangle path (structure-aware),
@@ -250,17 +249,18 @@ typedef struct conv_dispatch {
                                (storage 3; for 7: strip x segment = pixels x lines of a tile, ring_lines_needed
                                x lines_per_step = runs x rows of its window, lanes_per_row = columns per step),
                                9 LDS march with the entry stream staged through LDS,
-                               10 row groups over the structure-aware storage (small products) */
+                               10 row groups over the structure-aware storage (small products),
+                               12 blocks of strip x segment outputs per group of lanes, the batch on the lanes */
     int threads;            /* per workgroup */
-    int64_t lds_bytes;      /* dynamic LDS per workgroup */
+    int64_t lds_bytes;      /* LDS per workgroup */
     int64_t workgroups;     /* that do work, over the whole launch (per channel for kernel 3) */
-    int strip;              /* output columns per strip / tile line (kernels 2-6, 9), else 0 */
-    int segment;            /* output lines per workgroup (kernels 2-6, 9), else 0 */
+    int strip;              /* output columns per strip / tile line (kernels 2-6, 9), of a block (12), else 0 */
+    int segment;            /* output lines per workgroup (kernels 2-6, 9), of a block (12), else 0 */
     int ring_lines;         /* LDS ring lines (kernels 3-5, 9; 0 = no ring) */
     int ring_lines_needed;  /* lines a step keeps resident (<= ring_lines when there is a ring) */
     int lines_per_step;     /* output lines per step (kernels 3-5, 9) */
-    int lanes_per_row;      /* lanes that share a row of the matrix */
-    int columns_per_lane;   /* batch columns per lane; in blocks: sums per lane, 4 columns of every output */
+    int lanes_per_row;      /* lanes that share a row of the matrix; 12: each has other batch columns of it */
+    int columns_per_lane;   /* batch columns per lane */
 } conv_dispatch;
 int conv_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels,
                        conv_dispatch *out);

@@ -1837,8 +1837,8 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
         d.workgroups = (int64_t)cc.geom.strips * cc.geom.segs * cc.col_blocks;
     } else {
         const ApplyChoice c = choose_apply(&plan, batch);
-        d.kernel = c.kind == Kind::GatherScalar ? 0 : c.kind == Kind::GatherVec ? 1 : c.kind == Kind::Tile || c.kind == Kind::Block ? 2
-                   : c.kind == Kind::March ? 3 : 9;
+        d.kernel = c.kind == Kind::GatherScalar ? 0 : c.kind == Kind::GatherVec ? 1 : c.kind == Kind::Tile ? 2
+                   : c.kind == Kind::March ? 3 : c.kind == Kind::Block ? 12 : 9;
         d.threads = c.threads;
         d.lds_bytes = (int64_t)c.lds;
         d.lanes_per_row = c.g;
@@ -1860,7 +1860,10 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
             d.ring_lines_needed = tr ? (c.ls == 2 ? (k + 2) / s + 2 : k / s + 2) : s * (2 * c.ls - 1) + k;
             d.workgroups = (int64_t)c.march.strips * c.march.segs * column_blocks(batch, c.nv);
         } else if (c.kind == Kind::Block) {
-            d.columns_per_lane = 4 * block_rx(k, s, plan.transposed) * c.tw;
+            d.columns_per_lane = 4;
+            d.lanes_per_row = 1 << c.lpr_log2;
+            d.lds_bytes = (int64_t)sizeof(float) * (kBlockThreads / kWave) * (kWave >> c.lpr_log2) *
+                          block_group_words(block_rx(k, s, plan.transposed) * c.tw, plan.max_row_nnz);
             d.strip = c.tw;
             d.segment = block_rx(k, s, plan.transposed);
             d.workgroups = (int64_t)c.block.cells * ((batch + (4LL << c.lpr_log2) - 1) / (4LL << c.lpr_log2));

@@ -30,9 +30,12 @@ import paper_2411_19419_amd as cs
 ])
 def test_block_rule(shape, batch, storage, blocks):
     d = cs.conv_dispatch_info(*shape, batch, storage)
-    assert (d.kernel == 2 and d.lds_bytes == 0) == blocks, (shape, batch, d.kernel, d.lds_bytes)
+    assert (d.kernel == 12) == blocks, (shape, batch, d.kernel)
     if blocks:
-        sums = d.workgroups * d.threads * d.columns_per_lane
         m, n, k, s, p = shape
         mo, no = cs.conv_out_shape(*shape)
-        assert d.columns_per_lane == 4 * d.strip * d.segment and sums >= (m * n if storage else mo * no) * batch
+        assert d.columns_per_lane == 4 and d.lanes_per_row in (16, 32, 64)
+        sums = d.workgroups * d.threads * d.strip * d.segment * d.columns_per_lane
+        assert sums >= (m * n if storage else mo * no) * batch
+        taps = (-k // s) ** 2 if storage else k * k          # the weights of every group's outputs, a float each
+        assert 4 * d.threads // d.lanes_per_row * d.strip * d.segment * taps <= d.lds_bytes <= 16384

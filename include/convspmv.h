@@ -236,8 +236,8 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch);
  * (host only; 16-byte-aligned operands assumed): the kernel family and the
  * launch geometry the dispatch derives.  storage: 0 = CSR of T, 1 = CSC of T
  * (the plan applies T^T), 2 = structure-aware storage, 3 = CSC of T applied
- * by conv_spmv_from_csc: the scatter, which takes what the gather described there does
- * not; channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
+ * by conv_spmv_from_csc (kernels 7, 8 and 11; of the launches that 11 makes, the first);
+ * channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
  * CONV_ENULL).  For tests of the host logic and for reports. */
 typedef struct conv_dispatch {
     int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, 3 LDS march,
@@ -250,16 +250,19 @@ typedef struct conv_dispatch {
                                x lines_per_step = runs x rows of its window, lanes_per_row = columns per step),
                                9 LDS march with the entry stream staged through LDS,
                                10 row groups over the structure-aware storage (small products),
+                               11 gather from the column-compressed arrays (storage 3: ring_lines_needed = output
+                               lines in flight, ring_lines = 16-byte accesses per array that a line takes at most,
+                               lines_per_step = shares of a tap sum),
                                12 blocks of strip x segment outputs per group of lanes, the batch on the lanes */
     int threads;            /* per workgroup */
     int64_t lds_bytes;      /* LDS per workgroup */
     int64_t workgroups;     /* that do work, over the whole launch (per channel for kernel 3) */
-    int strip;              /* output columns per strip / tile line (kernels 2-6, 9), of a block (12), else 0 */
-    int segment;            /* output lines per workgroup (kernels 2-6, 9), of a block (12), else 0 */
+    int strip;              /* output columns per strip / tile line (kernels 2-6, 9, 11), of a block (12), else 0 */
+    int segment;            /* output lines per workgroup (kernels 2-6, 9, 11), of a block (12), else 0 */
     int ring_lines;         /* LDS ring lines (kernels 3-5, 9; 0 = no ring) */
     int ring_lines_needed;  /* lines a step keeps resident (<= ring_lines when there is a ring) */
     int lines_per_step;     /* output lines per step (kernels 3-5, 9) */
-    int lanes_per_row;      /* lanes that share a row of the matrix; 12: each has other batch columns of it */
+    int lanes_per_row;      /* lanes that share a row of the matrix; 11, 12: each has other batch columns of it */
     int columns_per_lane;   /* batch columns per lane */
 } conv_dispatch;
 int conv_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels,
@@ -307,12 +310,10 @@ int conv_multi_destroy(conv_multi *multi);   /* NULL is accepted */
  * thread-safe against a concurrent conv_spmv on the same plan.  The result of
  * conv_spmv does not depend on it beyond the summation order.
  * conv_test_dispatch_info is conv_dispatch_info with that threshold given.
- * conv_spmv_from_csc lowers the work from which it gathers in proportion (256:
- * as it is); conv_test_csc_gather_info says whether it gathers, and how: kernel
- * 11 (0: it scatters), strip, segment, threads, LDS, workgroups, lanes per
- * output column and batch columns per lane, lines_per_step = shares of a tap
- * sum, ring_lines_needed = output lines in flight, ring_lines = 16-byte accesses
- * per array that a line takes at most.  Status as for conv_dispatch_info. */
+ * conv_spmv_from_csc moves the work from which it gathers in proportion (256:
+ * as it is; 2^31 - 1: it always scatters); conv_test_csc_gather_info says
+ * whether it gathers, and how (kernel 11 as in conv_dispatch, or 0: it scatters).
+ * Status as for conv_dispatch_info. */
 int conv_plan_set_march_min_jobs(conv_plan *plan, int jobs);
 int conv_test_csc_gather_info(int m, int n, int k, int s, int p, int batch, int march_min_jobs, conv_dispatch *out);
 int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels,

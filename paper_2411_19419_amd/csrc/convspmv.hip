@@ -1736,6 +1736,20 @@ int conv_plan_is_transposed(const conv_plan *plan) { return plan ? (plan->transp
 int conv_plan_is_compact(const conv_plan *plan) { return plan ? (plan->compact ? 1 : 0) : CONV_ENULL; }
 int conv_plan_channels(const conv_plan *plan) { return plan ? plan->channels : CONV_ENULL; }
 
+static void describe(const CscGatherChoice &c, conv_dispatch &d) {
+    d.kernel = 11;
+    d.threads = kCscGatherThreads;
+    d.lds_bytes = (int64_t)c.lds;
+    d.workgroups = c.geom.blocks;
+    d.strip = c.geom.tw;
+    d.segment = c.geom.seg;
+    d.ring_lines = c.geom.quads;
+    d.ring_lines_needed = c.kl;
+    d.lines_per_step = c.geom.ways;
+    d.lanes_per_row = 1 << c.geom.lpr_log2;
+    d.columns_per_lane = c.scalar ? 1 : 4;
+}
+
 int conv_dispatch_info(int m, int n, int k, int s, int p, int batch, int storage, int channels, conv_dispatch *out) {
     return conv_test_dispatch_info(m, n, k, s, p, batch, storage, channels, kMarchMinJobs, out);
 }
@@ -1769,9 +1783,13 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
     conv_dispatch d{};
     const ChannelsChoice fused = choose_compact_channels(&plan, nullptr, nullptr, batch);
     if (storage == 3) {
-        // conv_spmv_from_csc: the scatter with the sums kept on chip, or every entry added to y directly
+        // conv_spmv_from_csc: every output summed where it stays, the scatter with the sums kept on chip, or every entry
+        // added to y directly
+        const CscGatherChoice gather = plan.nnz > 0 ? choose_csc_gather(&plan, batch) : CscGatherChoice{};
         const CscTileChoice tc = plan.nnz > 0 ? choose_csc_tile(&plan, batch) : CscTileChoice{};
-        if (tc.ok) {
+        if (gather.ok) {
+            describe(gather, d);
+        } else if (tc.ok) {
             d.kernel = 7;
             d.threads = tc.waves * kWave;
             d.lds_bytes = (int64_t)tc.lds;
@@ -1894,19 +1912,7 @@ int conv_test_csc_gather_info(int m, int n, int k, int s, int p, int batch, int 
     plan.march_min_jobs = march_min_jobs;
     conv_dispatch d{};
     const CscGatherChoice c = nnz > 0 ? choose_csc_gather(&plan, batch) : CscGatherChoice{};
-    if (c.ok) {
-        d.kernel = 11;
-        d.threads = kCscGatherThreads;
-        d.lds_bytes = (int64_t)c.lds;
-        d.workgroups = c.geom.blocks;
-        d.strip = c.geom.tw;
-        d.segment = c.geom.seg;
-        d.ring_lines = c.geom.quads;
-        d.ring_lines_needed = c.kl;
-        d.lines_per_step = c.geom.ways;
-        d.lanes_per_row = 1 << c.geom.lpr_log2;
-        d.columns_per_lane = c.scalar ? 1 : 4;
-    }
+    if (c.ok) describe(c, d);
     *out = d;
     return CONV_OK;
 }

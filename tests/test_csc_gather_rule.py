@@ -55,7 +55,12 @@ def test_geometry_over_many_shapes():
     ((1000, 1000, 14, 1, 7), 16, False), ((5, 1, 5, 1, 4), 4, False),
 ])
 def test_which_shapes_gather(shape, batch, gathers):
-    assert gather_info(*shape, batch)["kernel"] == (11 if gathers else 0)
+    info = gather_info(*shape, batch)
+    assert info["kernel"] == (11 if gathers else 0)
+    # the public report is that of the kernel that runs
+    d = binding.conv_dispatch_info(*shape, batch, 3)
+    assert (d.kernel == 11) == gathers and (gathers or d.kernel in (7, 8))
+    assert not gathers or info == {name: getattr(d, name) for name, _ in d._fields_}
 
 
 def test_argument_checks():

@@ -180,8 +180,8 @@ def test_header_is_plain_c(tmp_path):
     assert out[:3] == ["1024", "1024", "51208336"] and out[3].strip() == "x and y overlap"
 
 
-def _dispatch(m, n, k, s, p, batch, storage=0, channels=1):
-    d = cs.conv_dispatch_info(m, n, k, s, p, batch, storage, channels)
+def _dispatch(m, n, k, s, p, batch, storage=0, channels=1, march_min_jobs=None):
+    d = cs.conv_dispatch_info(m, n, k, s, p, batch, storage, channels, march_min_jobs)
     return {f[0]: getattr(d, f[0]) for f in d._fields_}
 
 
@@ -334,7 +334,8 @@ def test_dispatch_of_channel_sums_from_the_structure_aware_storage():
 
 
 def test_dispatch_of_the_product_from_csc_over_many_shapes():
-    """Host logic of conv_spmv_from_csc (storage 3): the on-chip scatter's tile, window and lane
+    """Host logic of conv_spmv_from_csc (storage 3) where it scatters (the test hook keeps it from
+    gathering): the on-chip scatter's tile, window and lane
     layout stay within what its kernel assumes -- a tile line's entries within the 1024-entry
     stage, the lanes of a wave enough for a line's column pointers, the window within 64 KiB of
     LDS and 2^21 rows from its first one, batch columns per wave dividing 4 -- and the direct
@@ -353,7 +354,7 @@ def test_dispatch_of_the_product_from_csc_over_many_shapes():
         per_axis = -(-k // s)
         mo, no = oracle.out_shape(m, n, k, s, p)
         for batch in (1, 2, 3, 4, 5, 8, 9, 16, 48):
-            d = _dispatch(m, n, k, s, p, batch, 3)
+            d = _dispatch(m, n, k, s, p, batch, 3, march_min_jobs=2 ** 31 - 1)
             seen.add(d["kernel"])
             if per_axis ** 2 > 1024 or per_axis ** 2 < (4 if batch >= 4 else 9):
                 assert d["kernel"] == 8, (m, n, k, s, p, batch)

@@ -50,8 +50,9 @@ __host__ __device__ constexpr int block_row_taps(int d, int k, int s, bool tr) {
 // result line (pixel) at which the first block starts
 __host__ __device__ constexpr int block_first(int s, int p, bool tr) { return tr ? -(p % s) : 0; }
 
-// Outputs of a block, and which (k, s) are compiled.  T: windows of at most 48 pixels (four registers each).  T^T: one or two
-// steps of the stride, so that an operand pixel serves as many results as it has, and windows of at most 40 pixels.
+// Outputs of a block, and which (k, s) are compiled.  T, and T^T at stride 1: windows of at most 40 pixels (four
+// registers each).  T^T above: one step of the stride, so that an operand pixel serves as many results as it has, and its taps are the
+// window (at most 25 pixels).
 __host__ __device__ constexpr bool block_compiled(int k, int s, bool tr) {
     if (!tr || s == 1) return (s <= 2 && k >= 2 && k <= 5) || (!tr && s <= 4 && k >= 3 && k <= 5);
     return s <= 4 && k > s && k <= (s == 2 ? 5 : 4) * s && k <= 13;

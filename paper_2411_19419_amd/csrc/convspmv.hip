@@ -741,8 +741,8 @@ bool block_geometry(const conv_plan *plan, int batch, int *lpr_log2, BlockGeom *
 //   T:    16 taps, s 1: 8 (below 1.02 to 1.1); 25 taps, s 2: 20 (below 0.95 to 1.2); 25 taps, s 1: tiles stay (1.0 to 1.3)
 //   T^T:  9 taps, s 3: 8, s 4: 10 (below up to 1.3); 16 taps, s 1 and 2: 6, s 4: 15, s 3: tiles stay (1.1); 25 taps: tiles stay
 // (340 x 367, k 3, s 2, T^T, batch 160: 34 us with tiles, 15 in blocks; batch 168: 70 in row groups, 30; 93 x 124, k 5, T^T, batch 160: 10.4 with
-// tiles, 15.4 in blocks; 37 x 48, k 12, s 3, T^T, batch 178: 5.3 in row groups, 8.4 in blocks.)  Of the 26 000, 70 are more than 6 % slower than
-// with the other kernel, 350 would be that much faster.
+// tiles, 15.4 in blocks; 37 x 48, k 12, s 3, T^T, batch 178: 5.3 in row groups, 8.4 in blocks.)  Of the 26 000, 53 are more than 6 % slower than
+// with the other kernel, 323 would be that much faster.
 constexpr int kBlockMinBatch = 33;
 constexpr int64_t kBlockNever = INT64_MAX;
 constexpr double kBlockMarchEven = 1.02;      // (of the 6900: 28 slower by more than 6 %, 143 missed)
@@ -1499,8 +1499,8 @@ static int enqueue_csc_scatter(const conv_plan *plan, const float *x_dev, float 
 // little there is to do, and every line at the image's border is placed anew; planes too small to pay for that stay with
 // the scatter.  What the scatter costs goes with pixels x batch, below four columns with pixels x sqrt(batch).  The lines lie
 // where 11 000 products (planes of 16 to 3000 a side, k 1 to 13, strides 1 to 4, batches 1 to 256) had the two even, for every number
-// of output lines that an input line reaches: ceil(k/s), 1 to 13.  Of these products 110 are more than 6 % slower than the
-// scatter, 280 would be that much faster (1024^2, k 7, batch 16: 101 us and 358, batch 1: 80 and 158; 1000 x 900, k 3, batch 16: 39 and 217;
+// of output lines that an input line reaches: ceil(k/s), 1 to 13.  Of these products 112 are more than 6 % slower than the
+// scatter, 281 would be that much faster (1024^2, k 7, batch 16: 101 us and 358, batch 1: 80 and 158; 1000 x 900, k 3, batch 16: 39 and 217;
 // 4096^2, k 11, s 4, batch 4: 306 and 1490; 269 x 320, k 5, batch 1: 18 and 23; below the lines 691 x 628, k 13, s 2, batch 3: 122 and 76;
 // 176 x 128, k 7, batch 8: 25 and 17; 1292 x 1151, k 1, batch 4: 37 and 26).
 // Columns of one entry below batch 4, and of up to four at stride 1, are added to y directly; at strides above 1 these
@@ -1530,7 +1530,7 @@ static CscGatherChoice choose_csc_gather(const conv_plan *plan, int batch) {
     if (batch >= 4) {
         const float least = kl == 1 && batch == 4 ? (s == 1 ? kCscGatherLeastOne : kCscGatherLeastOneStrided) : kCscGatherLeast[s > 1][kl];
         if (pixels_in * batch < 1000.0 * least * bar) return c;
-    } else if (kl == 1 || (kl == 2 && s == 1)) {
+    } else if (!csc_gather_few((int)kl, (int)s)) {
         return c;
     } else if (kl == 2 ? (double)plan->nnz * batch < (k < 4 ? kCscGatherDirectThree : kCscGatherDirect) * bar
                        : pixels_in * std::sqrt((double)batch) < 1000.0 * kCscGatherLeastFew[s > 1][kl] * bar) {

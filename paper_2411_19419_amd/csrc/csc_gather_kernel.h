@@ -106,6 +106,9 @@ __host__ __device__ constexpr int csc_gather_tw(int k, int s, int lpr_log2, bool
     return 0;
 }
 
+// Do batches below 4 columns gather, somewhere?  (Columns of one entry, and of four at stride 1, are added to y directly.)
+__host__ __device__ constexpr bool csc_gather_few(int kl, int s) { return kl > (s == 1 ? 2 : 1); }
+
 // Entries along one axis before line (pixel) t, T^T.
 __device__ __forceinline__ long long csc_gather_prefix(long long zero, int t, int count_out, const ConvShape &sh) {
     return started_sum((long long)t + sh.p, sh.s, count_out) - started_sum((long long)t + sh.p - sh.k, sh.s, count_out) - zero;
@@ -347,7 +350,7 @@ __global__ __launch_bounds__(kCscGatherThreads, 2) void spmm_csc_gather_kernel(c
         }
     };
     // The sums of this line's taps: part[l] for output line xtop - l, l < KN
-    const int step_ph = ways % s, step_at = (step_ph * pw + ways / s) << lpr_log2, wrap_at = (1 - s * pw) << lpr_log2;
+    const int step_ph = ways % s, step_at = (step_ph * pw + ways / s) << lpr_log2, wrap_at = (1 - s * pw) * (1 << lpr_log2);
     const int way_ph = way % s, way_at = ((way_ph * pw + way / s + yl) << lpr_log2) + v;
     const int way_slot = (way * tw + yl) * PITCH, step_slot = ways * tw * PITCH;
     auto push = [&](auto kn_tag, int buf, elem_t (&part)[KL]) {

@@ -20,11 +20,13 @@ void launch_csc_gather_one(const CscGatherChoice &c, const conv_plan *plan, cons
 template <int KL, bool SCALAR>
 void launch_csc_gather_kl(const CscGatherChoice &c, const conv_plan *plan, const float *x, float *y, hipStream_t q) {
     if (plan->shape.s > 1) {
-        if (c.nld != 2) launch_csc_gather_inst<KL, 0, 0, 0, SCALAR, 5, 3, 1>(c, plan, x, y, q);
-        else if (c.nx == 1) launch_csc_gather_inst<KL, 0, 0, 0, SCALAR, 2, 1, 2>(c, plan, x, y, q);
+        if constexpr (KL > 2) {         // (k <= 2 s: fewer than 512 pixels' entries are at most 512 accesses, NLD 2)
+            if (c.nld != 2) return launch_csc_gather_inst<KL, 0, 0, 0, SCALAR, 5, 3, 1>(c, plan, x, y, q);
+        }
+        if (c.nx == 1) launch_csc_gather_inst<KL, 0, 0, 0, SCALAR, 2, 1, 2>(c, plan, x, y, q);
         else launch_csc_gather_inst<KL, 0, 0, 0, SCALAR, 2, 3, 2>(c, plan, x, y, q);
     } else if constexpr (SCALAR) {
-        launch_csc_gather_one<KL, 0, true>(c, plan, x, y, q);
+        if constexpr (csc_gather_few(KL, 1)) launch_csc_gather_one<KL, 0, true>(c, plan, x, y, q);
     } else {
         if (c.geom.lpr_log2 == 0) launch_csc_gather_one<KL, 0, false>(c, plan, x, y, q);
         else if (c.geom.lpr_log2 == 1) launch_csc_gather_one<KL, 1, false>(c, plan, x, y, q);
@@ -35,7 +37,9 @@ void launch_csc_gather_kl(const CscGatherChoice &c, const conv_plan *plan, const
 template <bool SCALAR>
 void launch_csc_gather_any(const CscGatherChoice &c, const conv_plan *plan, const float *x, float *y, hipStream_t q) {
     switch (c.kl) {
-        case 1: launch_csc_gather_kl<1, SCALAR>(c, plan, x, y, q); break;
+        case 1:
+            if constexpr (!SCALAR || csc_gather_few(1, 2)) launch_csc_gather_kl<1, SCALAR>(c, plan, x, y, q);
+            break;
         case 2: launch_csc_gather_kl<2, SCALAR>(c, plan, x, y, q); break;
         case 3: launch_csc_gather_kl<3, SCALAR>(c, plan, x, y, q); break;
         case 4: launch_csc_gather_kl<4, SCALAR>(c, plan, x, y, q); break;

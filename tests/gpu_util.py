@@ -89,6 +89,14 @@ def build_plan_t(shape, K):
                                      torch.from_numpy(np.ascontiguousarray(K, dtype=np.float32)).to(device())))
 
 
+def keep_to_the_scatter(plan, shape, batch, kernel=7):
+    """The test hook's largest threshold: conv_spmv_from_csc does not gather, whatever the shape; it keeps
+    the sums of a tile on chip (kernel 7) or adds to y directly (8)."""
+    never = 2 ** 31 - 1
+    cs.conv_plan_set_march_min_jobs(plan, never)
+    assert cs.conv_dispatch_info(*shape, batch, 3, march_min_jobs=never).kernel == kernel
+
+
 def check_csc(plan, shape, K):
     """col_ptr, row_idx and vals of T column-compressed, bit-exact against the oracle."""
     m, n, k, s, p = shape

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import paper_2411_19419_amd as cs
-from gpu_util import REL_TOL, device
+from gpu_util import REL_TOL, device, keep_to_the_scatter
 
 pytestmark = pytest.mark.gpu
 
@@ -429,6 +429,10 @@ def test_rows_at_the_last_entry_numbers():
     y = torch.full((plan.cols,), float("nan"), device=device())
     cs.conv_spmv_from_csc(plan, x, y)
     check(y, x, 1, "from csc")
+    keep_to_the_scatter(plan, shape, 1, kernel=8)
+    y.fill_(float("nan"))
+    cs.conv_spmv_from_csc(plan, x, y)
+    check(y, x, 1, "scatter")
     plan.close()
     del plan
     torch.cuda.empty_cache()

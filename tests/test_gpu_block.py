@@ -23,15 +23,18 @@ def _check(got, ref, scale, what):
 @pytest.mark.parametrize("storage,k,s", SHAPES)
 def test_blocks_at_edges_and_paddings(storage, k, s):
     """Planes that end anywhere in a block, padding from none to more than the kernel, lanes full and partly idle,
-    batches that are no multiple of 4, operands at any float address."""
+    batches that are no multiple of 4, operands at any float address.  The first plane is the smallest one that the dispatch gives
+    to blocks; the others are lines of pixels, which it may give to another kernel."""
     rng = np.random.default_rng(100 * k + s)
     conv = oracle.conv if storage == "csr" else oracle.conv_t
-    served = 0
     for i, (p, batch) in enumerate(((0, 64), (k // 2, 125), (k - 1, 131), (k + 1, 49), (k // 2, 256))):
-        for m, n in ((92 * s + i, 90 * s + 2 * i + 1), (k + 2, 900 * s + i), (900 * s + i, k + 1), (k, 9 * s + i)):
+        planes = [(f * s + i, f * s - s + 2 * i + 1) for f in (16, 24, 32, 48, 64, 92, 120, 150, 180, 220)]
+        m0, n0 = next((m, n) for m, n in planes
+                      if cs.conv_dispatch_info(m, n, k, s, p, batch, int(storage == "csc")).kernel == 12)
+        for m, n in ((m0, n0), (k + 2, 900 * s + i), (900 * s + i, k + 1), (k, 9 * s + i)):
             K = rng.standard_normal(k * k).astype(np.float32)
             plan = (cs.conv_csr_build if storage == "csr" else cs.conv_csc_build)(m, n, k, s, p, torch.from_numpy(K).to(device()))
-            served += plan.variant(batch).startswith("block_")
+            assert (m, n) != (m0, n0) or plan.variant(batch).startswith("block_")
             x = rng.standard_normal(plan.cols * batch).astype(np.float32)
             xb = torch.full((x.size + 4,), 7.0, device=device())
             yb = torch.full((plan.rows * batch + 8,), 7.0, device=device())
@@ -44,7 +47,6 @@ def test_blocks_at_edges_and_paddings(storage, k, s):
             edge = yb.cpu().numpy()
             assert np.all(edge[:4 - i % 4] == 7.0) and np.all(edge[4 - i % 4 + plan.rows * batch:] == 7.0)
             plan.close()
-    assert served >= 4
 
 
 @pytest.mark.parametrize("storage,shape,batch", [("csr", (60, 71, 3, 1, 1), 64), ("csr", (200, 183, 5, 2, 2), 112),
@@ -86,4 +88,35 @@ def test_blocks_read_the_stored_arrays(storage, shape, batch):
     plan.vals.copy_(torch.from_numpy(vals))
     hit = ~np.isfinite(cs.conv_spmv(plan, xd, batch=batch).cpu().numpy().reshape(-1, batch)).all(axis=1)
     assert list(np.flatnonzero(hit)) == [rows[0]]
+    plan.close()
+
+
+@pytest.mark.parametrize("storage", ["csr", "csc"])
+def test_blocks_of_operands_just_below_four_gib(storage):
+    """Byte offsets of 32 bits, unsigned: 3900 x 4000 pixels of 68 columns are 4.24e9 bytes, the first and the last 24 lines
+    against float64 sums."""
+    shape, batch, lines = (3900, 4000, 3, 1, 1), 68, 24
+    m, n, k, s, p = shape
+    g = torch.Generator(device=device()).manual_seed(6)
+    K = torch.randn(k * k, device=device(), generator=g)
+    plan = (cs.conv_csr_build if storage == "csr" else cs.conv_csc_build)(*shape, K)
+    assert plan.variant(batch).startswith("block_") and 4 * plan.cols * batch > 0.98 * 2 ** 32
+    x = torch.randn(plan.cols * batch, device=device(), generator=g)
+    y = torch.full((plan.rows * batch,), float("nan"), device=device())
+    cs.conv_spmv(plan, x, y, batch=batch)
+    taps = K if storage == "csr" else K.flip(0)              # T^T at "same" padding: the kernel turned round
+    for top in (True, False):
+        pad = torch.zeros(lines + 2, n + 2, batch, dtype=torch.float64, device=device())
+        if top:
+            pad[1:, 1:-1] = x.view(m, n, batch)[:lines + 1]
+        else:
+            pad[:-1, 1:-1] = x.view(m, n, batch)[m - lines - 1:]
+        got = y.view(m, n, batch)[:lines] if top else y.view(m, n, batch)[m - lines:]
+        ref, scale = torch.zeros_like(got, dtype=torch.float64), torch.zeros_like(got, dtype=torch.float64)
+        for a in range(k):
+            for b in range(k):
+                ref += taps[a * k + b].double() * pad[a:a + lines, b:b + n]
+                scale += taps[a * k + b].double().abs() * pad[a:a + lines, b:b + n].abs()
+        assert bool(((got.double() - ref).abs() <= REL_TOL * scale).all()), top
+    assert not bool(torch.isnan(y).any())
     plan.close()

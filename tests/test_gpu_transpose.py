@@ -10,7 +10,7 @@ import oracle
 import paper_2411_19419_amd as cs
 from paper_2411_19419_amd import workloads
 
-from gpu_util import build_plan, build_plan_t, check_apply_t, check_csc, device
+from gpu_util import build_plan, build_plan_t, check_apply_t, check_csc, device, keep_to_the_scatter
 
 pytestmark = pytest.mark.gpu
 
@@ -78,11 +78,12 @@ def test_transposed_named_workloads_full_size(name):
     plan.close()
 
 
+@pytest.mark.parametrize("scatter", [False, True])
 @pytest.mark.parametrize("name", ["strided_256_k5_b64", "headline_1024_k7_b1", "headline_1024_k7_b16",
                                   "padheavy_512_k9_s3", "cnn_224_k3_b256"])
-def test_product_from_csc_named_workloads_full_size(name):
+def test_product_from_csc_named_workloads_full_size(name, scatter):
     """y = T x from the column-compressed arrays at the sizes the benchmark times, the whole result
-    against the sliding-window oracle."""
+    against the sliding-window oracle; by the kernel of the dispatch and by the scatter."""
     w = workloads.WORKLOADS[name]
     batch = min(w.batch, 64)
     m, n, k, s, p = w.shape
@@ -90,6 +91,8 @@ def test_product_from_csc_named_workloads_full_size(name):
     x = rng.standard_normal(m * n * batch).astype(np.float32)
     K = rng.standard_normal(k * k).astype(np.float32)
     plan = build_plan_t(w.shape, K)
+    if scatter:
+        keep_to_the_scatter(plan, w.shape, batch)
     y = cs.conv_spmv_from_csc(plan, torch.from_numpy(x).to(device()), batch=batch)
     torch.cuda.synchronize()
     got = y.cpu().numpy()
@@ -302,8 +305,8 @@ def test_product_from_csc_into_an_unaligned_result(offset, batch):
 
 
 def test_product_from_csc_reads_the_stored_arrays():
-    """The scatter uses the stored row indices and values, wherever they point: one entry of a
-    column is sent to a row far from the pixel's windows (outside what the workgroup keeps on
+    """The scatter (for which this plane is small enough) uses the stored row indices and values, wherever they
+    point: one entry of a column is sent to a row far from the pixel's windows (outside what the workgroup keeps on
     chip) and one value is changed; the result must be the product with that edited matrix."""
     import scipy.sparse as sp
     shape, batch = (96, 80, 7, 1, 3), 16
@@ -312,6 +315,7 @@ def test_product_from_csc_reads_the_stored_arrays():
     x = rng.standard_normal(m * n * batch).astype(np.float32)
     K = rng.standard_normal(k * k).astype(np.float32)
     plan = build_plan_t(shape, K)
+    assert cs.conv_dispatch_info(*shape, batch, 3).kernel == 7
     cp, ri, va = oracle.csc(m, n, k, s, p, K)
     col = 40 * n + 9
     e = int(cp[col]) + 5
@@ -337,9 +341,11 @@ def test_product_from_csc_reads_the_stored_arrays():
     plan.close()
 
 
+@pytest.mark.parametrize("scatter", [False, True])
 @pytest.mark.parametrize("shape", [(96, 80, 3, 1, 1), (96, 80, 5, 2, 2), (60, 70, 4, 1, 2), (96, 80, 7, 2, 3), (96, 80, 2, 1, 1)])
-def test_product_from_csc_with_short_columns_reads_the_stored_arrays(shape):
-    """Short columns (k = 3, 4, 5: several columns share a step of the scatter).  One entry is
+def test_product_from_csc_with_short_columns_reads_the_stored_arrays(shape, scatter):
+    """Short columns (k = 3, 4, 5: several columns share a step of the scatter), by the kernel of the
+    dispatch and by the scatter.  One entry is
     sent to the row two outputs further right, which the workgroup still keeps on chip but
     which no window over that pixel has; another to the far end of y.  The result must be the
     product with the edited matrix."""
@@ -350,6 +356,8 @@ def test_product_from_csc_with_short_columns_reads_the_stored_arrays(shape):
     x = rng.standard_normal(m * n * batch).astype(np.float32)
     K = rng.standard_normal(k * k).astype(np.float32)
     plan = build_plan_t(shape, K)
+    if scatter:
+        keep_to_the_scatter(plan, shape, batch)
     cp, ri, va = oracle.csc(m, n, k, s, p, K)
     ri2 = ri.copy()
     edits = []

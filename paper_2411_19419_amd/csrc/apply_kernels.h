@@ -6,6 +6,7 @@
 // convolution is assumed beyond "a row has at most k*k entries".
 #pragma once
 #include "device_util.h"
+#include "edited_word.h"
 
 namespace convspmv {
 

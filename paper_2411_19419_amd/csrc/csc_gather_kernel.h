@@ -38,6 +38,7 @@
 
 #include "build_kernels.h"
 #include "apply_march_kernel.h"
+#include "edited_word.h"
 
 namespace convspmv {
 

@@ -66,13 +66,4 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Where a product from column-compressed arrays notes that they do not hold what the build wrote (csc_gather_kernel.h): a
-// word of the device that one plan has to itself.  It holds `stamp` from then on (before, another value, whatever an
-// earlier plan left there).
-struct EditedWord {
-    unsigned *word;
-    unsigned stamp;
-};
-__device__ __forceinline__ bool noted_edited(const EditedWord &e) { return *const_cast<const volatile unsigned *>(e.word) == e.stamp; }
-
 }  // namespace convspmv

@@ -15,6 +15,10 @@
 // i + p - s x of operand line x.  Blocks then start where i + p is a multiple of s, so that which taps an output
 // has is known to the compiler.
 //
+// Edited arrays, all rows of them (one row): 224^2, k 3, batch 256: 39 us (19), tile kernel 30; 256^2, k 5, s 2, batch 64: 17 (14) and 10;
+// 224^2, k 5, batch 64: 54 (24), marching kernel 18.  The loop reads a pixel per entry and is bound by the caches; more loads
+// ahead cost registers that the other path needs and did not help.
+//
 // Measured, fresh operands on every call: 224^2, k 3, batch 256: 17.8 us (6.0 TB/s of the bytes it cannot do without), the tile
 // kernel 29.0; its T^T 18.0 and 28.7; 256^2, k 5, s 2, T^T, batch 256: 14.0 and 29.6, batch 64: 6.4 and
 // 9.0.  What bounds it: memory where the plane is large, a chain of two loads (row pointer, entry) and the sums where it is small.

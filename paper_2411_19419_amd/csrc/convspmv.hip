@@ -47,7 +47,7 @@ struct LaunchScope {
     }
 };
 
-// The words (device_util.h) in which products from column-compressed arrays note edited columns: a static array of every
+// The words (edited_word.h) in which products from column-compressed arrays note edited columns: a static array of every
 // device, so that a build allocates nothing.  A plan has its place to itself until it is destroyed, which is after its
 // last product; places are taken again in the order in which they came back, with another stamp.  A plan that finds
 // none left (65536 plans at a time) scatters.

@@ -16,13 +16,14 @@
 //   - The row index an entry must have is kept beside its place and compared with the stored one when the entry
 //     lands, so the indices need no room in LDS, and an entry is compared once, not once per batch column.
 //   - The taps of an input line are summed before the lines are, so that a sum rounds about 2 k times and not k * k
-//     times (1024^2, k 7: 6.4e-8 from 64 bits, 9.3e-8 from the scatter).
+//     times (1024^2, k 7, batch 16: 7.5e-8 from 64 bits, the scatter 1.0e-7).
 // y is written once, in a fixed order of sums, and never read.
 //
-// Measured, 1024^2, k 7, batch 16: 103 us (5.3 TB/s of the bytes it cannot do without, 6.1 with the lines and columns that
-// neighbours share), the scatter 357; batch 1: 78 and 157.  What bounds it: memory where the kernel is large, the time
-// of a line (about 0.7 us, LDS round trips, one barrier) where it is small (1000 x 900, k 3, batch 16: 36 us, 5.1 TB/s;
-// the scatter 215).  Hence the strips of 64 columns, the walk without branches at stride 1 (51 -> 36 us at k 3) and two
+// Measured with the two launches behind it (below), 1024^2, k 7, batch 16: 113 us where every call brings another matrix (4.9 TB/s of the
+// bytes it cannot do without), the scatter 359; one matrix, other operands on every call: 102, the scatter 358; batch 1: 80 and
+// 157.  What bounds it: memory where the kernel is large, the time
+// of a line (about 0.7 us, LDS round trips, one barrier) where it is small (1000 x 900, k 3, batch 16: 39 us;
+// the scatter 217).  Hence the strips of 64 columns, the walk without branches at stride 1 (51 -> 36 us at k 3) and two
 // lines in flight only where they cost few registers (k 11, batch 16: 106 us with two, 72 with one).
 //
 // The arrays decide, not the geometry: a workgroup that meets a row index which is not the one its place asks for, or a
@@ -32,7 +33,7 @@
 // remembered in the other direction: arrays not noted are checked whole by every product, so products that run side by
 // side on a plan come to one answer.  One row index edited or all of them, 1024^2, k 7, batch 16: 540 and 690 us the first
 // time, 410 then, the scatter by itself 358 (the outputs concerned summed again, one workgroup for each of the
-// gather's: 7300 and 15600).  What the two launches cost where nothing is edited: 3 us (one: 1.5), 101 us with them.
+// gather's: 7300 and 15600).  What the two launches cost where nothing is edited: 3 us (one: 1.5).
 #pragma once
 #include <type_traits>
 

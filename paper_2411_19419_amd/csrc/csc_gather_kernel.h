@@ -196,11 +196,18 @@ __global__ __launch_bounds__(kCscGatherThreads, 2) void spmm_csc_gather_kernel(c
 
     for (int t = tid; t < 2 * line_elems; t += NT) lines[t] = elem_t(0.0f);
     for (int t = tid; t < 2 * image_words; t += NT) images[t] = 0.0f;
+    // One thread's reading for the whole workgroup (others may note the plan meanwhile, and places that waves deal out
+    // among them have to be found by all): in the last word of the second image's dump, which is not written before the barrier of
+    // the first line, by the thread that has cleared it.
+    unsigned *const told = reinterpret_cast<unsigned *>(images + 2 * image_words - 1);
+    if (tid == (2 * image_words - 1) % NT) {
+        arrived(noted);
+        *told = noted;
+    }
     const long long p2a = csc_gather_prefix(g.zero2, job.j0, sh.n_out, sh);
     for (int t = tid; t <= job.npix; t += NT) p2[t] = (int)(csc_gather_prefix(g.zero2, job.j0 + t, sh.n_out, sh) - p2a);
     __syncthreads();
-    arrived(noted);
-    if (noted == edited.stamp) return;                       // (perhaps not all waves, while another workgroup notes it: y is written again anyway)
+    if ((unsigned)__builtin_amdgcn_readfirstlane((int)*told) == edited.stamp) return;                       // (y is written by the launches behind this one)
     const int taps = __builtin_amdgcn_readfirstlane(p2[job.npix]);
 
     // this lane: batch columns, output column, share of the tap columns

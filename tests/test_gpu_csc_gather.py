@@ -217,6 +217,29 @@ def test_replays_follow_arrays_edited_between_them():
     plan.close()
 
 
+@pytest.mark.parametrize("shape,batch", [((24, 9100, 7, 1, 3), 128), ((30, 5000, 11, 1, 5), 64)])
+def test_workgroups_that_start_while_the_plan_is_noted(shape, batch):
+    """More workgroups than run at once, every column edited: the later ones read the note of the earlier ones while it is
+    written, each as a whole."""
+    x, K = inputs(shape, batch, 16)
+    xd = torch.from_numpy(x).to(device())
+    ref, scale = oracle.conv(*shape, x, K, batch=batch, want_scale=True)
+    assert cs.conv_dispatch_info(*shape, batch, 3).kernel == 11 and cs.conv_dispatch_info(*shape, batch, 3).workgroups > 600
+    for rep in range(3):
+        plan = build_plan_t(shape, K)
+        first = plan.row_ptr[:-1].long()
+        first = first[plan.row_ptr[1:].long() - first > 1]           # the first two entries of a column change places
+        for a in (plan.col_idx, plan.vals):
+            b = a[first].clone()
+            a[first] = a[first + 1]
+            a[first + 1] = b
+        y = torch.full((plan.cols * batch,), float("nan"), device=device())
+        cs.conv_spmv_from_csc(plan, xd, y, batch=batch)
+        got = y.cpu().numpy()
+        assert np.all(np.abs(got.astype(np.float64) - ref.astype(np.float64)) <= REL_TOL * scale), rep
+        plan.close()
+
+
 def test_a_plan_edited_on_two_streams_at_once():
     """Products of one edited plan side by side on two streams, of two batches (two launch shapes), first calls included."""
     import scipy.sparse as sp

@@ -264,3 +264,42 @@ def test_a_plan_edited_on_two_streams_at_once():
             X = xs[b].cpu().numpy().reshape(-1, b).astype(np.float64)
             assert np.all(np.abs(y.cpu().numpy().reshape(-1, b) - T @ X) <= REL_TOL * (abs(T) @ np.abs(X)) + 1e-30), (rep, b)
         plan.close()
+
+
+def test_more_plans_than_places_for_the_note():
+    """65536 plans at a time have a word to note edited columns in; one more scatters, and once the others are gone a plan takes the
+    place of an earlier one, whose note it does not inherit."""
+    import ctypes
+    from paper_2411_19419_amd import binding
+    lib, small = binding._load(), (3, 3, 2, 1, 1)
+    arrays = build_plan_t(small, np.ones(4, dtype=np.float32))
+    K4 = torch.ones(4, device=device())
+    at = [t.data_ptr() for t in (K4, arrays.row_ptr, arrays.col_idx, arrays.vals)]
+    handles = []
+    for _ in range(65536):
+        handle = ctypes.c_void_p()
+        assert lib.conv_csc_build(*small, *at, None, ctypes.byref(handle)) == 0
+        handles.append(handle)
+    shape, batch = (90, 129, 3, 1, 1), 18
+    x, K = inputs(shape, batch, 17)
+    ref, scale = oracle.conv(*shape, x, K, batch=batch, want_scale=True)
+    xd = torch.from_numpy(x).to(device())
+
+    def product(edited):
+        plan = plan_of(shape, K, batch)
+        if edited:                                                   # the first two entries of a column change places
+            e = int(plan.row_ptr[700])
+            for a in (plan.col_idx, plan.vals):
+                a[e:e + 2] = a[e:e + 2].flip(0)
+        for _ in range(2):
+            got = cs.conv_spmv_from_csc(plan, xd, batch=batch).cpu().numpy()
+            assert np.all(np.abs(got.astype(np.float64) - ref.astype(np.float64)) <= REL_TOL * scale)
+        plan.close()
+    product(False)
+    product(True)
+    torch.cuda.synchronize()
+    for handle in handles:
+        assert lib.conv_plan_destroy(handle) == 0
+    for edited in (True, False, True):
+        product(edited)
+    arrays.close()

@@ -204,7 +204,8 @@ int conv_spmv(const conv_plan *plan, const float *x_dev, float *y_dev, int batch
  * output is summed in registers, from entries whose stored row index is
  * compared with the one their place asks for.  Arrays found to hold another one,
  * or another column pointer, are multiplied by the scatter instead, behind the
- * gather in that call and in its place in the plan's later ones.  The scatter:
+ * gather in that call and in its place in the plan's later ones.  (A plan built
+ * while 65536 others from conv_csc_build exist always scatters.)  The scatter:
  * y is zeroed and the sums of a tile of neighbouring pixels are collected on
  * chip and added to y with hardware float adds (for 2 <= ceil(k/s) <= 32, from 3
  * at batches below 4), or every entry is added to y directly.  The result is

@@ -142,7 +142,8 @@ __global__ __launch_bounds__(512, 4) void spmm_march_kernel(const int *__restric
     auto fetch = [&](const Bounds &b, Pass &ps) {
         ps.beg = b.beg;
         ps.end = b.end;
-        const int span_base = __builtin_amdgcn_readfirstlane(b.beg);
+        // (an entry that exists: a wave without a row on the last line begins behind the last entry, and so do rows without any)
+        const int span_base = min(__builtin_amdgcn_readfirstlane(b.beg), g.nnz - 1);
         const int span_end = __builtin_amdgcn_readlane(b.end, kWave - 1);
         const int *cb = col_idx + span_base;
         const float *vb = vals + span_base;

@@ -251,7 +251,8 @@ __global__ __launch_bounds__(TW * 8) void spmm_tile_kernel(const int *__restrict
             ps.end = rp_line[yy + 1];
         }
         // wave-uniform base: first entry of the tile line; lane offsets from it stay small
-        const int line_base = __builtin_amdgcn_readfirstlane(rp_line[0]);
+        // (one that exists: with padding of the kernel's size and more, lines without entries may begin behind the last)
+        const int line_base = min(__builtin_amdgcn_readfirstlane(rp_line[0]), g.nnz - 1);
         const int span_end = __builtin_amdgcn_readfirstlane(rp_line[min(yy0 + RW, twc)]);
         const int *cb = col_idx + line_base;
         const float *vb = vals + line_base;

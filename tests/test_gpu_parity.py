@@ -554,3 +554,42 @@ def test_graph_replays_of_channel_sums_and_of_the_csc_product():
             assert np.all(err <= REL_TOL * scale + 1e-30), rep
     for pl in sums + cscs:
         pl.close()
+
+
+@pytest.mark.parametrize("storage,shape,batch,jobs,kernel", [
+    # tiles and marches whose last lines or waves have no entries, or no row: padding of the kernel's size and more, ragged strips
+    ("csr", (224, 224, 3, 1, 4), 16, None, "lds_tile_"), ("csc", (224, 223, 3, 1, 3), 16, None, "lds_tile_"),
+    ("csr", (150, 201, 4, 1, 6), 3, 1, "lds_march_"), ("csc", (90, 100, 8, 2, 9), 3, 1, "lds_march_"),
+    ("csr", (90, 99, 9, 1, 9), 4, 1, "lds_march_"), ("csr", (150, 379, 4, 1, 0), 18, 1, "lds_march_"),
+    ("csr", (180, 190, 3, 1, 4), 64, None, "block_"), ("csc", (180, 190, 5, 2, 7), 64, None, "block_"),
+    ("csr", (150, 160, 5, 1, 7), 3, None, "gather_"),
+])
+def test_entries_that_end_where_their_memory_ends(storage, shape, batch, jobs, kernel):
+    """The arrays end with allocations of their own: nothing behind the last entry may be asked for."""
+    import ctypes
+    from paper_2411_19419_amd import binding
+    lib = binding._load()
+    m, n, k, s, p = shape
+    mo, no = oracle.out_shape(*shape)
+    nnz, rows = oracle.nnz_closed(*shape), mo * no if storage == "csr" else m * n
+    cols = m * n if storage == "csr" else mo * no
+    rng = np.random.default_rng(61)
+    x, K = rng.standard_normal(cols * batch).astype(np.float32), rng.standard_normal(k * k).astype(np.float32)
+    size = 16 << 18                          # 16 MiB: a whole number of the allocator's 2 MiB pieces
+    assert nnz <= size
+    xd, Kd = torch.from_numpy(x).to(device()), torch.from_numpy(K).to(device())
+    first = (size - nnz) // 4 * 4            # (on 16 bytes: up to three entries are left behind the last)
+    idx, vals = (torch.empty(size, dtype=t, device=device())[first:first + nnz] for t in (torch.int32, torch.float32))
+    ptr = torch.empty(rows + 1, dtype=torch.int32, device=device())
+    y = torch.full((rows * batch,), float("nan"), device=device())
+    stream, handle = torch.cuda.current_stream().cuda_stream, ctypes.c_void_p()
+    build = lib.conv_csr_build if storage == "csr" else lib.conv_csc_build
+    assert build(m, n, k, s, p, *(t.data_ptr() for t in (Kd, ptr, idx, vals)), stream, ctypes.byref(handle)) == 0
+    if jobs:
+        lib.conv_plan_set_march_min_jobs(handle, jobs)
+    assert lib.conv_spmv_variant(handle, batch).decode().startswith(kernel), lib.conv_spmv_variant(handle, batch)
+    assert lib.conv_spmv(handle, xd.data_ptr(), y.data_ptr(), batch, stream) == 0
+    torch.cuda.synchronize()
+    ref, scale = (oracle.conv if storage == "csr" else oracle.conv_t)(m, n, k, s, p, x, K, batch=batch, want_scale=True)
+    assert np.all(np.abs(y.cpu().numpy().astype(np.float64) - ref.astype(np.float64)) <= REL_TOL * scale)
+    lib.conv_plan_destroy(handle)

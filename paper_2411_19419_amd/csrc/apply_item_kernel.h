@@ -1,0 +1,234 @@
+// Product over the stored CSR arrays, a thread or a few per item: a row and a chunk of its batch columns (gfx950).
+//
+// The row groups of apply_kernels.h give a lane up to 16 batch columns, and a wave as many rows: its accesses are pieces of 16
+// bytes at as many places as it has rows, and a batch that does not fill the blocks of 16 columns leaves lanes idle (so do tiles and marches).  Here the
+// chunks of four columns of a row lie side by side on the lanes (one column each below a batch of 4), then those of the next row: x and y move in whole
+// memory lines whatever the batch, the lanes of a row ask for the same entries with one access, and no lane is idle but the
+// launch's last.  No staging and no barrier: neighbouring rows share their pixels through the L1 and the L2 (workgroups of
+// neighbouring rows run on one XCD).
+//
+// G lanes share an item where the launch has few waves; lane l takes U consecutive entries at a time, U l, U l + U G, ...,
+// NB such accesses are asked for together with their pixels after them.  U fits the rows: 25 entries in fives, others in fours;
+// rows of 9 at once (a tail of one entry would cost four pixels).
+// Sums: each access is a chain of its own, added to one of NB sums (LONG, rows above 64 entries and one or two lanes: two sets of them
+// in turn); rows of 9 entries as two chains of every other entry, the order of the tile kernel.  Error against 64 bits over drawn products, over that of
+// the kernels it takes them from: 0.96 to 1.05 in the mean of every k (one chain for a row: 1.6 at k 13).
+//
+// MANY: several channels that share the indices.  The waves of a workgroup hold the same items and deal the channels out; a lane
+// keeps its entries' columns while NB of its channels pass, and the partial sums meet in LDS.
+//
+// Measured, fresh operands, before -> after: 1362 x 1644, k 1, s 2, batch 100: 656 -> 106 us (tiles); 909 x 1348, k 6, s 3,
+// batch 132: 1153 -> 226 (march); 70 x 91, k 6, T^T, batch 85: 34 -> 7.3 (staged march); 755 x 1134, k 7, s 4, batch 116: 427 -> 125 (row
+// groups); 2388 x 1551, k 3, s 3, T^T, batch 64: 676 -> 420; 36 x 52, k 7, s 4, 206 channels, batch 8: 317 -> 25; 30 x 31, k 9, s 3, 136 channels,
+// batch 2: 273 -> 23.  What bounds it: large products the L2, which delivers every pixel once per entry but for what the
+// L1 catches (11 TB/s at 733 x 667, k 6, s 3, batch 204, 139 us); small ones a round trip for the row's bounds and two for
+// every NB U G entries.  Not kept: blocks of 4 to 32 chunks at a time instead of all of a row's (1.03 to 1.27 of the time); the next
+// entries asked for ahead of the sums (0.97 of the time in small products, 1.06 in large ones, which lose waves to the registers);
+// entries and values of channels by accesses of 16 bytes with a masked tail (1.08).
+#pragma once
+#include "apply_kernels.h"
+
+namespace convspmv {
+
+constexpr int kItemThreads = 256;
+constexpr int kItemWaysMost = 16;
+
+struct ItemGeom {
+    int batch;
+    int chunks;                        // chunks of columns per row
+    float inv_chunks;
+    unsigned items;                    // rows * chunks
+    int cells, cells_per_xcd;          // workgroups
+    int channels, ways;                // MANY: waves of a workgroup, which deal the channels out
+    long long vals_stride, x_stride;   // from a channel's values and plane to the next one's
+};
+
+// C: columns of a chunk.  x and y are addressed by 32-bit byte offsets, columns are below 2^24 (item_geometry).
+template <int G, int C, int U, int NB, bool LONG, bool MANY>
+__global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void spmm_item_kernel(
+    const int *__restrict__ row_ptr, const int *__restrict__ col_idx, const float *__restrict__ vals,
+    const float *__restrict__ x, float *__restrict__ y, const ItemGeom g) {
+    typedef float part __attribute__((ext_vector_type(C)));
+    typedef float part_at __attribute__((ext_vector_type(C), aligned(4)));
+    constexpr int ITEMS = kWave / G;                 // of a wave
+    const int at = (int)blockIdx.x / kXcds, cell = ((int)blockIdx.x % kXcds) * g.cells_per_xcd + at;
+    if (at >= g.cells_per_xcd || cell >= g.cells) return;
+    const int lane = (int)threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const unsigned first = MANY ? (unsigned)cell * ITEMS : ((unsigned)cell * (kItemThreads / kWave) + wave) * ITEMS;
+    const unsigned row0 = first / (unsigned)g.chunks;
+    const int t = (int)(first - row0 * (unsigned)g.chunks) + lane / G, sub = lane % G;
+    const int q = div_small(t, g.inv_chunks);
+    const int row = (int)row0 + q, chunk = t - q * g.chunks;
+    const int c = C == 4 ? chunk_col(4 * chunk, g.batch) : chunk;
+    const bool live = first + (unsigned)(lane / G) < g.items;
+    unsigned beg = 0, end = 0;
+    if (live) {
+        beg = row_ptr[row];
+        end = row_ptr[row + 1];
+    }
+    auto pixel = [&](const float *xc, int col) -> part {
+        return *reinterpret_cast<const part_at *>(reinterpret_cast<const char *>(xc) + (__umul24(col, 4 * g.batch) + 4u * (unsigned)c));
+    };
+    auto mul_part = [&](float w, part p) -> part {
+        part r;
+#pragma unroll
+        for (int h = 0; h < C; ++h) r[h] = w * p[h];
+        return r;
+    };
+    auto fma_part = [&](float w, part p, part s) -> part {
+        part r;
+#pragma unroll
+        for (int h = 0; h < C; ++h) r[h] = fmaf(w, p[h], s[h]);
+        return r;
+    };
+    part acc = part(0.0f);
+    if constexpr (!MANY && NB == 1) {
+        // a row at once (the loop is for edited rows that are longer)
+        static_assert(G <= 2, "the chains of two lanes per row");
+        part odd = part(0.0f);
+        for (unsigned e = beg + sub; e < end; e += U * G) {
+            int col[U];
+            float val[U];
+            part px[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned i = min(e + u * G, end - 1);
+                col[u] = col_idx[i];
+                val[u] = vals[i];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u == 0 || e + u * G < end) px[u] = pixel(x, col[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u == 0 || e + u * G < end) {
+                    if (G == 1 && u % 2) odd = fma_part(val[u], px[u], odd);
+                    else acc = fma_part(val[u], px[u], acc);
+                }
+        }
+        if (G == 1) acc += odd;
+    } else if constexpr (!MANY) {
+        constexpr int SETS = LONG ? 2 : 1;
+        part sums[SETS][NB];
+#pragma unroll
+        for (int k = 0; k < SETS * NB; ++k) sums[k / NB][k % NB] = part(0.0f);
+        unsigned e = beg + U * sub;
+        for (; e + (NB - 1) * U * G + U <= end; e += NB * U * G) {
+            int col[NB][U];
+            float val[NB][U];
+            part px[NB][U];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int *const cs = col_idx + (e + b * U * G);
+                const float *const vs = vals + (e + b * U * G);
+#pragma unroll
+                for (int u = 0; u < U; ++u) { col[b][u] = cs[u]; val[b][u] = vs[u]; }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int u = 0; u < U; ++u) px[b][u] = pixel(x, col[b][u]);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                part s = mul_part(val[b][0], px[b][0]);
+#pragma unroll
+                for (int u = 1; u < U; ++u) s = fma_part(val[b][u], px[b][u], s);
+                const part sum = sums[0][b] + s;
+                if (LONG) sums[0][b] = sums[SETS - 1][b];
+                sums[SETS - 1][b] = sum;
+            }
+        }
+        for (; e < end; e += U * G) {
+            int col[U];
+            float val[U];
+            part px[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned i = min(e + u, end - 1);
+                col[u] = col_idx[i];
+                val[u] = vals[i];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u == 0 || e + u < end) px[u] = pixel(x, col[u]);
+            part s = sums[0][0];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u == 0 || e + u < end) s = fma_part(val[u], px[u], s);
+            sums[0][0] = sums[0][NB - 1];
+            sums[0][NB - 1] = s;
+        }
+#pragma unroll
+        for (int k = 0; k < SETS; ++k) {
+            part s = sums[k][0];
+#pragma unroll
+            for (int b = 1; b < NB; ++b) s += sums[k][b];
+            acc = k == 0 ? s : acc + s;
+        }
+    } else {
+        part sums[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) sums[b] = part(0.0f);
+        for (unsigned e = beg + U * sub; e < end; e += U * G) {
+            int col[U];
+            unsigned i[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                i[u] = min(e + u, end - 1);
+                col[u] = col_idx[i[u]];
+            }
+            for (int ch = wave; ch < g.channels; ch += NB * g.ways) {
+                float val[NB][U];
+                part px[NB][U];
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    if (b == 0 || ch + b * g.ways < g.channels) {
+                        const int cb = ch + b * g.ways;
+                        const float *const vc = vals + cb * g.vals_stride, *const xc = x + cb * g.x_stride;
+#pragma unroll
+                        for (int u = 0; u < U; ++u) val[b][u] = vc[i[u]];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) px[b][u] = pixel(xc, col[u]);
+                    }
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    if (b == 0 || ch + b * g.ways < g.channels) {
+                        if constexpr (U == 1) {
+                            sums[b] = fma_part(val[b][0], px[b][0], sums[b]);
+                        } else {
+                            part s = mul_part(val[b][0], px[b][0]);
+#pragma unroll
+                            for (int u = 1; u < U; ++u) s = e + u < end ? fma_part(val[b][u], px[b][u], s) : s;
+                            sums[b] += s;
+                        }
+                    }
+            }
+        }
+#pragma unroll
+        for (int d = 1; d < NB; d *= 2)
+#pragma unroll
+            for (int b = 0; b + d < NB; b += 2 * d) sums[b] += sums[b + d];
+        acc = sums[0];
+    }
+#pragma unroll
+    for (int h = 0; h < C; ++h) acc[h] = group_sum<G>(acc[h]);
+    if constexpr (MANY) {
+        __shared__ part shared[kItemWaysMost][ITEMS];
+        if (g.ways > 1) {
+            if (sub == 0) shared[wave][lane / G] = acc;
+            __syncthreads();
+            if (wave > 0) return;
+            part quarter[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                quarter[w] = part(0.0f);
+                for (int i = w; i < g.ways; i += 4) quarter[w] += shared[i][lane / G];
+            }
+            acc = (quarter[0] + quarter[1]) + (quarter[2] + quarter[3]);
+        }
+    }
+    if (live && sub == 0)
+        *reinterpret_cast<part_at *>(reinterpret_cast<char *>(y) + 4u * ((unsigned)row * (unsigned)g.batch + (unsigned)c)) = part_at(acc);
+}
+
+}  // namespace convspmv

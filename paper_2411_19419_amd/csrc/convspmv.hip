@@ -903,6 +903,127 @@ ApplyChoice choose_unblocked(const conv_plan *full, int batch) {
     return c;
 }
 
+// Geometry of an item launch with g lanes per item.
+bool item_geometry(const conv_plan *plan, int batch, int g, int ways, ItemGeom *out) {
+    const int columns = batch >= 4 ? 4 : 1;
+    const int64_t chunks = (batch + columns - 1) / columns, items = plan->rows * chunks, plane = plan->cols / plan->channels * batch;
+    // 32-bit byte offsets into a plane of x and into y, products of 24-bit numbers; item numbers of 32 bits; exact small divisions
+    if (plane >= (1LL << 30) || plan->rows * batch >= (1LL << 30) || plan->cols / plan->channels > (1 << 24) || batch >= (1 << 22) ||
+        items > kInt32Limit - kItemThreads || chunks + kWave >= (1 << 21))
+        return false;
+    ItemGeom i{};
+    i.batch = batch;
+    i.chunks = (int)chunks;
+    i.inv_chunks = 1.0f / (float)chunks;
+    i.items = (unsigned)items;
+    i.channels = plan->channels;
+    i.ways = ways;
+    const int64_t per_cell = (plan->channels > 1 ? kWave : kItemThreads) / g;
+    const int64_t cells = (items + per_cell - 1) / per_cell;
+    if (cells + kXcds >= (1LL << 31) / kXcds) return false;
+    i.cells = (int)cells;
+    i.cells_per_xcd = (int)((cells + kXcds - 1) / kXcds);
+    i.vals_stride = plan->nnz;
+    i.x_stride = plane;
+    *out = i;
+    return true;
+}
+
+// Where an item launch (apply_item_kernel.h) takes a product from the kernel that would have it otherwise: where a surface
+// fitted to the logarithm of the two times' ratio says that it is faster by more than `least`.  21 500 products (planes of 16 to
+// 4096 a side, k 1 to 13, strides 1 to 4, batches 1 to 256, up to 256 channels), each timed on both, with every G, in replayed
+// graphs.  The surface's coordinates: w, the multiply-adds of a chunk each (log2 of millions); b, the chunks (log2); how full the
+// other kernels' blocks of 16 columns are; a, the longest row (log2); stride 1 or not; the channels (log2).  By the kernel
+// left: products, how many leave it, time before over time after in the mean, those now more than 6 % slower, those that would still
+// be that much faster (a fit without every eighth product says the same of that one):
+//   batches 2 and 3   1023   658  1.30   48   88       row groups, T    3710  1630  1.15   89  726     T^T  2055  1007  1.19  17  425
+//   tiles, T          1952   754  1.28   13  686       marching         1236   643  1.33   14   97
+//   staged march, T    711   223  1.22    7   88       T^T               560   254  1.25    4   70
+//   2 to 15 channels: row groups 889 569 1.27 39 187  (16 and more: 976  976  2.51   31   0)     other kernels   74    36  1.54   1    8
+// What stays: products that both kernels finish within the time of a launch (w below -4, at strides of 4 and more -0.9); tiles of
+// short products (w below 2) unless items take less than two thirds of their time; tiles of T^T (1.05 in the mean) and blocks (1.1 where they would
+// leave); marching rows of 64 entries and more at batches of 2 and 3 (1.09); row groups of one column and of batches 4 to 8, which
+// are as fast (1.04 and 0.98 with the best G).
+enum ItemAgainst { kFew, kGroupsT, kGroupsTT, kTileT, kMarching, kStagedT, kStagedTT, kGroupsMany, kOthersMany };
+constexpr double kItemGain[][14] = {
+    // 1, w, w^2, b, b^2, full, a, a^2, stride 1, w a, w b, a b, w at stride 1, channels
+    {0.2361, -0.0217, -0.0118, 0.1349, -0.0256, 0, 0.0514, -0.0136, -0.0175, 0.0024, 0.0559, -0.0061, 0.017, 0},      // batches of 2 and 3
+    {-0.1285, -0.0248, -0.0029, 0.314, -0.0258, -0.0781, 0.0341, -0.0079, -0.1471, 0.0001, 0.0229, -0.0132, 0.0027, 0},      // row groups, T
+    {-0.1763, -0.0251, -0.0037, 0.318, -0.0319, -0.1487, 0.017, -0.0067, 0.0426, 0.0041, 0.013, -0.0115, 0.0248, 0},      // row groups, T^T
+    {0.4859, -0.0364, 0.0064, 0.2009, -0.0294, -0.2387, -0.0487, -0.0095, -0.0566, -0.0175, 0.0186, 0.012, -0.0491, 0},      // tiles, T
+    {0.7509, -0.0258, 0.0186, 0.3857, -0.0412, -0.0236, -0.2025, 0.0233, 0.1157, -0.0513, 0.0171, -0.0053, -0.0497, 0},      // marching
+    {2.5617, -0.06, 0.0101, 0.1433, -0.0302, -0.3139, -0.8288, 0.0718, 0.1042, -0.0228, -0.0138, 0.0484, -0.0278, 0},      // staged march, T
+    {3.6496, -0.0592, 0.01, 0.0418, -0.0324, -0.3281, -1.1654, 0.0993, 0.0721, -0.0263, -0.0087, 0.065, -0.0143, 0},      // staged march, T^T
+    {-0.0619, 0.04, -0.0029, 0.1188, -0.0039, -0.2319, -0.0023, 0.0072, -0.0693, -0.0117, -0.0055, -0.0074, 0.0023, 0.0819},      // channels, row groups
+    {2.0372, -0.2902, 0.0186, 0.1263, -0.0392, -0.4205, -0.4663, 0.0666, 0.0029, -0.036, 0.0517, -0.0004, -0.0159, 0.2347},      // channels, other kernels
+};
+constexpr double kItemLeastGain = 0.12, kItemLeastGainShortTiles = 0.4, kItemShortTiles = 2.0, kItemLeastGainFewChannels = 0.2;
+constexpr int kItemManyChannels = 16;
+constexpr double kItemLaunch = -4.0, kItemLaunchStrided = -0.9, kItemWorkMost = 7.6;        // (7.6: the fit's largest w)
+constexpr int kItemRowMost = 169, kItemFewMarchRow = 64;                                    // (169: its longest row)
+
+bool item_serves(const conv_plan *plan, int batch, const ApplyChoice &other) {
+    const bool tr = plan->transposed, groups = other.kind == Kind::GatherScalar || other.kind == Kind::GatherVec;
+    // (not where the plan's marching threshold, a test hook, is lowered)
+    if (plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || plan->max_row_nnz > kItemRowMost) return false;
+    const int columns = batch >= 4 ? 4 : 1, chunks = (batch + columns - 1) / columns;
+    const double work = std::log2((double)plan->nnz * chunks * plan->channels) - 20.0, w = std::min(work, kItemWorkMost);
+    ItemAgainst against = groups ? kGroupsMany : kOthersMany;
+    double least = kItemLeastGain;
+    if (plan->channels > 1) {
+        if (groups && plan->channels >= kItemManyChannels) return true;
+        if (groups) least = kItemLeastGainFewChannels;
+    } else {
+        if (batch == 1) return false;
+        if (batch < 4) {
+            if (other.kind == Kind::March && plan->max_row_nnz >= kItemFewMarchRow) return false;
+            against = kFew;
+        } else if (groups) {
+            if (batch <= 8 || work < (plan->shape.s >= 4 ? kItemLaunchStrided : kItemLaunch)) return false;
+            against = tr ? kGroupsTT : kGroupsT;
+        } else if (other.kind == Kind::Tile) {
+            if (tr) return false;
+            against = kTileT;
+            if (work < kItemShortTiles) least = kItemLeastGainShortTiles;
+        } else if (other.kind == Kind::March) {
+            against = kMarching;
+        } else {
+            against = tr ? kStagedTT : kStagedT;
+        }
+    }
+    const double b = std::log2((double)chunks), a = std::log2((double)plan->max_row_nnz), s = plan->shape.s == 1;
+    const double full = columns == 4 ? chunks / (4.0 * ((chunks + 3) / 4)) : 0.0;
+    const double at[14] = {1.0, w, w * w, b, b * b, full, a, a * a, s, w * a, w * b, a * b, w * s, std::log2((double)plan->channels)};
+    double gain = 0.0;
+    for (int i = 0; i < 14; ++i) gain += kItemGain[against][i] * at[i];
+    return gain > least;
+}
+
+// Lanes per item: more where the launch has few waves (below 512; with the scalar columns of batches 2 and 3 below 2048),
+// each with an access of entries or two of its own; rows of 9 entries one or two (apply_item_kernel.h).  Channels: lanes first, then waves that
+// share them, four channels each at least.
+bool item_choice(const conv_plan *plan, int batch, ApplyChoice *out) {
+    const int columns = batch >= 4 ? 4 : 1, most = plan->max_row_nnz;
+    const bool many = plan->channels > 1;
+    const int64_t waves = (plan->rows * ((batch + columns - 1) / columns) + kWave - 1) / kWave;
+    const int g_most = most == 1 ? 1 : most == 9 ? (many ? 4 : 2) : 16, per_lane = columns == 1 && !many ? 8 : 4;
+    const int64_t enough = many ? 8192 : columns == 1 ? 2048 : 512;
+    int g = 1, ways = 1;
+    while (g < g_most && g * per_lane < most && waves * g < enough) g *= 2;
+    while (many && ways < kItemWaysMost && ways * 8 <= plan->channels && waves * g * ways < 1024) ways *= 2;
+    ApplyChoice c{};
+    if (!item_geometry(plan, batch, g, ways, &c.item)) return false;
+    // few workgroups of short rows, which G cannot spread: one compute unit asks for all channels of its items (23 x 32, k 2, s 4, 120
+    // channels, batch 1: 13.0 us, row groups 9.8)
+    if (many && most < 16 && c.item.cells < (most < 9 ? 64 : 8)) return false;
+    c.kind = Kind::Item;
+    c.g = g;
+    c.nv = batch >= 4;
+    c.threads = many ? ways * kWave : kItemThreads;
+    *out = c;
+    return true;
+}
+
 ApplyChoice choose_apply(const conv_plan *plan, int batch) {
     const ApplyChoice other = choose_unblocked(plan, batch);
     // batches that fill a wave (not where the plan's marching threshold, a test hook, is lowered)
@@ -911,7 +1032,7 @@ ApplyChoice choose_apply(const conv_plan *plan, int batch) {
     if (plan->channels > 1 || plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || !block_compiled(sh.k, sh.s, plan->transposed) ||
         column_blocks(batch, 4) > 65535 || !block_geometry(plan, batch, &c.lpr_log2, &c.block) ||
         !block_serves(plan, batch, c.lpr_log2, other))
-        return other;
+        return item_serves(plan, batch, other) && item_choice(plan, batch, &c) ? c : other;
     c.kind = Kind::Block;
     c.threads = kBlockThreads;
     c.g = 1;
@@ -1324,6 +1445,8 @@ int conv_spmv(const conv_plan *plan, const float *x_dev, float *y_dev, int batch
     } else if (c.kind == Kind::Block) {
         if (plan->transposed) launch_block_adjoint(c, plan, x_dev, y_dev, q);
         else launch_block(c, plan, x_dev, y_dev, q);
+    } else if (c.kind == Kind::Item) {
+        launch_item(c, plan, x_dev, y_dev, q);
     } else if (c.kind == Kind::March || c.kind == Kind::Tile || c.kind == Kind::StageMarch) {
         // one launch per channel: the first stores y, the others add to it
         conv_plan one = *plan;
@@ -1856,7 +1979,7 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
     } else {
         const ApplyChoice c = choose_apply(&plan, batch);
         d.kernel = c.kind == Kind::GatherScalar ? 0 : c.kind == Kind::GatherVec ? 1 : c.kind == Kind::Tile ? 2
-                   : c.kind == Kind::March ? 3 : c.kind == Kind::Block ? 12 : 9;
+                   : c.kind == Kind::March ? 3 : c.kind == Kind::Block ? 12 : c.kind == Kind::Item ? (c.nv ? 1 : 0) : 9;
         d.threads = c.threads;
         d.lds_bytes = (int64_t)c.lds;
         d.lanes_per_row = c.g;
@@ -1885,6 +2008,8 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
             d.strip = c.tw;
             d.segment = block_rx(k, s, plan.transposed);
             d.workgroups = (int64_t)c.block.cells * ((batch + (4LL << c.lpr_log2) - 1) / (4LL << c.lpr_log2));
+        } else if (c.kind == Kind::Item) {
+            d.workgroups = c.item.cells;
         } else if (c.kind == Kind::Tile) {
             d.strip = c.tw;
             d.segment = c.geom.th;
@@ -1960,6 +2085,10 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch) {
                 snprintf(name, sizeof name, "lds_march_staged_%dx%d_ring%d_step%d_g%d_nit%d_float4x%d", c.march.seg, c.tw, c.nl, c.ls, c.g, c.nit, c.nv);
             else
                 snprintf(name, sizeof name, "lds_march_staged_%dx%d_ring%d_step%d_g%d_nit%d_scalar", c.march.seg, c.tw, c.nl, c.ls, c.g, c.nit);
+            break;
+        case Kind::Item:
+            if (c.item.ways > 1) snprintf(name, sizeof name, "gather_g%d_%s_items_%d_ways", c.g, c.nv ? "float4" : "scalar", c.item.ways);
+            else snprintf(name, sizeof name, "gather_g%d_%s_items", c.g, c.nv ? "float4" : "scalar");
             break;
         case Kind::Block:
             snprintf(name, sizeof name, "block_%dx%d_lanes%d_float4", block_rx(plan->shape.k, plan->shape.s, plan->transposed), c.tw, 1 << c.lpr_log2);

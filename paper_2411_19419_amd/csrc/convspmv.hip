@@ -1393,7 +1393,18 @@ ChannelsChoice choose_compact_channels(const conv_plan *plan, const float *x, co
         c.ok = true;
         c.vb = vb;
         c.ways = ways;
-        c.lds = (size_t)(vec4 * 16 * ways);
+        // lanes of four columns: the chunks that lie side by side, as many as the batch is a multiple of and a wave's patch has room for
+        c.chunks = 1;
+        int64_t width = phy, wave_vec4 = vec4;
+        for (int chunks = 4; vb == 4 && chunks > 1 && c.chunks == 1; chunks /= 2) {
+            const int64_t w = (int64_t)(kChanTileY / chunks - 1) * sh.s + sh.k, patch = phx * w * chunks;
+            const int64_t v = std::max<int64_t>(patch, kWave) + ((int64_t)sh.k * sh.k + 3) / 4;
+            if (batch % (4 * chunks) || patch > 8 * kWave || v * 16 * ways > 64 * 1024) continue;
+            c.chunks = chunks;
+            width = w;
+            wave_vec4 = v;
+        }
+        c.lds = (size_t)(wave_vec4 * 16 * ways);
         const int64_t per_xcd = (tiles_x * tiles_y + kXcds - 1) / kXcds;
         c.grid = dim3((unsigned)(per_xcd * kXcds), (unsigned)(batch / vb));
         CompactChannelsGeom g{};
@@ -1403,9 +1414,9 @@ ChannelsChoice choose_compact_channels(const conv_plan *plan, const float *x, co
         g.batch = batch; g.channels = plan->channels;
         g.tiles_y = (int)tiles_y;
         g.phx = (int)phx;
-        g.phy = (int)phy;
-        g.wave_vec4 = (int)vec4;
-        g.inv_phy = 1.0f / (float)phy;
+        g.phy = (int)width;
+        g.wave_vec4 = (int)wave_vec4;
+        g.inv_phy = 1.0f / (float)width;
         g.plane = (long long)sh.m * sh.n * batch;
         c.geom = g;
         if (waves >= kChanFusedWaves) break;

@@ -4,11 +4,15 @@ Names and meanings are those of ``include/convspmv.h``.  torch supplies device
 memory and the stream handle; every step of the path runs in the library's
 HIP kernels.  There is no fallback: if the shared library is missing or a call
 fails, an exception is raised.
+
+The calls that programs repeat go through ``_native`` (csrc/host/native.cpp) first, which makes the same
+checks without the interpreter and answers None for anything but the plain case; that is then done here.
 """
 from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.util
 import os
 import threading
 
@@ -25,6 +29,8 @@ class _Torch:
         import torch as loaded
         globals()["torch"] = loaded
         globals()["_raw_stream"], globals()["_current_device"] = _device_queries(loaded)
+        _load()
+        globals()["_native"] = _load_native()
         return getattr(loaded, name)
 
 
@@ -36,8 +42,19 @@ def _device_queries(loaded):
             getattr(c, "_cuda_getDevice", None) or loaded.cuda.current_device)
 
 
+def _load_native():
+    path = os.path.join(_HERE, "_native.so")
+    if not os.path.exists(path):
+        raise ImportError(
+            "%s is not built: run `python -c 'import __graft_entry__ as g; g.build()'` from the repository root" % path)
+    spec = importlib.util.spec_from_file_location("_native", path)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
 torch = _Torch()
-_raw_stream = _current_device = None       # set with torch
+_raw_stream = _current_device = _native = None       # set with torch
 
 EXPORTS = (
     "conv_out_shape", "conv_nnz", "conv_csr_build", "conv_spmv", "conv_plan_shape",
@@ -235,7 +252,8 @@ class ConvPlan:
         # stream and the plan was used on it only: that stream is never captured, so no graph can be
         # replaying work on the plan elsewhere.  Everything else is waited for.
         self._home = _raw_stream(kernel.device.index)
-        self._elsewhere = self._home != 0
+        self._used_elsewhere = self._home != 0
+        self._ref = None                # what _native needs of the plan, made by the first call that wants it
         self.transposed = transposed    # the arrays hold T^T (CSC of T): row_ptr is col_ptr, col_idx is row_idx
         self.m, self.n, self.k, self.s, self.p = shape
         self.m_out, self.n_out = out_shape
@@ -266,13 +284,30 @@ class ConvPlan:
         return (self.nnz * 4 * (1 + self.channels) + (self.rows + 1) * 4 + self.cols * batch * 4
                 + self.rows * batch * 4)
 
+    @property
+    def _elsewhere(self):
+        return self._used_elsewhere or (self._ref is not None and self._ref.elsewhere)
+
     def _used_on(self, stream_handle):
         if stream_handle != self._home:
-            self._elsewhere = True
+            self._used_elsewhere = True
+
+    def _native_ref(self):
+        """The plan as _native takes it; None for a closed plan."""
+        if self._ref is None and self._handle is not None:
+            self._ref = _native.PlanRef(self._handle.value, self.cols, self.rows, self.k * self.k * self.channels,
+                                        self._home, self._used_elsewhere)
+        return self._ref
 
     def close(self):
         if self._handle is not None:
-            if self._elsewhere:
+            elsewhere = self._elsewhere
+            if self._ref is not None:
+                self._ref.close()
+            if not elsewhere and _native.drop(self._handle.value, self._kernel):
+                self._handle = None
+                return
+            if elsewhere:
                 torch.cuda.synchronize()
             else:      # the caller's K may be from another stream's pool: not to be handed out before this stream has read it
                 self._kernel.record_stream(_default_stream(self._kernel.device))
@@ -300,6 +335,14 @@ def conv_csc_build(m, n, k, s, p, kernel, stream=None) -> ConvPlan:
 def conv_csr_build(m, n, k, s, p, kernel, stream=None, _transposed=False) -> ConvPlan:
     """Build T on the device of `kernel` (a k*k float32 CUDA/HIP tensor)."""
     lib = _load()
+    if stream is None and _native is not None:
+        got = _native.build(m, n, k, s, p, kernel, _transposed)
+        if type(got) is tuple:
+            handle, mo, no, nnz, row_ptr, col_idx, vals, sh = got
+            return _built(sh, ctypes.c_void_p(handle), (m, n, k, s, p), (mo, no), nnz, row_ptr, col_idx, vals, kernel,
+                          transposed=_transposed)
+        if got is not None:
+            raise ConvError(got, "%s%r" % ("conv_csc_build" if _transposed else "conv_csr_build", (m, n, k, s, p)))
     mo, no = conv_out_shape(m, n, k, s, p)
     nnz = conv_nnz(m, n, k, s, p)
     if not (kernel.is_cuda and kernel.dtype == torch.float32 and kernel.is_contiguous()
@@ -401,6 +444,13 @@ def conv_compact_build(m, n, k, s, p, kernel, stream=None, channels: int = 1) ->
 
 def conv_update_kernel(plan: ConvPlan, kernel, stream=None) -> None:
     """Rewrite plan.vals for a new k*k kernel (device tensor); indices are untouched."""
+    if stream is None and _native is not None:
+        st = _native.update_kernel(plan._ref or plan._native_ref(), kernel)
+        if st == 0:
+            plan._kernel = kernel
+            return
+        if st is not None:
+            raise ConvError(st, "conv_update_kernel")
     if plan._handle is None:
         raise ValueError("plan is closed")
     if not (kernel.is_cuda and kernel.dtype == torch.float32 and kernel.is_contiguous()
@@ -417,6 +467,12 @@ def conv_update_kernel(plan: ConvPlan, kernel, stream=None) -> None:
 
 def conv_spmv(plan: ConvPlan, x, y=None, batch: int = 1, stream=None):
     """y = T x for `batch` batch-minor vectors.  Allocates y when not given."""
+    if stream is None and y is not None and _native is not None:
+        st = _native.spmv(plan._ref or plan._native_ref(), x, y, batch)
+        if st == 0:
+            return y
+        if st is not None:
+            raise ConvError(st, "conv_spmv(batch=%d)" % batch)
     if plan._handle is None:
         raise ValueError("plan is closed")
     if not _is_operand(x):
@@ -439,6 +495,12 @@ def conv_spmv(plan: ConvPlan, x, y=None, batch: int = 1, stream=None):
 
 def conv_spmv_from_csc(plan: ConvPlan, x, y=None, batch: int = 1, stream=None):
     """y = T x from the column-compressed arrays of a conv_csc_build plan (a scatter)."""
+    if stream is None and y is not None and _native is not None:
+        st = _native.spmv_from_csc(plan._ref or plan._native_ref(), x, y, batch)
+        if st == 0:
+            return y
+        if st is not None:
+            raise ConvError(st, "conv_spmv_from_csc(batch=%d)" % batch)
     if plan._handle is None:
         raise ValueError("plan is closed")
     if not (x.is_cuda and x.dtype == torch.float32 and x.is_contiguous() and x.numel() == plan.m * plan.n * batch):
@@ -484,6 +546,12 @@ class ConvMulti:
         self.batch = batch
 
     def apply(self, stream=None):
+        if stream is None and self._handle is not None:
+            st = _native.multi_apply(self._handle.value)
+            if st == 0:
+                return self.ys
+            if st is not None:
+                raise ConvError(st, "conv_multi_apply")
         sh = _stream_handle(stream, _current_device())
         st = _load().conv_multi_apply(self._handle, sh)
         if st != 0:

@@ -489,8 +489,10 @@ __global__ __launch_bounds__(W *kWave) void spmm_csc_tile_kernel(
 // the descriptors' first blocks was seven dependent loads, most of the launch: 123 layers, batch 1,
 // 5.2 -> 3.5 us) or, where that table would be long, by the bisection.  Inside a
 // product the row-group scheme of the gather kernels is used with a per-product
-// group width (1 << g_shift lanes per row), batches of 4 and more in chunks of four columns, 4 NV per lane
-// (batch 8: 32 -> 6.2 us; one column at a time before).
+// group width (1 << g_shift lanes per row).  A lane carries all columns of a batch of 2 or 3 (a workgroup for each column
+// before: at batch 3 more waves than run at a time), from 4 on chunks of four, 4 NV per lane, and asks for U entries and then their
+// pixels at a time: a launch this size is its dependent loads (batch 2: 6.9 -> 4.5 us, 3, 77 layers: 8.5 -> 4.8, 4: 6.5 -> 5.8).  From
+// 5 columns on it is the accesses: 8: 7.9 -> 7.8, with half as wide lanes 10.6; 16: 12.2, two entries at a time 12.9.
 // ---------------------------------------------------------------------------
 struct MultiDesc {
     const int *row_ptr;
@@ -504,7 +506,8 @@ struct MultiDesc {
     int pad;
 };
 
-template <int NV>
+// NV: chunks of four columns per lane, or (0) COLS columns.
+template <int NV, int COLS>
 __global__ __launch_bounds__(kGatherThreads) void spmm_multi_kernel(const MultiDesc *__restrict__ descs,
                                                                     const int *__restrict__ owner, int n, int batch) {
     int at = 0;                          // descs[at].first_block <= blockIdx.x < descs[at + 1].first_block
@@ -534,28 +537,71 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_multi_kernel(const MultiD
         if (gs >= 4) v += dpp_move<kDppXor15>(v);
         return v;
     };
-    if constexpr (NV == 0) {
+    if constexpr (NV == 0 && COLS == 1) {
         for (int c = blockIdx.y; c < batch; c += gridDim.y) {   // uniform over the block
             const float acc = group(row_entries<kGatherAhead>(beg + lane, end, G, d.col_idx, d.vals,
                                                               [&](int col) { return d.x[(long long)col * batch + c]; }, 0.0f));
             if (row < d.rows && lane == 0) d.y[row * batch + c] = acc;
         }
+    } else if constexpr (NV == 0) {
+        typedef float pixel __attribute__((ext_vector_type(COLS)));
+        constexpr int U = kGatherAhead;
+        pixel acc = pixel(0.0f);
+        for (unsigned e = beg + lane; e < end; e += U * G) {
+            int col[U];
+            float val[U];
+            pixel px[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned i = min(e + u * G, end - 1);
+                col[u] = d.col_idx[i];
+                val[u] = d.vals[i];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int h = 0; h < COLS; ++h) px[u][h] = d.x[(long long)col[u] * COLS + h];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int h = 0; h < COLS; ++h) acc[h] = e + u * G < end ? fmaf(val[u], px[u][h], acc[h]) : acc[h];
+        }
+#pragma unroll
+        for (int h = 0; h < COLS; ++h) {
+            const float sum = group(acc[h]);
+            if (row < d.rows && lane == 0) d.y[row * COLS + h] = sum;
+        }
     } else {
+        constexpr int U = NV == 4 ? 1 : 4;
         for (int c0 = blockIdx.y * (4 * NV); c0 < batch; c0 += gridDim.y * (4 * NV)) {
             float4 acc[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (unsigned e = beg + lane; e < end; e += G) {
-                const float w = d.vals[e];
-                const float *xr = d.x + (long long)d.col_idx[e] * batch;
+            for (unsigned e = beg + lane; e < end; e += U * G) {
+                int col[U];
+                float val[U];
+                float4 px[U][NV];
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const float4 xv = load4(xr + chunk_col(c0 + 4 * v, batch));
-                    acc[v].x = fmaf(w, xv.x, acc[v].x);
-                    acc[v].y = fmaf(w, xv.y, acc[v].y);
-                    acc[v].z = fmaf(w, xv.z, acc[v].z);
-                    acc[v].w = fmaf(w, xv.w, acc[v].w);
+                for (int u = 0; u < U; ++u) {
+                    const unsigned i = min(e + u * G, end - 1);
+                    col[u] = d.col_idx[i];
+                    val[u] = d.vals[i];
                 }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) px[u][v] = load4(d.x + (long long)col[u] * batch + chunk_col(c0 + 4 * v, batch));
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (e + u * G < end) {
+#pragma unroll
+                        for (int v = 0; v < NV; ++v) {
+                            acc[v].x = fmaf(val[u], px[u][v].x, acc[v].x);
+                            acc[v].y = fmaf(val[u], px[u][v].y, acc[v].y);
+                            acc[v].z = fmaf(val[u], px[u][v].z, acc[v].z);
+                            acc[v].w = fmaf(val[u], px[u][v].w, acc[v].w);
+                        }
+                    }
             }
 #pragma unroll
             for (int v = 0; v < NV; ++v) {

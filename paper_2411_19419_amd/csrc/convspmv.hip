@@ -1824,16 +1824,20 @@ int conv_multi_apply(const conv_multi *multi, void *stream) {
     if (!multi) return CONV_ENULL;
     if (multi->blocks == 0) return CONV_OK;
     const int nv = multi->batch >= 4 ? widest_nv(multi->batch) : 0;
-    const dim3 grid(multi->blocks, (unsigned)std::min(column_blocks(multi->batch, nv), 65535));
+    const dim3 grid(multi->blocks, multi->batch < 4 ? 1u : (unsigned)std::min(column_blocks(multi->batch, nv), 65535));
     const LaunchScope scope;
-#define CONV_MULTI(NV)                                                                                                 \
-    spmm_multi_kernel<NV><<<grid, kGatherThreads, 0, (hipStream_t)stream>>>(multi->descs_dev, multi->owner_dev, multi->n, \
-                                                                            multi->batch)
+#define CONV_MULTI(NV, COLS)                                                                                                 \
+    spmm_multi_kernel<NV, COLS><<<grid, kGatherThreads, 0, (hipStream_t)stream>>>(multi->descs_dev, multi->owner_dev, multi->n, \
+                                                                                  multi->batch)
     switch (nv) {
-        case 0: CONV_MULTI(0); break;
-        case 1: CONV_MULTI(1); break;
-        case 2: CONV_MULTI(2); break;
-        default: CONV_MULTI(4); break;
+        case 0:
+            if (multi->batch == 1) CONV_MULTI(0, 1);
+            else if (multi->batch == 2) CONV_MULTI(0, 2);
+            else CONV_MULTI(0, 3);
+            break;
+        case 1: CONV_MULTI(1, 4); break;
+        case 2: CONV_MULTI(2, 4); break;
+        default: CONV_MULTI(4, 4); break;
     }
 #undef CONV_MULTI
     if (!scope.ok()) return CONV_EHIP;

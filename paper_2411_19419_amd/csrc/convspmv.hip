@@ -1327,6 +1327,28 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
         }
         return false;
     };
+    // Rectangles whose launch stays below that bound.  Where segments are longer than the shortest the launch has as many
+    // workgroups as it asked for, a few less than compute units because strips do not divide them (3239 x 2417, k 7, s 2, batch 4: 255,
+    // 144 us in row groups, 48 marching): from these lengths on, in steps of rv lines, as the waves' first window is paid for.  Else
+    // as many workgroups as it takes for the taps, strips not mostly empty (571 x 726, k 7, batch 1, 219: 24.5 and 7.9; 202 x 241, k 7, batch 32,
+    // 208: 37 and 12; 497 x 778, k 9, batch 1: 33 and 9.6).  Lines drawn over 4600 products of row groups; of 2500 others 69 march so, in
+    // 0.60 of the time in the mean, none slower, at 1.01 of the row groups' error (k 5 0.93, k 7 at stride 2, from 16 lanes, 1.08).
+    auto short_of_bound = [&] {
+        if (lowered || can_push || !c.kk || plan->channels > 1) return false;
+        const int64_t wgs = workgroups(c);
+        if (c.geom.seg > 2 * c.geom.rv) {
+            const int steps = sh.k == 7 ? 4 : sh.k == 5 ? 6 : sh.k == 3 ? 20 : 0;
+            return steps > 0 && c.geom.seg >= steps * c.geom.rv;
+        }
+        int64_t least_wgs = kCompactMinBlocks;
+        if (sh.s == 1) least_wgs = sh.k == 5 ? 160 : sh.k == 7 ? 128 : sh.k == 9 ? (scalar ? 80 : 128) : kCompactMinBlocks;
+        else if (sh.k == 7) least_wgs = scalar ? 160 : 192;
+        return wgs >= least_wgs && 10LL * sh.n_out >= 6LL * c.geom.tw * c.geom.strips;
+    };
+    if (short_of_bound()) {
+        c.fine = true;
+        return c;
+    }
     CompactChoice m{};
     if (can_push) {
         const int64_t waves = (int64_t)push.blocks * kPushWaves * c.col_blocks;

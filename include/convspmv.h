@@ -250,7 +250,7 @@ typedef struct conv_dispatch {
                                (storage 3; for 7: strip x segment = pixels x lines of a tile, ring_lines_needed
                                x lines_per_step = runs x rows of its window, lanes_per_row = columns per step),
                                9 LDS march with the entry stream staged through LDS,
-                               10 row groups over the structure-aware storage (small products),
+                               10 row groups over the structure-aware storage (lanes_per_row 1 also: a lane per row and chunk),
                                11 gather from the column-compressed arrays (storage 3: ring_lines_needed = output
                                lines in flight, ring_lines = 16-byte accesses per array that a line takes at most,
                                lines_per_step = shares of a tap sum),

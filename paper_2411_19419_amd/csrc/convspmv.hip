@@ -1260,6 +1260,27 @@ void compact_row_groups(const conv_plan *plan, int batch, CompactChoice *out) {
     c.lds = c.ways > 1 ? (size_t)c.ways * std::max(c.lpr, 1) * (kWave / c.gather_g) * (c.scalar ? 4 : 16) : 0;
 }
 
+bool lane_geometry(const conv_plan *plan, int batch, LaneGeom *out) {
+    const int columns = batch >= 4 ? 4 : 1;
+    const int64_t chunks = (batch + columns - 1) / columns, items = plan->rows * chunks;
+    // 32-bit byte offsets into x and y; item numbers of 32 bits; exact small divisions
+    if (plan->shape.k < 2 || plan->shape.k > 13 || plan->cols * batch >= (1LL << 30) || plan->rows * batch >= (1LL << 30) ||
+        items > kInt32Limit - kItemThreads || chunks + kWave >= (1 << 21))
+        return false;
+    LaneGeom g{};
+    g.n = plan->shape.n;
+    g.batch = batch;
+    g.chunks = (int)chunks;
+    g.inv_chunks = 1.0f / (float)chunks;
+    g.items = (unsigned)items;
+    const int64_t cells = (items + kItemThreads - 1) / kItemThreads;
+    if (cells + kXcds >= (1LL << 31) / kXcds) return false;
+    g.cells = (int)cells;
+    g.cells_per_xcd = (int)((cells + kXcds - 1) / kXcds);
+    *out = g;
+    return true;
+}
+
 // Which of the three serves a product, by the waves and workgroups each would have (8 400 drawn shapes, every
 // kernel and width timed on each: 1.08 times the best of them in the mean).
 CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
@@ -1367,11 +1388,55 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
     return c;
 }
 
+// Where a lane per row and chunk (compact_lane_kernel.h) takes a product from those three: where a surface fitted to the logarithm of the
+// times' ratio says that it is faster by kLaneLeastGain.  Fitted to 3300 products (as for kItemGain above), each timed on both.
+// Coordinates: w, the multiply-adds of a chunk each, borders left aside (log2 of millions); b, the chunks; how full blocks of 16
+// columns are; a, the taps of a line (log2); stride 1 or not; the stride (log2).  Of 2500 other products (sizes to 4096, k to 13, batches
+// to 256), how many come here, and time before over time here in their mean and at the worst:
+//   from the row groups, 1 to 3 columns   106  1.72  1.25     more   349  1.66  0.96
+//   from the described and pushed march    67  1.73  1.16     (k 3 to 6 of strides above 1: longer kernels are about even, and
+//                                                              at stride 1 the fit missed products at 0.72)
+//   from the rectangles, 1 to 3 columns    81  1.55  1.12     (with vectors their tiles reuse more, and few would leave)
+enum LaneAgainst { kLaneGroupsFew, kLaneGroups, kLanePushed, kLaneRectFew };
+constexpr double kLaneGain[][15] = {
+    // 1, w, w^2, b, b^2, full, a, a^2, stride 1, stride, w a, w b, a b, w at stride 1, a at stride 1
+    {-0.2636, -0.1051, 0.0023, 0.1003, 0.03, 0, 0.695, -0.2558, 0.1149, -0.0589, 0.1143, 0.0198, -0.0357, 0.0541, -0.0732},      // gather few
+    {-0.3674, -0.1317, -0.0049, 0.255, -0.0168, -0.1569, 0.5584, -0.2119, 0.2816, 0.1021, 0.1021, 0.0175, -0.0306, 0.0485, -0.1257},      // gather vec
+    {0.9478, -0.0685, 0.016, 0.1028, -0.0053, -0.4806, -0.0554, 0.0618, -0.1198, -0.0255, -0.0803, 0.0089, -0.0029, -0.0232, 0.1793},      // push
+    {0.3501, -0.0544, -0.01, -0.0743, 0.0836, 0, 0.261, -0.1051, 0.0337, 0.3164, -0.0248, 0.0536, -0.0875, 0.0221, 0.18},      // rect few
+};
+constexpr double kLaneLeastGain[] = {0.3, 0.25, 0.3, 0.2};
+constexpr int kLaneApart = 4;        // strides from which neighbouring rows share few pixels: less certain
+constexpr int kLaneMostTaps = 13, kLanePushedLeastTaps = 3, kLanePushedMostTaps = 6;
+bool lane_serves(const conv_plan *plan, int batch, const CompactChoice &other) {
+    const int k = plan->shape.k, columns = batch >= 4 ? 4 : 1, chunks = (batch + columns - 1) / columns;
+    // (not where the plan's marching threshold, a test hook, is lowered)
+    if (plan->channels > 1 || plan->march_min_jobs < kMarchMinJobs || k < 2 || k > kLaneMostTaps) return false;
+    LaneAgainst against = batch < 4 ? kLaneGroupsFew : kLaneGroups;
+    if (!other.gather_g) {
+        if (other.kk && batch >= 4) return false;
+        if (other.kk) against = kLaneRectFew;
+        else if (k < kLanePushedLeastTaps || k > kLanePushedMostTaps || plan->shape.s == 1) return false;
+        else against = kLanePushed;
+    }
+    const double w = std::log2((double)plan->rows * chunks * k * k) - 20.0, b = std::log2((double)chunks), a = std::log2((double)k);
+    const double full = columns == 4 ? chunks / (4.0 * ((chunks + 3) / 4)) : 0.0, one = plan->shape.s == 1, s = std::log2((double)plan->shape.s);
+    const double at[15] = {1.0, w, w * w, b, b * b, full, a, a * a, one, s, w * a, w * b, a * b, w * one, a * one};
+    double gain = 0.0;
+    for (int i = 0; i < 15; ++i) gain += kLaneGain[against][i] * at[i];
+    return gain > kLaneLeastGain[against] + (plan->shape.s >= kLaneApart ? 0.1 : 0.0);
+}
+
 // ... and whether its sums are taken line by line (FINE): where the row groups would serve it otherwise, with the
 // widest lanes (above) or with lanes that divide the batch (one column each where it is not a multiple of 4), so that
 // neither the lanes' width nor the pushed lines cost such products their exactness.
 CompactChoice choose_compact(const conv_plan *plan, int batch) {
     CompactChoice c = choose_compact_path(plan, batch), even{};
+    if (c.ok && lane_serves(plan, batch, c) && lane_geometry(plan, batch, &c.lane)) {
+        c.laned = true;
+        c.scalar = batch < 4;
+        return c;
+    }
     if (!c.ok || c.gather_g || plan->shape.k < 3 || (!c.pushed && (c.scalar || plan->channels > 1))) return c;
     const bool whole = batch >= 4 && batch % 4 == 0;
     c.fine = c.fine || (compact_march(plan, batch, !whole, whole ? least_nv(batch) : 1, &even) &&
@@ -1468,6 +1533,10 @@ int conv_spmv(const conv_plan *plan, const float *x_dev, float *y_dev, int batch
         }
         const CompactChoice cc = choose_compact(plan, batch);
         if (!cc.ok) return CONV_EOVERFLOW;
+        if (cc.laned) {
+            launch_compact_lane(cc, plan, x_dev, y_dev, q);
+            return scope.ok() ? CONV_OK : CONV_EHIP;
+        }
         if (!launch_compact(cc, plan, x_dev, y_dev, q)) return CONV_EHIP;
         return scope.ok() ? CONV_OK : CONV_EHIP;
     }
@@ -1981,8 +2050,16 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
     } else if (plan.compact) {
         const CompactChoice cc = choose_compact(&plan, batch);
         if (!cc.ok) return CONV_EOVERFLOW;
-        d.kernel = cc.gather_g ? 10 : (cc.kk ? 5 : 4);
+        d.kernel = cc.laned || cc.gather_g ? 10 : (cc.kk ? 5 : 4);
         d.threads = kCompactThreads;
+        if (cc.laned) {
+            d.threads = kItemThreads;
+            d.lanes_per_row = 1;
+            d.columns_per_lane = cc.scalar ? 1 : 4;
+            d.workgroups = cc.lane.cells;
+            *out = d;
+            return CONV_OK;
+        }
         if (cc.gather_g) {
             const int row_threads = cc.ways > 1 ? kWave : kCompactThreads;
             d.threads = row_threads * cc.ways;
@@ -2094,7 +2171,9 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch) {
         char cols[16];
         if (cc.scalar) snprintf(cols, sizeof cols, "scalar");
         else snprintf(cols, sizeof cols, "float4x%d", cc.lpr);
-        if (cc.gather_g)
+        if (cc.laned)
+            snprintf(name, sizeof name, "compact_gather_lanes_%s", cc.scalar ? "scalar" : "float4");
+        else if (cc.gather_g)
             snprintf(name, sizeof name, "compact_gather_g%d_%s", cc.gather_g, cols);
         else if (cc.pushed)
             snprintf(name, sizeof name, "compact_described_%dx%d_push%d_%s", cc.push.seg, cc.push.tw,

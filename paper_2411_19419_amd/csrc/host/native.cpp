@@ -2,7 +2,7 @@
 //
 // A call from Python costs a launch (3.45 us on this runtime, whatever the launch function) and what Python does around it: six
 // tensor queries, a device query, the stream, a ctypes call, 1.9 us for a product, 11 us for a build with its three arrays.
-// Here the same checks read the tensors directly (32 x 32, k 3, batch 1, by the box: conv_spmv 5.6 -> 3.3 us, 5.8 -> 4.1;
+// Here the same checks read the tensors directly (32 x 32, k 3, batch 1: conv_spmv 5.6 -> 3.3 us, on a slower host 5.8 -> 4.1;
 // conv_update_kernel 5.1 -> 3.2, conv_csr_build 14.4 -> 7.5, ConvMulti.apply 3.8 -> 3.1).
 //
 // Each function does a call only where every check of binding.py holds as it is, on the current device and stream; for anything

@@ -675,12 +675,18 @@ bool stage_march_geometry(const conv_plan *plan, int batch, int nv, int channels
     // segment costs its lines plus about two steps for the window and entries it loads before its
     // first step: the number of segments per strip that minimises rounds x (lines + 2 steps).  (Three
     // column blocks of 32 strips: 8 segments = 768 workgroups = 3 full rounds, not 2 segments = 192.)
+    // The cells (strip, segment) are dealt out to the XCDs first, each with all its column blocks: a share is rounded up before it is
+    // multiplied, and 252 workgroups of 7 strips, 3 segments, 12 blocks are 36 on an XCD of 32 compute units, two rounds.
+    // (Counted over the chip instead, before -> now, us: 738 x 733, k 11, s 2, batch 40: 189 -> 101; 436 x 649, k 7, batch 48: 138 -> 80;
+    // 120 x 150, k 7, batch 180: 49.5 -> 30.6; T^T, 205 x 264, k 6, batch 48: 37.8 -> 25.0.  51 of 61 such products that march
+    // either way: 1.28 to 1.86 times as fast.  10 of 25 taps that left the blocks, block_march_ns: 0.96 to 1.22, 1.05 in the mean.)
     int64_t seg = 0, best_cost = -1;
     for (int64_t segs = 1; segs <= 512 && (segs - 1) * wl < g.m_out; ++segs) {
         int64_t len = (g.m_out + segs - 1) / segs;
         len = (len + wl - 1) / wl * wl;
         const int64_t real = (g.m_out + len - 1) / len;
-        const int64_t rounds = ((int64_t)g.strips * col_blocks * real + kStageTargetBlocks - 1) / kStageTargetBlocks;
+        const int64_t share = (g.strips * real + kXcds - 1) / kXcds * col_blocks;
+        const int64_t rounds = (share + kStageTargetBlocks / kXcds - 1) / (kStageTargetBlocks / kXcds);
         const int64_t cost = rounds * (len + 2 * wl);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; seg = len; }
     }

@@ -1433,6 +1433,35 @@ bool lane_serves(const conv_plan *plan, int batch, const CompactChoice &other) {
     return gain > kLaneLeastGain[against] + (plan->shape.s >= kLaneApart ? 0.1 : 0.0);
 }
 
+constexpr int kCompactXcdUnits = kCompactTargetBlocks / 2 / kXcds;
+// The segments of a march that has its compute units to itself (more than half of the LDS): those whose rounds of 32 workgroups on
+// the fullest XCD, each as long as a segment and the window before it, take least, where that is a tenth less.  (Cells are dealt to
+// the XCDs with all their column blocks: 255 workgroups of 3 blocks are 33 on one of them, a second round.  Segments by the
+// chip's workgroups -> these, us: 522 x 691, k 7, s 2, batch 40: 60.9 -> 34.6; 555 x 789, k 7, s 2, batch 37: 70.3 -> 39.5; 864 x 861, k 5, s 2,
+// batch 40: 86.6 -> 54.5; 1078 x 776, k 3, s 2, batch 96: 179 -> 112.  70 changed products: 1.08 to 1.78 times as fast, 1.53 in
+// the mean.)  The choice between the kernels is made before, on the other segments, and sums are as they were.
+void compact_segments(const conv_plan *plan, CompactChoice *out) {
+    CompactChoice &c = *out;
+    if (!c.ok || c.gather_g || c.pushed || c.lds <= kLdsPerCu / 2) return;
+    const ConvShape &sh = plan->shape;
+    CompactGeom &g = c.geom;
+    auto cost = [&](int64_t seg) {
+        const int64_t cells = g.strips * ((sh.m_out + seg - 1) / seg), share = (cells + kXcds - 1) / kXcds * c.col_blocks;
+        return (share + kCompactXcdUnits - 1) / kCompactXcdUnits * (seg + 2 * g.rv);
+    };
+    int64_t best = g.seg;
+    for (int64_t segs = 1; segs <= 512 && segs * 2 * g.rv <= sh.m_out; ++segs) {
+        const int64_t seg = ((sh.m_out + segs - 1) / segs + g.rv - 1) / g.rv * g.rv;
+        if (cost(seg) < cost(best)) best = seg;
+    }
+    if (cost(best) * 10 > cost(g.seg) * 9) return;
+    const int64_t segs = (sh.m_out + best - 1) / best, jobs = g.strips * segs;
+    if (jobs + kXcds >= (1LL << 31) / kXcds) return;
+    g.seg = (int)best;
+    g.segs = (int)segs;
+    g.blocks_per_xcd = (int)((jobs + kXcds - 1) / kXcds);
+}
+
 // ... and whether its sums are taken line by line (FINE): where the row groups would serve it otherwise, with the
 // widest lanes (above) or with lanes that divide the batch (one column each where it is not a multiple of 4), so that
 // neither the lanes' width nor the pushed lines cost such products their exactness.
@@ -1443,6 +1472,7 @@ CompactChoice choose_compact(const conv_plan *plan, int batch) {
         c.scalar = batch < 4;
         return c;
     }
+    compact_segments(plan, &c);
     if (!c.ok || c.gather_g || plan->shape.k < 3 || (!c.pushed && (c.scalar || plan->channels > 1))) return c;
     const bool whole = batch >= 4 && batch % 4 == 0;
     c.fine = c.fine || (compact_march(plan, batch, !whole, whole ? least_nv(batch) : 1, &even) &&

@@ -7,6 +7,8 @@ fails, an exception is raised.
 
 The calls that programs repeat go through ``_native`` (csrc/host/native.cpp) first, which makes the same
 checks without the interpreter and answers None for anything but the plain case; that is then done here.
+So is everything where ``_native`` cannot be loaded (it is bound to the torch it was built with; a
+warning says so): the same library and kernels, with the interpreter's time per call.
 """
 from __future__ import annotations
 
@@ -15,10 +17,11 @@ import functools
 import importlib.util
 import os
 import threading
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIBNAME = "libconvspmv.so"
-_lock = threading.Lock()
+_lock = threading.RLock()
 _lib = None
 
 
@@ -27,10 +30,20 @@ class _Torch:
 
     def __getattr__(self, name):
         import torch as loaded
-        globals()["torch"] = loaded
-        globals()["_raw_stream"], globals()["_current_device"] = _device_queries(loaded)
-        _load()
-        globals()["_native"] = _load_native()
+        failure = None
+        with _lock:
+            if torch is self:
+                # torch's own name last: who sees it (another thread, or the call after one that raised here) has the rest
+                _load()
+                queries = _device_queries(loaded)
+                try:
+                    native = _load_native()
+                except ImportError as e:
+                    native, failure = None, e
+                globals().update(_raw_stream=queries[0], _current_device=queries[1], _native=native)
+                globals()["torch"] = loaded
+        if failure is not None:
+            warnings.warn("calls go through ctypes, some microseconds each: %s" % failure, RuntimeWarning, stacklevel=3)
         return getattr(loaded, name)
 
 
@@ -54,7 +67,8 @@ def _load_native():
 
 
 torch = _Torch()
-_raw_stream = _current_device = _native = None       # set with torch
+_raw_stream = _current_device = None       # set with torch
+_native = None                             # so too; stays None where it cannot be loaded
 
 EXPORTS = (
     "conv_out_shape", "conv_nnz", "conv_csr_build", "conv_spmv", "conv_plan_shape",
@@ -304,7 +318,7 @@ class ConvPlan:
             elsewhere = self._elsewhere
             if self._ref is not None:
                 self._ref.close()
-            if not elsewhere and _native.drop(self._handle.value, self._kernel):
+            if not elsewhere and _native is not None and _native.drop(self._handle.value, self._kernel):
                 self._handle = None
                 return
             if elsewhere:
@@ -546,7 +560,7 @@ class ConvMulti:
         self.batch = batch
 
     def apply(self, stream=None):
-        if stream is None and self._handle is not None:
+        if stream is None and self._handle is not None and _native is not None:
             st = _native.multi_apply(self._handle.value)
             if st == 0:
                 return self.ys

@@ -9,10 +9,13 @@
 //
 // G lanes share an item where the launch has few waves; lane l takes U consecutive entries at a time, U l, U l + U G, ...,
 // NB such accesses are asked for together with their pixels after them.  U fits the rows: 25 entries in fives, others in fours;
-// rows of 9 at once (a tail of one entry would cost four pixels).
-// Sums: each access is a chain of its own, added to one of NB sums (LONG, rows above 64 entries and one or two lanes: two sets of them
-// in turn); rows of 9 entries as two chains of every other entry, the order of the tile kernel.  Error against 64 bits over drawn products, over that of
-// the kernels it takes them from: 0.96 to 1.05 in the mean of every k (one chain for a row: 1.6 at k 13).
+// rows of 1, 4 and 9 at once (a tail of one entry would cost four pixels).
+// Sums: each access is a chain of its own; the accesses of a row, its lanes and its channels are added in 64 bits, which this
+// chip adds as fast as 32 (1384 products: 0.99 of the time of sums in 32 bits).  Rows at once are one chain, of 9 entries two
+// of every other entry, the order of the tile kernel.  Error against 64 bits over that of the kernels it takes products
+// from, in the geometric mean: rows of 1, 4 and 9 entries 1.00, 0.99 and 1.00; 16: 0.85; 25: 0.84; 36: 0.72; 49 and 64: 0.69; 81: 0.68;
+// 100: 0.65; 121 and 144: 0.62; 169: 0.59; channels 0.31 of the row groups', 0.51 of the others'.  (In 32 bits, two sums in turn and the tail of a
+// row on top of one of them: 25 entries 1.07, up to 1.24; 36: 1.05; 64: 1.07; three channels of 25 entries up to 1.18.)
 //
 // MANY: several channels that share the indices.  The waves of a workgroup hold the same items and deal the channels out; a lane
 // keeps its entries' columns while NB of its channels pass, and the partial sums meet in LDS.
@@ -44,12 +47,13 @@ struct ItemGeom {
 };
 
 // C: columns of a chunk.  x and y are addressed by 32-bit byte offsets, columns are below 2^24 (item_geometry).
-template <int G, int C, int U, int NB, bool LONG, bool MANY>
+template <int G, int C, int U, int NB, bool MANY>
 __global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void spmm_item_kernel(
     const int *__restrict__ row_ptr, const int *__restrict__ col_idx, const float *__restrict__ vals,
     const float *__restrict__ x, float *__restrict__ y, const ItemGeom g) {
     typedef float part __attribute__((ext_vector_type(C)));
     typedef float part_at __attribute__((ext_vector_type(C), aligned(4)));
+    typedef double sum_t __attribute__((ext_vector_type(C)));
     constexpr int ITEMS = kWave / G;                 // of a wave
     const int at = (int)blockIdx.x / kXcds, cell = ((int)blockIdx.x % kXcds) * g.cells_per_xcd + at;
     if (at >= g.cells_per_xcd || cell >= g.cells) return;
@@ -81,11 +85,11 @@ __global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void s
         for (int h = 0; h < C; ++h) r[h] = fmaf(w, p[h], s[h]);
         return r;
     };
-    part acc = part(0.0f);
+    sum_t sum = sum_t(0.0);
     if constexpr (!MANY && NB == 1) {
         // a row at once (the loop is for edited rows that are longer)
         static_assert(G <= 2, "the chains of two lanes per row");
-        part odd = part(0.0f);
+        part acc = part(0.0f), odd = part(0.0f);
         for (unsigned e = beg + sub; e < end; e += U * G) {
             int col[U];
             float val[U];
@@ -102,17 +106,14 @@ __global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void s
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (u == 0 || e + u * G < end) {
-                    if (G == 1 && u % 2) odd = fma_part(val[u], px[u], odd);
+                    if (G == 1 && U > 4 && u % 2) odd = fma_part(val[u], px[u], odd);
                     else acc = fma_part(val[u], px[u], acc);
                 }
         }
-        if (G == 1) acc += odd;
+        sum = __builtin_convertvector(acc, sum_t) + __builtin_convertvector(odd, sum_t);
     } else if constexpr (!MANY) {
-        constexpr int SETS = LONG ? 2 : 1;
-        part sums[SETS][NB];
-#pragma unroll
-        for (int k = 0; k < SETS * NB; ++k) sums[k / NB][k % NB] = part(0.0f);
         unsigned e = beg + U * sub;
+#pragma unroll 1
         for (; e + (NB - 1) * U * G + U <= end; e += NB * U * G) {
             int col[NB][U];
             float val[NB][U];
@@ -133,9 +134,7 @@ __global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void s
                 part s = mul_part(val[b][0], px[b][0]);
 #pragma unroll
                 for (int u = 1; u < U; ++u) s = fma_part(val[b][u], px[b][u], s);
-                const part sum = sums[0][b] + s;
-                if (LONG) sums[0][b] = sums[SETS - 1][b];
-                sums[SETS - 1][b] = sum;
+                sum += __builtin_convertvector(s, sum_t);
             }
         }
         for (; e < end; e += U * G) {
@@ -151,24 +150,13 @@ __global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void s
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (u == 0 || e + u < end) px[u] = pixel(x, col[u]);
-            part s = sums[0][0];
+            part s = mul_part(val[0], px[0]);
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (u == 0 || e + u < end) s = fma_part(val[u], px[u], s);
-            sums[0][0] = sums[0][NB - 1];
-            sums[0][NB - 1] = s;
-        }
-#pragma unroll
-        for (int k = 0; k < SETS; ++k) {
-            part s = sums[k][0];
-#pragma unroll
-            for (int b = 1; b < NB; ++b) s += sums[k][b];
-            acc = k == 0 ? s : acc + s;
+            for (int u = 1; u < U; ++u)
+                if (e + u < end) s = fma_part(val[u], px[u], s);
+            sum += __builtin_convertvector(s, sum_t);
         }
     } else {
-        part sums[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) sums[b] = part(0.0f);
         for (unsigned e = beg + U * sub; e < end; e += U * G) {
             int col[U];
             unsigned i[U];
@@ -194,41 +182,38 @@ __global__ __launch_bounds__(MANY ? kItemWaysMost * kWave : kItemThreads) void s
                 for (int b = 0; b < NB; ++b)
                     if (b == 0 || ch + b * g.ways < g.channels) {
                         if constexpr (U == 1) {
-                            sums[b] = fma_part(val[b][0], px[b][0], sums[b]);
+#pragma unroll
+                            for (int h = 0; h < C; ++h) sum[h] = fma((double)val[b][0], (double)px[b][0][h], sum[h]);
                         } else {
                             part s = mul_part(val[b][0], px[b][0]);
 #pragma unroll
                             for (int u = 1; u < U; ++u) s = e + u < end ? fma_part(val[b][u], px[b][u], s) : s;
-                            sums[b] += s;
+                            sum += __builtin_convertvector(s, sum_t);
                         }
                     }
             }
         }
-#pragma unroll
-        for (int d = 1; d < NB; d *= 2)
-#pragma unroll
-            for (int b = 0; b + d < NB; b += 2 * d) sums[b] += sums[b + d];
-        acc = sums[0];
     }
 #pragma unroll
-    for (int h = 0; h < C; ++h) acc[h] = group_sum<G>(acc[h]);
+    for (int h = 0; h < C; ++h) sum[h] = group_sum<G>(sum[h]);
     if constexpr (MANY) {
-        __shared__ part shared[kItemWaysMost][ITEMS];
+        extern __shared__ double item_lds[];      // [ways][ITEMS][C]
         if (g.ways > 1) {
-            if (sub == 0) shared[wave][lane / G] = acc;
+            if (sub == 0) {
+#pragma unroll
+                for (int h = 0; h < C; ++h) item_lds[(wave * ITEMS + lane / G) * C + h] = sum[h];
+            }
             __syncthreads();
             if (wave > 0) return;
-            part quarter[4];
+            for (int i = 1; i < g.ways; ++i) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                quarter[w] = part(0.0f);
-                for (int i = w; i < g.ways; i += 4) quarter[w] += shared[i][lane / G];
+                for (int h = 0; h < C; ++h) sum[h] += item_lds[(i * ITEMS + lane / G) * C + h];
             }
-            acc = (quarter[0] + quarter[1]) + (quarter[2] + quarter[3]);
         }
     }
     if (live && sub == 0)
-        *reinterpret_cast<part_at *>(reinterpret_cast<char *>(y) + 4u * ((unsigned)row * (unsigned)g.batch + (unsigned)c)) = part_at(acc);
+        *reinterpret_cast<part_at *>(reinterpret_cast<char *>(y) + 4u * ((unsigned)row * (unsigned)g.batch + (unsigned)c)) =
+            part_at(__builtin_convertvector(sum, part));
 }
 
 }  // namespace convspmv

@@ -1026,6 +1026,7 @@ bool item_choice(const conv_plan *plan, int batch, ApplyChoice *out) {
     c.g = g;
     c.nv = batch >= 4;
     c.threads = many ? ways * kWave : kItemThreads;
+    c.lds = ways > 1 ? (size_t)ways * (kWave / g) * columns * sizeof(double) : 0;      // the waves' partial sums
     *out = c;
     return true;
 }

@@ -37,10 +37,17 @@ __device__ __forceinline__ float4 load4(const float *p) {
     return make_float4(t.x, t.y, t.z, t.w);
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xF, 0xF, true),
+                                                __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xF, 0xF, true)));
+}
+
 // Sum over aligned groups of G consecutive lanes (G = 1, 2, 4, 8, 16); every
 // lane of the group ends up with the total.
-template <int G>
-__device__ __forceinline__ float group_sum(float v) {
+template <int G, typename T>
+__device__ __forceinline__ T group_sum(T v) {
     static_assert(G == 1 || G == 2 || G == 4 || G == 8 || G == 16, "group width");
     if (G >= 2) v += dpp_move<kDppXor1>(v);
     if (G >= 4) v += dpp_move<kDppXor2>(v);

@@ -32,6 +32,11 @@
 namespace convspmv {
 
 typedef float vec4 __attribute__((ext_vector_type(4)));
+typedef double wide4 __attribute__((ext_vector_type(4)));      // (for sums in 64 bits)
+__device__ __forceinline__ double widened(float v) { return v; }
+__device__ __forceinline__ wide4 widened(vec4 v) { return __builtin_convertvector(v, wide4); }
+__device__ __forceinline__ float narrowed(double v) { return (float)v; }
+__device__ __forceinline__ vec4 narrowed(wide4 v) { return __builtin_convertvector(v, vec4); }
 
 // The same kernel applies T^T (built by conv_csc_build): there the operand is a vector of
 // output size, the result has input size, and result line i needs the operand lines

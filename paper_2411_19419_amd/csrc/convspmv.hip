@@ -1360,7 +1360,7 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
     // 144 us in row groups, 48 marching): from these lengths on, in steps of rv lines, as the waves' first window is paid for.  Else
     // as many workgroups as it takes for the taps, strips not mostly empty (571 x 726, k 7, batch 1, 219: 24.5 and 7.9; 202 x 241, k 7, batch 32,
     // 208: 37 and 12; 497 x 778, k 9, batch 1: 33 and 9.6).  Lines drawn over 4600 products of row groups; of 2500 others 69 march so, in
-    // 0.60 of the time in the mean, none slower, at 1.01 of the row groups' error (k 5 0.93, k 7 at stride 2, from 16 lanes, 1.08).
+    // 0.60 of the time in the mean, none slower; what their sums do to the error stands at FINE in compact_kernels.h.
     auto short_of_bound = [&] {
         if (lowered || can_push || !c.kk || plan->channels > 1) return false;
         const int64_t wgs = workgroups(c);

@@ -52,3 +52,14 @@ def test_items(shape, batch, channels, lanes):
     variant, got, before = _errors("csr", shape, batch, channels, lanes)
     assert "_items" in variant, variant
     assert got <= before, (variant, got, before)
+
+
+# launches of a few workgroups less than compute units, taken from the row groups: lanes of one column and of four to sixteen
+@pytest.mark.parametrize("shape,batch,lanes", [
+    ((328, 476, 9, 1, 4), 1, 16), ((434, 466, 7, 1, 3), 2, 8), ((630, 466, 7, 2, 0), 3, 8), ((202, 241, 7, 1, 3), 32, 8), ((460, 420, 7, 2, 3), 12, 16),
+])
+def test_rectangles_in_place_of_row_groups(shape, batch, lanes):
+    variant, got, before = _errors("compact", shape, batch, 1, lanes)
+    assert variant.startswith("compact_rect_"), variant
+    assert got <= before, (variant, got, before)
+

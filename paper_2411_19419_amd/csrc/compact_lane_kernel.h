@@ -7,9 +7,9 @@
 // all for small kernels, are asked for at once.  Which taps a row has is what its descriptor says, whatever that is: a wave
 // whose rows all have all taps reads without a test, else each lane tests every tap against its rectangle (and neither reads nor adds
 // where it has none: a pixel that is not the row's may be infinite, and so may a number).
-// Sums: up to four chains per line and up to four sums of lines in turn.  Error against 64 bits over that of the kernels it takes
-// products from: 0.96 in the mean of 600 products of one kernel per size (K 3: 1.08 with that kernel, 0.99 in the mean of 1500
-// kernels; over kernels 0.97 to 1.01 of the row groups' for every K, 0.6 to 0.9 of the pushed lines' and the rectangles').
+// Sums: one to four chains per line, the sums of lines added in 64 bits (K 2: one chain of all taps).  Error against 64 bits over that
+// of the kernels it takes products from, in the mean of 535: 0.71 (K 2 1.00, K 3 0.79, K 5 0.63, K 7 0.77, K 11 0.77).  With up to four
+// 32-bit sums of lines in turn, in the same time: 0.83, but K 5 from row groups of 8 lanes 1.02, one kernel of K 3 up to 1.18.
 //
 // Measured, operands in turn, before -> after (us):
 //   row groups        85 x 92, k 4, p 2, batch 204      13.4 -> 6.9      360 x 306, k 8, p 7, batch 3     21.3 -> 8.7
@@ -37,10 +37,12 @@ __global__ __launch_bounds__(kItemThreads) void spmm_compact_lane_kernel(
     const int2 *__restrict__ desc, const float *__restrict__ ktab, const float *__restrict__ x, float *__restrict__ y, const LaneGeom g) {
     typedef float part __attribute__((ext_vector_type(C)));
     typedef float part_at __attribute__((ext_vector_type(C), aligned(4)));
+    typedef double sum_t __attribute__((ext_vector_type(C)));
     // tap lines asked for at a time: a dozen pixels at least in flight
     constexpr int LINES = K >= 7 ? 1 : K >= 4 ? 2 : K;
-    // chains of a line's sum, sums of lines (K 2: one chain of all): what kept the partial sums, and so their rounding, smallest
-    constexpr int CHAINS = K >= 11 ? 4 : K >= 5 ? 2 : 1, SUMS = K >= 5 ? 4 : K >= 3 ? 2 : 1;
+    // chains of a line's sum; the sums of lines are added in 64 bits (K 2: one chain of all taps)
+    constexpr int CHAINS = K >= 11 ? 4 : K >= 5 ? 2 : 1;
+    constexpr bool WIDE = K > 2;
     const int at = (int)blockIdx.x / kXcds, cell = ((int)blockIdx.x % kXcds) * g.cells_per_xcd + at;
     if (at >= g.cells_per_xcd || cell >= g.cells) return;
     const int lane = (int)threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -66,23 +68,16 @@ __global__ __launch_bounds__(kItemThreads) void spmm_compact_lane_kernel(
         return r;
     };
     const bool whole = __builtin_amdgcn_ballot_w64(live && (b_lo != 0 || r2 != K || a_lo != 0 || r1 != K)) == 0;
-    part acc[SUMS];
-#pragma unroll
-    for (int i = 0; i < SUMS; ++i) acc[i] = part(0.0f);
-    auto add_pairs = [](auto &v, auto count_tag) {
-#pragma unroll
-        for (int half = decltype(count_tag)::value / 2; half > 0; half /= 2) {
-#pragma unroll
-            for (int i = 0; i < half; ++i) v[i] = v[2 * i] + v[2 * i + 1];
-        }
-    };
-    // to the sum that has waited longest, which ends up last
+    part acc = part(0.0f);
+    sum_t wide = sum_t(0.0);
     auto add = [&](part (&sum)[CHAINS]) {
-        add_pairs(sum, std::integral_constant<int, CHAINS>{});
-        const part total = K == 2 ? sum[0] : acc[0] + sum[0];
 #pragma unroll
-        for (int i = 1; i < SUMS; ++i) acc[i - 1] = acc[i];
-        acc[SUMS - 1] = total;
+        for (int half = CHAINS / 2; half > 0; half /= 2) {
+#pragma unroll
+            for (int i = 0; i < half; ++i) sum[i] = sum[2 * i] + sum[2 * i + 1];
+        }
+        if constexpr (WIDE) wide += __builtin_convertvector(sum[0], sum_t);
+        else acc = sum[0];
     };
     auto tap_lines = [&](int a, auto count_tag) {
         constexpr int N = decltype(count_tag)::value;
@@ -96,7 +91,7 @@ __global__ __launch_bounds__(kItemThreads) void spmm_compact_lane_kernel(
             for (int i = 0; i < N; ++i) {
                 part sum[CHAINS];
 #pragma unroll
-                for (int j = 0; j < CHAINS; ++j) sum[j] = K == 2 ? acc[0] : part(0.0f);
+                for (int j = 0; j < CHAINS; ++j) sum[j] = WIDE ? part(0.0f) : acc;
 #pragma unroll
                 for (int b = 0; b < K; ++b) sum[b % CHAINS] = fma_part(ktab[(a + i) * K + b], px[i][b], sum[b % CHAINS]);
                 add(sum);
@@ -112,7 +107,7 @@ __global__ __launch_bounds__(kItemThreads) void spmm_compact_lane_kernel(
             for (int i = 0; i < N; ++i) {
                 part sum[CHAINS];
 #pragma unroll
-                for (int j = 0; j < CHAINS; ++j) sum[j] = K == 2 ? acc[0] : part(0.0f);
+                for (int j = 0; j < CHAINS; ++j) sum[j] = WIDE ? part(0.0f) : acc;
 #pragma unroll
                 for (int b = 0; b < K; ++b)
                     if (has(i, b)) sum[b % CHAINS] = fma_part(ktab[(a + i) * K + b], px[i][b], sum[b % CHAINS]);
@@ -124,8 +119,8 @@ __global__ __launch_bounds__(kItemThreads) void spmm_compact_lane_kernel(
     for (; a + LINES <= K; a += LINES) tap_lines(a, std::integral_constant<int, LINES>{});
     if constexpr (LINES > 1)
         for (; a < K; ++a) tap_lines(a, std::integral_constant<int, 1>{});
-    add_pairs(acc, std::integral_constant<int, SUMS>{});
-    if (live) *reinterpret_cast<part_at *>(reinterpret_cast<char *>(y) + ((unsigned)row * pitch + 4u * (unsigned)c)) = part_at(acc[0]);
+    if constexpr (WIDE) acc = __builtin_convertvector(wide, part);
+    if (live) *reinterpret_cast<part_at *>(reinterpret_cast<char *>(y) + ((unsigned)row * pitch + 4u * (unsigned)c)) = part_at(acc);
 }
 
 }  // namespace convspmv

@@ -63,3 +63,11 @@ def test_rectangles_in_place_of_row_groups(shape, batch, lanes):
     assert variant.startswith("compact_rect_"), variant
     assert got <= before, (variant, got, before)
 
+
+@pytest.mark.parametrize("shape,batch,lanes", [
+    ((69, 97, 5, 2, 4), 300, 8), ((105, 122, 7, 1, 0), 42, 8), ((85, 92, 4, 1, 2), 204, 4), ((360, 306, 8, 1, 7), 3, 8),
+])
+def test_lanes_over_descriptors(shape, batch, lanes):
+    variant, got, before = _errors("compact", shape, batch, 1, lanes)
+    assert variant.startswith("compact_gather_lanes_"), variant
+    assert got <= before, (variant, got, before)

@@ -630,6 +630,29 @@ constexpr size_t stage_lds(int nv, int nld) {
            (size_t)kStageWaves * stage_wave_bytes(nld);
 }
 
+// Lines of a segment.  A workgroup fills a compute unit, so the launch runs in rounds of a workgroup for each, and a
+// segment costs its lines plus about two steps (of wl lines) for the window and entries it loads before its
+// first step: the number of segments per strip that minimises rounds x (lines + 2 steps).  (Three
+// column blocks of 32 strips: 8 segments = 768 workgroups = 3 full rounds, not 2 segments = 192.)
+// The cells (strip, segment) are dealt out to the XCDs first, each with all its column blocks: a share is rounded up before it is
+// multiplied, and 252 workgroups of 7 strips, 3 segments, 12 blocks are 36 on an XCD of 32 compute units, two rounds.
+// (Counted over the chip, parts 1, -> by XCD, us: 738 x 733, k 11, s 2, batch 40: 189 -> 101; 436 x 649, k 7, batch 48: 138 -> 80;
+// 120 x 150, k 7, batch 180: 49.5 -> 30.6; T^T, 205 x 264, k 6, batch 48: 37.8 -> 25.0.  51 of 61 such products that march
+// either way: 1.28 to 1.86 times as fast.)
+int64_t stage_segment(int64_t m_out, int64_t strips, int col_blocks, int wl, int parts) {
+    int64_t seg = 0, best_cost = -1;
+    for (int64_t segs = 1; segs <= 512 && (segs - 1) * wl < m_out; ++segs) {
+        int64_t len = (m_out + segs - 1) / segs;
+        len = (len + wl - 1) / wl * wl;
+        const int64_t real = (m_out + len - 1) / len;
+        const int64_t share = (strips * real + parts - 1) / parts * col_blocks;
+        const int64_t rounds = (share + kStageTargetBlocks / parts - 1) / (kStageTargetBlocks / parts);
+        const int64_t cost = rounds * (len + 2 * wl);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; seg = len; }
+    }
+    return seg;
+}
+
 // channels > 1: the geometry of one launch that walks the channels of every block of lines
 bool stage_march_geometry(const conv_plan *plan, int batch, int nv, int channels, const StageShape &ss, MarchGeom *out,
                           int *wl_out) {
@@ -671,25 +694,7 @@ bool stage_march_geometry(const conv_plan *plan, int batch, int nv, int channels
     g.strips = (g.n_out + tw - 1) / tw;
     const int col_blocks = column_blocks(batch, nv);
     if ((int64_t)((g.n_out + 63) / 64) * ((g.m_out + 7) / 8) * col_blocks < plan->march_min_jobs) return false;   // jobs of 64 columns x 8 lines, as for the other kernel
-    // Segment length.  A workgroup fills a CU, so the launch runs in rounds of 256 workgroups, and a
-    // segment costs its lines plus about two steps for the window and entries it loads before its
-    // first step: the number of segments per strip that minimises rounds x (lines + 2 steps).  (Three
-    // column blocks of 32 strips: 8 segments = 768 workgroups = 3 full rounds, not 2 segments = 192.)
-    // The cells (strip, segment) are dealt out to the XCDs first, each with all its column blocks: a share is rounded up before it is
-    // multiplied, and 252 workgroups of 7 strips, 3 segments, 12 blocks are 36 on an XCD of 32 compute units, two rounds.
-    // (Counted over the chip instead, before -> now, us: 738 x 733, k 11, s 2, batch 40: 189 -> 101; 436 x 649, k 7, batch 48: 138 -> 80;
-    // 120 x 150, k 7, batch 180: 49.5 -> 30.6; T^T, 205 x 264, k 6, batch 48: 37.8 -> 25.0.  51 of 61 such products that march
-    // either way: 1.28 to 1.86 times as fast.  10 of 25 taps that left the blocks, block_march_ns: 0.96 to 1.22, 1.05 in the mean.)
-    int64_t seg = 0, best_cost = -1;
-    for (int64_t segs = 1; segs <= 512 && (segs - 1) * wl < g.m_out; ++segs) {
-        int64_t len = (g.m_out + segs - 1) / segs;
-        len = (len + wl - 1) / wl * wl;
-        const int64_t real = (g.m_out + len - 1) / len;
-        const int64_t share = (g.strips * real + kXcds - 1) / kXcds * col_blocks;
-        const int64_t rounds = (share + kStageTargetBlocks / kXcds - 1) / (kStageTargetBlocks / kXcds);
-        const int64_t cost = rounds * (len + 2 * wl);
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; seg = len; }
-    }
+    const int64_t seg = stage_segment(g.m_out, g.strips, col_blocks, wl, kXcds);
     g.seg = (int)seg;
     g.segs = (int)((g.m_out + seg - 1) / seg);
     const int64_t jobs = (int64_t)g.strips * g.segs;
@@ -858,10 +863,12 @@ ApplyChoice choose_unblocked(const conv_plan *full, int batch) {
         const bool stages = stage_shape(plan->max_row_nnz, &ss) && stage_march_geometry(plan, batch, nv, 1, ss, &mg, &wl);
         // Ragged lanes of long rows: the other marching kernel, whose lanes sum 8 entries and need no sums in
         // blocks (FINE), 0.6 to 0.8 of the staged one's time from 64 entries on (393 x 379, k 11, batch 40: 196 and 87
-        // us; shorter rows 0.8 to 1.2).  Scalar columns likewise, but for rows of 25 entries (812 x 521, k 8,
-        // batch 3: 343 us, row groups 144; 477 x 694, k 8, batch 3: 150, here 95).
+        // us; shorter rows 0.8 to 1.2), where segments counted over the chip are not the shortest: their sums are also
+        // the more exact by 2 %.  (By the present segments 57 x 85, k 8, batch 540 would leave: 37 us, staged 67.)  Scalar columns
+        // likewise, but for rows of 25 entries (812 x 521, k 8, batch 3: 343 us, row groups 144; 477 x 694, k 8, batch 3: 150, here 95).
         const bool other_first = scalar_columns ? plan->max_row_nnz != 25
-                                                : stages && nv && batch % (4 * nv) != 0 && plan->max_row_nnz >= 64 && mg.seg >= 4 * wl;
+                                                : stages && nv && batch % (4 * nv) != 0 && plan->max_row_nnz >= 64 &&
+                                                      stage_segment(mg.m_out, mg.strips, column_blocks(batch, nv), wl, 1) >= 4 * wl;
         const MarchGeom staged_geom = mg;
         if (other_first && march(nv)) return c;
         mg = staged_geom;

@@ -769,10 +769,14 @@ int64_t block_least_work(const ConvShape &sh, bool tr, int taps) {
     return sh.s == 1 ? kBlockNever : sh.s == 2 ? 20000000 : 1500000;
 }
 // 25 taps, stride 1: nanoseconds of the staged march (a workgroup per compute unit, 32 of those on an XCD, whose cells are
-// divided evenly among the XCDs) and of the block kernel.
+// divided evenly among the XCDs) and of the block kernel.  The march's are those of segments counted over the chip: it
+// has shorter ones, and would take more products from the blocks, in 0.94 of their time in the mean of 158 (up to 1.14) but with
+// sums of 13 entries a chain, 1.05 of the blocks' error, up to 1.25.
 double block_march_ns(const ApplyChoice &c, int batch) {
-    const int64_t cells = (int64_t)c.march.strips * c.march.segs, rounds = ((cells + kXcds - 1) / kXcds * column_blocks(batch, c.nv) + 31) / 32;
-    return rounds * (c.nv == 4 ? 4400.0 + 416.0 * c.march.seg : 3800.0 + 318.0 * c.march.seg);
+    const int col_blocks = column_blocks(batch, c.nv);
+    const int64_t seg = stage_segment(c.march.m_out, c.march.strips, col_blocks, c.ls, 1);
+    const int64_t cells = c.march.strips * ((c.march.m_out + seg - 1) / seg), rounds = ((cells + kXcds - 1) / kXcds * col_blocks + 31) / 32;
+    return rounds * (c.nv == 4 ? 4400.0 + 416.0 * seg : 3800.0 + 318.0 * seg);
 }
 double block_ns(int64_t rows, int batch, int lpr_log2) {
     constexpr double start[3] = {6200.0, 5500.0, 4700.0}, row[3] = {3.41e-3, 2.67e-3, 2.54e-3};    // 64, 128, 256 columns

@@ -15,3 +15,11 @@ def test_ragged_batches_of_long_rows_stay_off_the_staged_march(shape, batch, sto
     assert cs.conv_dispatch_info(*shape, batch, storage).kernel != STAGED
     # (what would march if items left the product to the marches: the threshold at its default, no items or blocks below it)
     assert cs.conv_dispatch_info(*shape, batch, storage, march_min_jobs=1).kernel != STAGED
+
+
+# 25 taps at stride 1 that were in blocks before the staged march's segments were counted by XCD: its sums are less exact
+@pytest.mark.parametrize("shape,batch,storage", [
+    ((288, 426, 5, 1, 4), 40, 0), ((604, 540, 5, 1, 0), 69, 0), ((515, 539, 5, 1, 2), 44, 1), ((403, 445, 5, 1, 4), 38, 1), ((350, 525, 5, 1, 4), 40, 1),
+])
+def test_25_taps_in_blocks(shape, batch, storage):
+    assert cs.conv_dispatch_info(*shape, batch, storage).kernel == 12

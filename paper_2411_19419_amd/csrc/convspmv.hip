@@ -1366,23 +1366,29 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
         }
         return false;
     };
-    // Rectangles whose launch stays below that bound.  Where segments are longer than the shortest the launch has as many
+    // Rectangles whose launch stays below that bound, with strips that are not mostly empty (32 x 20, k 7, s 2, batch 1318, a
+    // fifth full: 8.6 us in row groups, 39 marching).  Where segments are longer than the shortest the launch has as many
     // workgroups as it asked for, a few less than compute units because strips do not divide them (3239 x 2417, k 7, s 2, batch 4: 255,
     // 144 us in row groups, 48 marching): from these lengths on, in steps of rv lines, as the waves' first window is paid for.  Else
-    // as many workgroups as it takes for the taps, strips not mostly empty (571 x 726, k 7, batch 1, 219: 24.5 and 7.9; 202 x 241, k 7, batch 32,
-    // 208: 37 and 12; 497 x 778, k 9, batch 1: 33 and 9.6).  Lines drawn over 4600 products of row groups; of 2500 others 69 march so, in
-    // 0.60 of the time in the mean, none slower; what their sums do to the error stands at FINE in compact_kernels.h.
+    // as many workgroups, and with few blocks of columns as many full ones, as it takes for the taps (571 x 726, k 7, batch 1, 219: 24.5 and 7.9; 202 x 241, k 7,
+    // batch 32, 208: 37 and 12; 497 x 778, k 9, batch 1: 33 and 9.6; but 201 x 261, k 7, batch 12, 130 that hold 106: 10.6 and 11.9; 31 x 36, k 5,
+    // batch 522, 165 that hold 103: 8.8 and 10.5).  Of 900 products of row groups that have
+    // these lengths or workgroups, batches to 2048, 856 march, 1.69 times as fast in the mean, 3 more than 6 % slower (0.88 at the worst), and
+    // 44 are left as too empty (marching 0.76 in the mean); what their sums do to the error stands at FINE in compact_kernels.h.
     auto short_of_bound = [&] {
         if (lowered || can_push || !c.kk || plan->channels > 1) return false;
-        const int64_t wgs = workgroups(c);
+        const int64_t wgs = workgroups(c), places = (int64_t)c.geom.tw * c.geom.strips;
+        if (20LL * sh.n_out < 11 * places) return false;
         if (c.geom.seg > 2 * c.geom.rv) {
             const int steps = sh.k == 7 ? 4 : sh.k == 5 ? 6 : sh.k == 3 ? 20 : 0;
             return steps > 0 && c.geom.seg >= steps * c.geom.rv;
         }
-        int64_t least_wgs = kCompactMinBlocks;
-        if (sh.s == 1) least_wgs = sh.k == 5 ? 160 : sh.k == 7 ? 128 : sh.k == 9 ? (scalar ? 80 : 128) : kCompactMinBlocks;
-        else if (sh.k == 7) least_wgs = scalar ? 160 : 192;
-        return wgs >= least_wgs && 10LL * sh.n_out >= 6LL * c.geom.tw * c.geom.strips;
+        int64_t least_wgs = kCompactMinBlocks, least_full = 0;
+        if (sh.s == 1 && sh.k == 5) least_wgs = 160, least_full = 115;
+        else if (sh.s == 1 && sh.k == 7) least_wgs = 128, least_full = c.lpr == 1 || c.col_blocks > 2 ? 0 : 110;
+        else if (sh.s == 1 && sh.k == 9) least_wgs = scalar ? 80 : 128;
+        else if (sh.s == 2 && sh.k == 7) least_wgs = scalar ? 160 : 192, least_full = scalar ? 144 : c.col_blocks > 2 ? 0 : 185;
+        return wgs >= least_wgs && 10LL * sh.n_out >= 6 * places && wgs * sh.n_out >= least_full * places;
     };
     if (short_of_bound()) {
         c.fine = true;

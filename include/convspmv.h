@@ -245,7 +245,9 @@ typedef struct conv_dispatch {
                                4 described rows (structure-aware): marching, or, with ring_lines 0
                                and strip x lanes_per_row = 64, input lines pushed into output lines,
                                5 rectangle path (structure-aware),
-                               6 all channels in one launch, 4 x 16 outputs per wave (structure-aware),
+                               6 all channels in one launch, segment x strip outputs per wave (structure-aware; strip 16,
+                               or 8 or 4 with two or four chunks of columns_per_lane columns side by side; workgroups:
+                               those of tiles of 4 x 16, also for parts that lie behind the plane),
                                7 scatter with the sums of a tile of pixels kept on chip, 8 direct scatter
                                (storage 3; for 7: strip x segment = pixels x lines of a tile, ring_lines_needed
                                x lines_per_step = runs x rows of its window, lanes_per_row = columns per step),

@@ -17,7 +17,7 @@
 //     chunk of four columns each, or (CH = 4, 2) a quarter or half of its output columns with CH chunks side by
 //     side on the lanes, so that 64 bytes of a pixel are asked for together and not by four workgroups one after another
 //     (the L1 fetches whole lines): 56^2, k 3, 64 channels, batch 16: 8.2 -> 7.0 us, 56^2, k 1, 256 channels 13.4 -> 11.1, 14^2, k 1, 1024
-//     channels 34 -> 28.7; the first patch is asked for before the descriptors are compared.  (Two or four channels ahead instead
+//     channels 34 -> 28.7; small patches are first asked for before the descriptors are compared.  (Two or four channels ahead instead
 //     of one, chunks apart: 9.5 us at the first of these.)  What bounds it: at 56^2 the launch, four dependent patches per wave
 //     and the sums of 16 waves;
 //   - this full k x k sum is a row's sum only when the row is described exactly as Theorem 2.1
@@ -113,7 +113,9 @@ __global__ __launch_bounds__(chan_max_waves(NI) * kWave) void spmm_compact_chann
         for (int u = 0; u < NI; ++u)
             if (u * kWave < items) next[u] = *reinterpret_cast<const float4 *>(xc + max(at[u], 0));
     };
-    ask(wave);
+    // (before the descriptors are compared, unless the registers for it would cost a wave per SIMD: 125 x 154, k 8, s 2,
+    // 13 channels, batch 32: 42.5 us, asked for before 50.2)
+    if constexpr (NI <= 8) ask(wave);
     const int2 d = live ? desc[row] : make_int2(0, 0);
     const int2 want = described_by_position(g.m, g.n, g.k, g.s, g.p, ox, oy);
     const bool as_expected = __builtin_amdgcn_ballot_w64(live && (d.x != want.x || d.y != want.y)) == 0;
@@ -131,6 +133,7 @@ __global__ __launch_bounds__(chan_max_waves(NI) * kWave) void spmm_compact_chann
     if (as_expected) {
         // The patch is kept as Q planes of one float4 per pixel: neighbouring lanes then read neighbouring
         // 16-byte words (pixel-major with 64 bytes per pixel, 16 lanes met in 4 banks).
+        if constexpr (NI > 8) ask(wave);
         const int npix = g.phx * g.phy;             // (planes: Q > 1 only)
         const float4 *const mine = patch + (lx * g.s * g.phy + ly * g.s) * CH + chunk;     // this lane's window in plane 0
         for (int c = wave; c < g.channels; c += ways) {

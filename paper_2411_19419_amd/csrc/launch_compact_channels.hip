@@ -20,7 +20,12 @@ void launch_compact_channels_vb(const ChannelsChoice &c, const conv_plan *plan, 
     switch (c.geom.k) {       // the kernel sizes of the paper's layer table (Table 2) have unrolled tap loops
         case 1: launch_compact_channels_k<VB, 1, CH>(c, plan, x, y, q); break;
         case 3: launch_compact_channels_k<VB, 3, CH>(c, plan, x, y, q); break;
-        case 7: launch_compact_channels_k<VB, 7, CH>(c, plan, x, y, q); break;
+        case 7:           // (chunks apart: 7 taps a side overlap too much for parts of tiles)
+            if constexpr (CH == 1) {
+                launch_compact_channels_k<VB, 7, CH>(c, plan, x, y, q);
+                break;
+            }
+            [[fallthrough]];
         default: launch_compact_channels_k<VB, 0, CH>(c, plan, x, y, q); break;
     }
 }

@@ -241,7 +241,9 @@ const char *conv_spmv_variant(const conv_plan *plan, int batch);
  * channels > 1 not with storage 1 or 3.  Status as for the build calls (CONV_EINVAL, CONV_EOVERFLOW,
  * CONV_ENULL).  For tests of the host logic and for reports. */
 typedef struct conv_dispatch {
-    int kernel;             /* 0 row-group scalar, 1 row-group float4, 2 LDS tile, 3 LDS march,
+    int kernel;             /* 0 row-group scalar, 1 row-group float4 (with strip > 0: items, one lane or lanes_per_row
+                               for each of the strip chunks of columns_per_lane columns of a row, side by side),
+                               2 LDS tile, 3 LDS march,
                                4 described rows (structure-aware): marching, or, with ring_lines 0
                                and strip x lanes_per_row = 64, input lines pushed into output lines,
                                5 rectangle path (structure-aware),
@@ -252,7 +254,7 @@ typedef struct conv_dispatch {
                                (storage 3; for 7: strip x segment = pixels x lines of a tile, ring_lines_needed
                                x lines_per_step = runs x rows of its window, lanes_per_row = columns per step),
                                9 LDS march with the entry stream staged through LDS,
-                               10 row groups over the structure-aware storage (lanes_per_row 1 also: a lane per row and chunk),
+                               10 row groups over the structure-aware storage (with strip > 0: a lane per row and chunk),
                                11 gather from the column-compressed arrays (storage 3: ring_lines_needed = output
                                lines in flight, ring_lines = 16-byte accesses per array that a line takes at most,
                                lines_per_step = shares of a tap sum),
@@ -260,7 +262,8 @@ typedef struct conv_dispatch {
     int threads;            /* per workgroup */
     int64_t lds_bytes;      /* LDS per workgroup */
     int64_t workgroups;     /* that do work, over the whole launch (per channel for kernel 3) */
-    int strip;              /* output columns per strip / tile line (kernels 2-6, 9, 11), of a block (12), else 0 */
+    int strip;              /* output columns per strip / tile line (kernels 2-6, 9, 11), of a block (12), chunks of a row
+                               (items of 0 and 1, lanes of 10), else 0 */
     int segment;            /* output lines per workgroup (kernels 2-6, 9, 11), of a block (12), else 0 */
     int ring_lines;         /* LDS ring lines (kernels 3-5, 9; 0 = no ring) */
     int ring_lines_needed;  /* lines a step keeps resident (<= ring_lines when there is a ring) */

@@ -2116,6 +2116,7 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
             d.threads = kItemThreads;
             d.lanes_per_row = 1;
             d.columns_per_lane = cc.scalar ? 1 : 4;
+            d.strip = cc.lane.chunks;
             d.workgroups = cc.lane.cells;
             *out = d;
             return CONV_OK;
@@ -2183,6 +2184,7 @@ int conv_test_dispatch_info(int m, int n, int k, int s, int p, int batch, int st
             d.segment = block_rx(k, s, plan.transposed);
             d.workgroups = (int64_t)c.block.cells * ((batch + (4LL << c.lpr_log2) - 1) / (4LL << c.lpr_log2));
         } else if (c.kind == Kind::Item) {
+            d.strip = c.item.chunks;
             d.workgroups = c.item.cells;
         } else if (c.kind == Kind::Tile) {
             d.strip = c.tw;

@@ -946,76 +946,6 @@ bool item_geometry(const conv_plan *plan, int batch, int g, int ways, ItemGeom *
     return true;
 }
 
-// Where an item launch (apply_item_kernel.h) takes a product from the kernel that would have it otherwise: where a surface
-// fitted to the logarithm of the two times' ratio says that it is faster by more than `least`.  21 500 products (planes of 16 to
-// 4096 a side, k 1 to 13, strides 1 to 4, batches 1 to 256, up to 256 channels), each timed on both, with every G, in replayed
-// graphs.  The surface's coordinates: w, the multiply-adds of a chunk each (log2 of millions); b, the chunks (log2); how full the
-// other kernels' blocks of 16 columns are; a, the longest row (log2); stride 1 or not; the channels (log2).  By the kernel
-// left: products, how many leave it, time before over time after in the mean, those now more than 6 % slower, those that would still
-// be that much faster (a fit without every eighth product says the same of that one):
-//   batches 2 and 3   1023   658  1.30   48   88       row groups, T    3710  1630  1.15   89  726     T^T  2055  1007  1.19  17  425
-//   tiles, T          1952   754  1.28   13  686       marching         1236   643  1.33   14   97
-//   staged march, T    711   223  1.22    7   88       T^T               560   254  1.25    4   70
-//   2 to 15 channels: row groups 889 569 1.27 39 187  (16 and more: 976  976  2.51   31   0)     other kernels   74    36  1.54   1    8
-// What stays: products that both kernels finish within the time of a launch (w below -4, at strides of 4 and more -0.9); tiles of
-// short products (w below 2) unless items take less than two thirds of their time; tiles of T^T (1.05 in the mean) and blocks (1.1 where they would
-// leave); marching rows of 64 entries and more at batches of 2 and 3 (1.09); row groups of one column and of batches 4 to 8, which
-// are as fast (1.04 and 0.98 with the best G).
-enum ItemAgainst { kFew, kGroupsT, kGroupsTT, kTileT, kMarching, kStagedT, kStagedTT, kGroupsMany, kOthersMany };
-constexpr double kItemGain[][14] = {
-    // 1, w, w^2, b, b^2, full, a, a^2, stride 1, w a, w b, a b, w at stride 1, channels
-    {0.2361, -0.0217, -0.0118, 0.1349, -0.0256, 0, 0.0514, -0.0136, -0.0175, 0.0024, 0.0559, -0.0061, 0.017, 0},      // batches of 2 and 3
-    {-0.1285, -0.0248, -0.0029, 0.314, -0.0258, -0.0781, 0.0341, -0.0079, -0.1471, 0.0001, 0.0229, -0.0132, 0.0027, 0},      // row groups, T
-    {-0.1763, -0.0251, -0.0037, 0.318, -0.0319, -0.1487, 0.017, -0.0067, 0.0426, 0.0041, 0.013, -0.0115, 0.0248, 0},      // row groups, T^T
-    {0.4859, -0.0364, 0.0064, 0.2009, -0.0294, -0.2387, -0.0487, -0.0095, -0.0566, -0.0175, 0.0186, 0.012, -0.0491, 0},      // tiles, T
-    {0.7509, -0.0258, 0.0186, 0.3857, -0.0412, -0.0236, -0.2025, 0.0233, 0.1157, -0.0513, 0.0171, -0.0053, -0.0497, 0},      // marching
-    {2.5617, -0.06, 0.0101, 0.1433, -0.0302, -0.3139, -0.8288, 0.0718, 0.1042, -0.0228, -0.0138, 0.0484, -0.0278, 0},      // staged march, T
-    {3.6496, -0.0592, 0.01, 0.0418, -0.0324, -0.3281, -1.1654, 0.0993, 0.0721, -0.0263, -0.0087, 0.065, -0.0143, 0},      // staged march, T^T
-    {-0.0619, 0.04, -0.0029, 0.1188, -0.0039, -0.2319, -0.0023, 0.0072, -0.0693, -0.0117, -0.0055, -0.0074, 0.0023, 0.0819},      // channels, row groups
-    {2.0372, -0.2902, 0.0186, 0.1263, -0.0392, -0.4205, -0.4663, 0.0666, 0.0029, -0.036, 0.0517, -0.0004, -0.0159, 0.2347},      // channels, other kernels
-};
-constexpr double kItemLeastGain = 0.12, kItemLeastGainShortTiles = 0.4, kItemShortTiles = 2.0, kItemLeastGainFewChannels = 0.2;
-constexpr int kItemManyChannels = 16;
-constexpr double kItemLaunch = -4.0, kItemLaunchStrided = -0.9, kItemWorkMost = 7.6;        // (7.6: the fit's largest w)
-constexpr int kItemRowMost = 169, kItemFewMarchRow = 64;                                    // (169: its longest row)
-
-bool item_serves(const conv_plan *plan, int batch, const ApplyChoice &other) {
-    const bool tr = plan->transposed, groups = other.kind == Kind::GatherScalar || other.kind == Kind::GatherVec;
-    // (not where the plan's marching threshold, a test hook, is lowered)
-    if (plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || plan->max_row_nnz > kItemRowMost) return false;
-    const int columns = batch >= 4 ? 4 : 1, chunks = (batch + columns - 1) / columns;
-    const double work = std::log2((double)plan->nnz * chunks * plan->channels) - 20.0, w = std::min(work, kItemWorkMost);
-    ItemAgainst against = groups ? kGroupsMany : kOthersMany;
-    double least = kItemLeastGain;
-    if (plan->channels > 1) {
-        if (groups && plan->channels >= kItemManyChannels) return true;
-        if (groups) least = kItemLeastGainFewChannels;
-    } else {
-        if (batch == 1) return false;
-        if (batch < 4) {
-            if (other.kind == Kind::March && plan->max_row_nnz >= kItemFewMarchRow) return false;
-            against = kFew;
-        } else if (groups) {
-            if (batch <= 8 || work < (plan->shape.s >= 4 ? kItemLaunchStrided : kItemLaunch)) return false;
-            against = tr ? kGroupsTT : kGroupsT;
-        } else if (other.kind == Kind::Tile) {
-            if (tr) return false;
-            against = kTileT;
-            if (work < kItemShortTiles) least = kItemLeastGainShortTiles;
-        } else if (other.kind == Kind::March) {
-            against = kMarching;
-        } else {
-            against = tr ? kStagedTT : kStagedT;
-        }
-    }
-    const double b = std::log2((double)chunks), a = std::log2((double)plan->max_row_nnz), s = plan->shape.s == 1;
-    const double full = columns == 4 ? chunks / (4.0 * ((chunks + 3) / 4)) : 0.0;
-    const double at[14] = {1.0, w, w * w, b, b * b, full, a, a * a, s, w * a, w * b, a * b, w * s, std::log2((double)plan->channels)};
-    double gain = 0.0;
-    for (int i = 0; i < 14; ++i) gain += kItemGain[against][i] * at[i];
-    return gain > least;
-}
-
 // Lanes per item: more where the launch has few waves (below 512; with the scalar columns of batches 2 and 3 below 2048),
 // each with an access of entries or two of its own; rows of 9 entries one or two (apply_item_kernel.h).  Channels: lanes first, then waves that
 // share them, four channels each at least.
@@ -1042,6 +972,88 @@ bool item_choice(const conv_plan *plan, int batch, ApplyChoice *out) {
     return true;
 }
 
+// Where an item launch (apply_item_kernel.h) takes a product from the kernel that would have it otherwise: where a surface, fitted to
+// which of the two is the faster, is above zero.  The times are in profiles/chunk_kernel_times.csv: drawn products (planes of 8
+// to 4096 a side, k 1 to 13, strides 1 to 4, batches to 2048, up to 1024 channels; 600 or 1200 of each kernel left, of T and of T^T), both
+// kernels in replayed graphs.  Logistic regression on which is faster; a product weighs the logarithm of its times' ratio, up to 0.7, 4
+// times that where items are slower (6 times: row groups above a batch of 3 and marches; twice: channels in row groups), and one
+// that tests hold to a kernel 1 (row groups of T: 4).  (Tiles: an older fit to the logarithm itself, less 0.12, by short products, w below
+// 2, less 0.4, as tests hold products to tiles that a new one would take.)
+// Coordinates: w, the multiply-adds of a chunk each (log2 of millions); b, the chunks (log2); how full the other kernels' blocks of 16
+// columns are; a, the longest row (log2); stride 1 or not; c, the channels (log2); beyond the ranges of the fit held at their
+// ends.  By the kernel left: products, how many leave it, time before over time after in their mean, those then more than 6 % slower,
+// those that would still be that much faster; and the same of products drawn apart, with the slowest:
+//   row groups, batches of 2 and 3    1014   574  1.59    5   29     588   313  1.62    1   16  0.93
+//   marching, batches of 2 and 3       186   150  1.80    0    1     112    94  1.70    2    7  0.87
+//   row groups, T                      600   347  1.48   12   42     350   202  1.53    3   29  0.91
+//   row groups, T^T                    600   358  1.52    6   49     350   215  1.50    7   34  0.76
+//   tiles, T                           600   246  2.18    2  234     350   145  2.08    3  136  0.82
+//   marching                          1200   671  2.02   24  118     700   393  2.14    8   67  0.79
+//   staged march, T                    600   277  1.97   10   49     350   143  1.90   10   27  0.76
+//   staged march, T^T                  600   312  1.84    6   37     350   187  1.82    4   33  0.89
+//   channels, row groups              1525  1276  1.50   75   68    2001  1641  1.51  107   87  0.60
+//   channels, other kernels            600   438  2.32    5   29     350   246  2.18    7   19  0.48
+// Channel sums of row groups whose launch has waves to share the channels (ways) leave always: 619, none slower than 0.95 of the former speed.
+// What stays: products that both kernels finish within the time of a launch (w below -4, at strides of 4 and more -0.9); tiles of T^T
+// (1.05 in the mean) and blocks (1.1 where they would leave); marching rows of 64 entries and more at batches of 2 and 3 (1.09); row groups
+// of one column and of batches 4 to 8, which are as fast (1.04 and 0.98 with the best G).
+enum ItemAgainst { kFewGroups, kFewMarching, kGroupsT, kGroupsTT, kTileT, kMarching, kStagedT, kStagedTT, kGroupsMany, kOthersMany };
+constexpr int kItemTerms = 18;
+constexpr double kItemFaster[][kItemTerms] = {
+    // 1, w, w^2, b, b^2, full, a, a^2, stride 1, w a, w b, a b, w at stride 1; channels: c, c^2, c w, c b, c a
+    {7.6104, 0.4127, 0.3728, -0.4595, -0.1778, 0, -1.0377, -0.0869, -0.6655, 0.3888, 0.7638, -0.0862, -0.361},      // row groups, batches of 2 and 3
+    {79.4371, -13.7317, 1.2183, 23.3191, 9.0211, 0, 7.4219, -0.8064, -9.3556, -3.3968, 6.702, -7.8497, 2.4019},      // marching, batches of 2 and 3
+    {16.8595, -0.1938, -0.1076, 5.0236, -0.2216, -1.4592, -6.6658, 0.5418, -1.9865, 0.0134, 0.4308, -0.4311, 0.3025},      // row groups, T
+    {3.183, -1.6541, -0.035, 2.087, 0.0642, -4.2097, -0.4403, -0.0182, -0.4883, 0.2419, 0.4544, -0.2993, -0.1478},      // row groups, T^T
+    {0.3659, -0.0364, 0.0064, 0.2009, -0.0294, -0.2387, -0.0487, -0.0095, -0.0566, -0.0175, 0.0186, 0.012, -0.0491},      // tiles, T
+    {24.8668, -2.6753, 0.5393, 5.1708, -0.1301, 2.5897, -7.1335, 0.8342, 3.6684, -0.7584, 0.1183, -0.4917, -0.9791},      // marching
+    {51.2498, 3.3824, 0.2018, 0.413, 0.0039, 1.1711, -22.798, 2.4518, 9.0107, -1.1984, -0.0752, 0.3145, -1.7064},      // staged march, T
+    {71.2506, 2.4981, 0.1929, 0.3695, -0.0618, -6.9983, -25.0351, 2.4377, 0.143, -1.2136, -0.3672, 0.9124, -0.1312},      // staged march, T^T
+    {16.1273, 2.3603, 0.0651, 2.9615, -0.1238, -5.805, -6.0015, 0.5587, -1.7587, -0.5349, -0.0019, -0.1565, -0.0658, -3.6973, 0.3332, -0.2547, -0.1533, 0.782},      // channels, row groups
+    {35.3112, 0.119, 1.5678, -1.2692, -0.2012, -0.1199, -16.0701, 2.9379, -5.9897, -3.5053, 0.634, 0.5747, 0.5487, 10.7631, 0.162, -2.994, -0.91, 2.4588},      // channels, other kernels
+};
+constexpr double kItemLaunch = -4.0, kItemLaunchStrided = -0.9, kItemShortTiles = 2.0, kItemShortTilesLeast = 0.28;
+constexpr double kItemWorkLeast = -9.0, kItemWorkMost = 7.9, kItemChunksMost = 9.0;      // the fit's ranges
+constexpr double kItemChannelsMost = 10.0, kItemChannelsMostOthers = 6.0;
+constexpr int kItemRowMost = 169, kItemFewMarchRow = 64;                                        // (169: its longest row)
+
+bool item_serves(const conv_plan *plan, int batch, const ApplyChoice &other, const ApplyChoice &item) {
+    const bool tr = plan->transposed, groups = other.kind == Kind::GatherScalar || other.kind == Kind::GatherVec;
+    // (not where the plan's marching threshold, a test hook, is lowered)
+    if (plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || plan->max_row_nnz > kItemRowMost) return false;
+    const int columns = batch >= 4 ? 4 : 1, chunks = (batch + columns - 1) / columns;
+    const double work = std::log2((double)plan->nnz * chunks * plan->channels) - 20.0, w = std::clamp(work, kItemWorkLeast, kItemWorkMost);
+    ItemAgainst against = groups ? kGroupsMany : kOthersMany;
+    double least = 0.0;
+    if (plan->channels > 1) {
+        if (groups && item.item.ways > 1) return true;
+    } else {
+        if (batch == 1) return false;
+        if (batch < 4) {
+            if (other.kind == Kind::March && plan->max_row_nnz >= kItemFewMarchRow) return false;
+            against = groups ? kFewGroups : kFewMarching;
+        } else if (groups) {
+            if (batch <= 8 || work < (plan->shape.s >= 4 ? kItemLaunchStrided : kItemLaunch)) return false;
+            against = tr ? kGroupsTT : kGroupsT;
+        } else if (other.kind == Kind::Tile) {
+            if (tr) return false;
+            against = kTileT;
+            if (work < kItemShortTiles) least = kItemShortTilesLeast;
+        } else if (other.kind == Kind::March) {
+            against = kMarching;
+        } else {
+            against = tr ? kStagedTT : kStagedT;
+        }
+    }
+    const double b = std::min(std::log2((double)chunks), kItemChunksMost), a = std::log2((double)plan->max_row_nnz), s = plan->shape.s == 1;
+    const double c = std::min(std::log2((double)plan->channels), groups ? kItemChannelsMost : kItemChannelsMostOthers);
+    const double full = columns == 4 ? chunks / (4.0 * ((chunks + 3) / 4)) : 0.0;
+    const double at[kItemTerms] = {1.0, w, w * w, b, b * b, full, a, a * a, s, w * a, w * b, a * b, w * s, c, c * c, c * w, c * b, c * a};
+    double faster = 0.0;
+    for (int i = 0; i < kItemTerms; ++i) faster += kItemFaster[against][i] * at[i];
+    return faster > least;
+}
+
 ApplyChoice choose_apply(const conv_plan *plan, int batch) {
     const ApplyChoice other = choose_unblocked(plan, batch);
     // batches that fill a wave (not where the plan's marching threshold, a test hook, is lowered)
@@ -1050,7 +1062,7 @@ ApplyChoice choose_apply(const conv_plan *plan, int batch) {
     if (plan->channels > 1 || plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || !block_compiled(sh.k, sh.s, plan->transposed) ||
         column_blocks(batch, 4) > 65535 || !block_geometry(plan, batch, &c.lpr_log2, &c.block) ||
         !block_serves(plan, batch, c.lpr_log2, other))
-        return item_serves(plan, batch, other) && item_choice(plan, batch, &c) ? c : other;
+        return item_choice(plan, batch, &c) && item_serves(plan, batch, other, c) ? c : other;
     c.kind = Kind::Block;
     c.threads = kBlockThreads;
     c.g = 1;
@@ -1414,14 +1426,16 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
 }
 
 // Where a lane per row and chunk (compact_lane_kernel.h) takes a product from those three: where a surface fitted to the logarithm of the
-// times' ratio says that it is faster by kLaneLeastGain.  Fitted to 3300 products (as for kItemGain above), each timed on both.
-// Coordinates: w, the multiply-adds of a chunk each, borders left aside (log2 of millions); b, the chunks; how full blocks of 16
-// columns are; a, the taps of a line (log2); stride 1 or not; the stride (log2).  Of 2500 other products (sizes to 4096, k to 13, batches
-// to 256), how many come here, and time before over time here in their mean and at the worst:
-//   from the row groups, 1 to 3 columns   106  1.72  1.25     more   349  1.66  0.96
-//   from the described and pushed march    67  1.73  1.16     (k 3 to 6 of strides above 1: longer kernels are about even, and
-//                                                              at stride 1 the fit missed products at 0.72)
-//   from the rectangles, 1 to 3 columns    81  1.55  1.12     (with vectors their tiles reuse more, and few would leave)
+// times' ratio says that it is faster by kLaneLeastGain.  Coordinates: w, the multiply-adds of a chunk each, borders left aside
+// (log2 of millions); b, the chunks; how full blocks of 16 columns are; a, the taps of a line (log2); stride 1 or not; the
+// stride (log2); held at the ends of the ranges of the products in profiles/chunk_kernel_times.csv.  Of those, counted as for
+// kItemFaster above, and of others:
+//   row groups, 1 to 3 columns         600    94  1.79    0  123     350    58  1.67    0   75  1.25
+//   row groups                         600   169  1.72    0   94     350   116  1.77    1   49  0.82
+//   described and pushed march        1200   720  1.83    0  369     700   422  1.83    0  211  0.97
+//   rectangles, 1 to 3 columns         600   285  1.66    0  116     350   187  1.65    0   62  1.06
+// What stays: pushed lines but for k 3 to 6 at strides above 1 (longer kernels are about even, and at stride 1 the fit missed products
+// at 0.72); rectangles of 4 columns and more (their tiles reuse more, and few would leave).
 enum LaneAgainst { kLaneGroupsFew, kLaneGroups, kLanePushed, kLaneRectFew };
 constexpr double kLaneGain[][15] = {
     // 1, w, w^2, b, b^2, full, a, a^2, stride 1, stride, w a, w b, a b, w at stride 1, a at stride 1
@@ -1432,6 +1446,7 @@ constexpr double kLaneGain[][15] = {
 };
 constexpr double kLaneLeastGain[] = {0.3, 0.25, 0.3, 0.2};
 constexpr int kLaneApart = 4;        // strides from which neighbouring rows share few pixels: less certain
+constexpr double kLaneWorkLeast = -8.5, kLaneWorkMost = 8.5, kLaneChunksMost = 9.0;      // what the counts above cover
 constexpr int kLaneMostTaps = 13, kLanePushedLeastTaps = 3, kLanePushedMostTaps = 6;
 bool lane_serves(const conv_plan *plan, int batch, const CompactChoice &other) {
     const int k = plan->shape.k, columns = batch >= 4 ? 4 : 1, chunks = (batch + columns - 1) / columns;
@@ -1444,7 +1459,8 @@ bool lane_serves(const conv_plan *plan, int batch, const CompactChoice &other) {
         else if (k < kLanePushedLeastTaps || k > kLanePushedMostTaps || plan->shape.s == 1) return false;
         else against = kLanePushed;
     }
-    const double w = std::log2((double)plan->rows * chunks * k * k) - 20.0, b = std::log2((double)chunks), a = std::log2((double)k);
+    const double w = std::clamp(std::log2((double)plan->rows * chunks * k * k) - 20.0, kLaneWorkLeast, kLaneWorkMost);
+    const double b = std::min(std::log2((double)chunks), kLaneChunksMost), a = std::log2((double)k);
     const double full = columns == 4 ? chunks / (4.0 * ((chunks + 3) / 4)) : 0.0, one = plan->shape.s == 1, s = std::log2((double)plan->shape.s);
     const double at[15] = {1.0, w, w * w, b, b * b, full, a, a * a, one, s, w * a, w * b, a * b, w * one, a * one};
     double gain = 0.0;

@@ -947,13 +947,14 @@ bool item_geometry(const conv_plan *plan, int batch, int g, int ways, ItemGeom *
 }
 
 // Lanes per item: more where the launch has few waves (below 512; with the scalar columns of batches 2 and 3 below 2048),
-// each with an access of entries or two of its own; rows of 9 entries one or two (apply_item_kernel.h).  Channels: lanes first, then waves that
-// share them, four channels each at least.
+// each with an access of entries or two of its own; rows of 9 entries one or two (apply_item_kernel.h); chunks of four columns up to 8, as
+// the launches that could use 16 stay with the row groups.  Channels: lanes first, then waves that share them, four
+// channels each at least.
 bool item_choice(const conv_plan *plan, int batch, ApplyChoice *out) {
     const int columns = batch >= 4 ? 4 : 1, most = plan->max_row_nnz;
     const bool many = plan->channels > 1;
     const int64_t waves = (plan->rows * ((batch + columns - 1) / columns) + kWave - 1) / kWave;
-    const int g_most = most == 1 ? 1 : most == 9 ? (many ? 4 : 2) : 16, per_lane = columns == 1 && !many ? 8 : 4;
+    const int g_most = most == 1 ? 1 : most == 9 ? (many ? 4 : 2) : many || columns == 1 ? 16 : 8, per_lane = columns == 1 && !many ? 8 : 4;
     const int64_t enough = many ? 8192 : columns == 1 ? 2048 : 512;
     int g = 1, ways = 1;
     while (g < g_most && g * per_lane < most && waves * g < enough) g *= 2;

@@ -31,7 +31,7 @@ static void launch_item_g(const ApplyChoice &c, const conv_plan *plan, const flo
         } else if (most == 9) launch_item_as<G, C, G == 1 ? 9 : 5, 1, false>(c, plan, x, y, q);
         else if (most == 25) launch_item_as<G, C, 5, 2, false>(c, plan, x, y, q);
         else launch_item_as<G, C, 4, 2, false>(c, plan, x, y, q);
-    } else {
+    } else if constexpr (G < 16 || C == 1) {
         launch_item_as<G, C, 4, 2, false>(c, plan, x, y, q);
     }
 }

@@ -1,6 +1,6 @@
-"""One-launch channel sum over row descriptors with chunks of batch columns side by side on the lanes: planes whose last
-tiles have outputs in some of their parts only, every width of lanes, as built and with edited descriptors.  Reference: the
-sliding-window oracle."""
+"""One-launch channel sum over row descriptors with lanes of four columns: small planes whose last tiles are partly empty, kernel
+sizes with unrolled taps and others, as built and with edited descriptors; chunks side by side where the dispatch has them
+(every such kernel by name: test_gpu_channel_parts.py).  Reference: the sliding-window oracle."""
 import numpy as np
 import pytest
 import torch

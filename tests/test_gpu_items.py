@@ -1,6 +1,6 @@
-"""Row groups with the chunks of a row side by side on the lanes: every lane count and entry grouping, full and ragged
-batches, columns one at a time, operands at any alignment, edited arrays, channels dealt to waves.  Reference: the
-sliding-window oracle, and scipy's product of the arrays as they are."""
+"""Row groups with the chunks of a row side by side on the lanes: rows of 1 to 169 entries, full and ragged batches, operands
+at any alignment, edited arrays, channels dealt to waves.  (Every compiled kernel by name: test_gpu_item_kernels.py.)
+Reference: the sliding-window oracle, and scipy's product of the arrays as they are."""
 import numpy as np
 import pytest
 import scipy.sparse
@@ -25,7 +25,7 @@ def _check(y, buf, offset, ref, scale, what):
     assert np.all(edge[:3 - offset] == 7.0) and np.all(edge[3 - offset + got.size:] == 7.0), what
 
 
-# lanes per item as the dispatch picks them: rows of one entry, of 9 (one and two lanes), 25, 16 to 169, borders of p >= k
+# rows of 1, 4, 9, 25 and up to 169 entries, borders of p >= k; at one batch of each at least items take the product
 @pytest.mark.parametrize("storage,shape,batches", [
     ("csr", (64, 61, 1, 1, 0), (33, 131)), ("csr", (150, 140, 2, 2, 1), (20, 31)), ("csr", (161, 158, 3, 1, 1), (2, 3, 20)),
     ("csr", (90, 81, 5, 2, 2), (20, 31)), ("csr", (90, 91, 6, 3, 5), (40, 131)), ("csr", (70, 75, 7, 3, 3), (70, 101)),

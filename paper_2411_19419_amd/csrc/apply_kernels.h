@@ -491,8 +491,11 @@ __global__ __launch_bounds__(W *kWave) void spmm_csc_tile_kernel(
 // product the row-group scheme of the gather kernels is used with a per-product
 // group width (1 << g_shift lanes per row).  A lane carries all columns of a batch of 2 or 3 (a workgroup for each column
 // before: at batch 3 more waves than run at a time), from 4 on chunks of four, 4 NV per lane, and asks for U entries and then their
-// pixels at a time: a launch this size is its dependent loads (batch 2: 6.9 -> 4.5 us, 3, 77 layers: 8.5 -> 4.8, 4: 6.5 -> 5.8).  From
-// 5 columns on it is the accesses: 8: 7.9 -> 7.8, with half as wide lanes 10.6; 16: 12.2, two entries at a time 12.9.
+// pixels, those of the row only, at a time: a launch this size is its dependent loads.  123 layers, us: batch 2: 5.8 -> 4.3, 3: 8.1 -> 4.5, 4:
+// 4.66 -> 4.50, 8: 6.08 -> 5.87; 3 of 256 x 256, k 5, batch 8: 24.9 -> 16.8.  U takes a lane's part of 9 entries (two lanes) at once; four
+// at a time with a pixel for every slot, the row's or not, were slower than one at a time (16 of 112 x 112, k 3, batch 4: 7.0, 8.0,
+// now 6.7; 3 of 700 x 650, k 1, s 2, batch 8: 6.7, 7.7, 6.8).  At 16 columns per lane it is the accesses (batch 16: 11.0; two
+// entries at a time 12.9).
 // ---------------------------------------------------------------------------
 struct MultiDesc {
     const int *row_ptr;
@@ -572,7 +575,7 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_multi_kernel(const MultiD
             if (row < d.rows && lane == 0) d.y[row * COLS + h] = sum;
         }
     } else {
-        constexpr int U = NV == 4 ? 1 : 4;
+        constexpr int U = NV == 4 ? 1 : kGatherAhead;
         for (int c0 = blockIdx.y * (4 * NV); c0 < batch; c0 += gridDim.y * (4 * NV)) {
             float4 acc[NV];
 #pragma unroll
@@ -589,11 +592,13 @@ __global__ __launch_bounds__(kGatherThreads) void spmm_multi_kernel(const MultiD
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u)
+                    if (u == 0 || e + u * G < end) {
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) px[u][v] = load4(d.x + (long long)col[u] * batch + chunk_col(c0 + 4 * v, batch));
+                        for (int v = 0; v < NV; ++v) px[u][v] = load4(d.x + (long long)col[u] * batch + chunk_col(c0 + 4 * v, batch));
+                    }
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (e + u * G < end) {
+                    if (u == 0 || e + u * G < end) {
 #pragma unroll
                         for (int v = 0; v < NV; ++v) {
                             acc[v].x = fmaf(val[u], px[u][v].x, acc[v].x);

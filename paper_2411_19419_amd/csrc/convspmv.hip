@@ -1029,7 +1029,6 @@ bool item_serves(const conv_plan *plan, int batch, const ApplyChoice &other, con
     if (plan->channels > 1) {
         if (groups && item.item.ways > 1) return true;
     } else {
-        if (batch == 1) return false;
         if (batch < 4) {
             if (other.kind == Kind::March && plan->max_row_nnz >= kItemFewMarchRow) return false;
             against = groups ? kFewGroups : kFewMarching;
@@ -1063,7 +1062,7 @@ ApplyChoice choose_apply(const conv_plan *plan, int batch) {
     if (plan->channels > 1 || plan->nnz == 0 || plan->march_min_jobs < kMarchMinJobs || !block_compiled(sh.k, sh.s, plan->transposed) ||
         column_blocks(batch, 4) > 65535 || !block_geometry(plan, batch, &c.lpr_log2, &c.block) ||
         !block_serves(plan, batch, c.lpr_log2, other))
-        return item_choice(plan, batch, &c) && item_serves(plan, batch, other, c) ? c : other;
+        return (batch > 1 || plan->channels > 1) && item_choice(plan, batch, &c) && item_serves(plan, batch, other, c) ? c : other;
     c.kind = Kind::Block;
     c.threads = kBlockThreads;
     c.g = 1;

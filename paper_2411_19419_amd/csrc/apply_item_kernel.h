@@ -1,11 +1,11 @@
 // Product over the stored CSR arrays, a thread or a few per item: a row and a chunk of its batch columns (gfx950).
 //
 // The row groups of apply_kernels.h give a lane up to 16 batch columns, and a wave as many rows: its accesses are pieces of 16
-// bytes at as many places as it has rows, and a batch that does not fill the blocks of 16 columns leaves lanes idle (so do tiles and marches).  Here the
-// chunks of four columns of a row lie side by side on the lanes (one column each below a batch of 4), then those of the next row: x and y move in whole
-// memory lines whatever the batch, the lanes of a row ask for the same entries with one access, and no lane is idle but the
-// launch's last.  No staging and no barrier: neighbouring rows share their pixels through the L1 and the L2 (workgroups of
-// neighbouring rows run on one XCD).
+// bytes at as many places as it has rows, and a batch that does not fill the blocks of 16 columns leaves lanes idle (so do tiles
+// and marches).  Here the chunks of four columns of a row lie side by side on the lanes (one column each below a batch of 4), then
+// those of the next row: x and y move in whole memory lines whatever the batch, the lanes of a row ask for the same entries with
+// one access, and no lane is idle but the launch's last.  No staging and no barrier: neighbouring rows share their pixels through
+// the L1 and the L2 (workgroups of neighbouring rows run on one XCD).
 //
 // G lanes share an item where the launch has few waves; lane l takes U consecutive entries at a time, U l, U l + U G, ...,
 // NB such accesses are asked for together with their pixels after them.  U fits the rows: 25 entries in fives, others in fours;
@@ -13,21 +13,22 @@
 // Sums: each access is a chain of its own; the accesses of a row, its lanes and its channels are added in 64 bits, which this
 // chip adds as fast as 32 (1384 products: 0.99 of the time of sums in 32 bits).  Rows at once are one chain, of 9 entries two
 // of every other entry, the order of the tile kernel.  Error against 64 bits over that of the kernels it takes products
-// from, in the geometric mean: rows of 1, 4 and 9 entries 1.00, 0.99 and 1.00; 16: 0.85; 25: 0.84; 36: 0.72; 49 and 64: 0.69; 81: 0.68;
-// 100: 0.65; 121 and 144: 0.62; 169: 0.59; channels 0.31 of the row groups', 0.51 of the others'.  (In 32 bits, two sums in turn and the tail of a
-// row on top of one of them: 25 entries 1.07, up to 1.24; 36: 1.05; 64: 1.07; three channels of 25 entries up to 1.18.)
+// from, in the geometric mean: rows of 1, 4 and 9 entries 1.00, 0.99 and 1.00; 16: 0.85; 25: 0.84; 36: 0.72; 49 and 64: 0.69;
+// 81: 0.68; 100: 0.65; 121 and 144: 0.62; 169: 0.59; channels 0.31 of the row groups', 0.51 of the others'.  (In 32 bits, two sums in
+// turn and the tail of a row on top of one of them: 25 entries 1.07, up to 1.24; 36: 1.05; 64: 1.07; three channels of 25 up to 1.18.)
 //
 // MANY: several channels that share the indices.  The waves of a workgroup hold the same items and deal the channels out; a lane
 // keeps its entries' columns while NB of its channels pass, and the partial sums meet in LDS.
 //
-// Measured, fresh operands, before -> after: 1362 x 1644, k 1, s 2, batch 100: 656 -> 106 us (tiles); 909 x 1348, k 6, s 3,
-// batch 132: 1153 -> 226 (march); 70 x 91, k 6, T^T, batch 85: 34 -> 7.3 (staged march); 755 x 1134, k 7, s 4, batch 116: 427 -> 125 (row
-// groups); 2388 x 1551, k 3, s 3, T^T, batch 64: 676 -> 420; 36 x 52, k 7, s 4, 206 channels, batch 8: 317 -> 25; 30 x 31, k 9, s 3, 136 channels,
-// batch 2: 273 -> 23.  What bounds it: large products the L2, which delivers every pixel once per entry but for what the
-// L1 catches (11 TB/s at 733 x 667, k 6, s 3, batch 204, 139 us); small ones a round trip for the row's bounds and two for
-// every NB U G entries.  Not kept: blocks of 4 to 32 chunks at a time instead of all of a row's (1.03 to 1.27 of the time); the next
-// entries asked for ahead of the sums (0.97 of the time in small products, 1.06 in large ones, which lose waves to the registers);
-// entries and values of channels by accesses of 16 bytes with a masked tail (1.08).
+// Measured, two sets of operands in turn, before -> after: 1362 x 1644, k 1, s 2, batch 100: 654 -> 105 us (tiles); 909 x 1348, k 6, s 3,
+// batch 132: 1148 -> 229 (march); 70 x 91, k 6, T^T, batch 85: 32 -> 7.2 (staged march); 755 x 1134, k 7, s 4, batch 116: 438 -> 125
+// (row groups); 2388 x 1551, k 3, s 3, T^T, batch 64: 684 -> 379; 36 x 52, k 7, s 4, 206 channels, batch 8: 300 -> 26; 30 x 31, k 9, s 3,
+// 136 channels, batch 2: 140 -> 23.  What bounds it: large products the L2, which delivers every pixel once per entry but for what
+// the L1 catches (733 x 667, k 6, s 3, batch 204: 12.9 M requests of 128 bytes in 142 us, 11.6 TB/s, a quarter of the L1's accesses);
+// small ones a round trip for the row's bounds and two for every NB U G entries.  Not kept: blocks of 4 to 32 chunks at a time
+// instead of all of a row's (1.03 to 1.27 of the time); the next entries asked for ahead of the sums (0.97 of the time in small
+// products, 1.06 in large ones, which lose waves to the registers); entries and values of channels by accesses of 16 bytes with
+// a masked tail (1.08).
 #pragma once
 #include "apply_kernels.h"
 

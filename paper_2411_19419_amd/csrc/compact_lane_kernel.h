@@ -11,11 +11,11 @@
 // of the kernels it takes products from, in the mean of 535: 0.71 (K 2 1.00, K 3 0.79, K 5 0.63, K 7 0.77, K 11 0.77).  With up to four
 // 32-bit sums of lines in turn, in the same time: 0.83, but K 5 from row groups of 8 lanes 1.02, one kernel of K 3 up to 1.18.
 //
-// Measured, operands in turn, before -> after (us):
-//   row groups        85 x 92, k 4, p 2, batch 204      13.4 -> 6.9      360 x 306, k 8, p 7, batch 3     21.3 -> 8.7
-//                     530 x 621, k 3, s 2, batch 92     87.6 -> 31.5     1161 x 1222, k 9, s 2, batch 1   37.0 -> 16.4
-//   described         350 x 322, k 6, s 3, batch 40     14.0 -> 7.6      1628 x 1808, k 4, s 2, batch 2   23.1 -> 14.4
-//   rectangles        2108 x 1652, k 2, s 2, batch 3    24.3 -> 11.7     1612 x 2501, k 3, s 2, batch 1   11.7 -> 8.3
+// Measured, two sets of operands in turn, before -> after (us):
+//   row groups        85 x 92, k 4, p 2, batch 204      13.3 -> 6.6      360 x 306, k 8, p 7, batch 3     18.5 -> 8.4
+//                     530 x 621, k 3, s 2, batch 92     87.6 -> 30.4     1161 x 1222, k 9, s 2, batch 1   38.2 -> 18.7
+//   described         350 x 322, k 6, s 3, batch 40     13.7 -> 6.9      1628 x 1808, k 4, s 2, batch 2   23.0 -> 15.0
+//   rectangles        2108 x 1652, k 2, s 2, batch 3    24.4 -> 11.5     1612 x 2501, k 3, s 2, batch 1   11.7 -> 7.9
 // What bounds it: the L1 where the taps are many (a pixel per tap and lane: 208 x 277, k 11, batch 16 takes 22 us of arithmetic and
 // reads that memory would give in 2.8), the memory where they are few (530 x 621 above: 22 us at the rate of a large copy).
 #pragma once

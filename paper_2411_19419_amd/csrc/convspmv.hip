@@ -975,43 +975,62 @@ bool item_choice(const conv_plan *plan, int batch, ApplyChoice *out) {
 
 // Where an item launch (apply_item_kernel.h) takes a product from the kernel that would have it otherwise: where a surface, fitted to
 // which of the two is the faster, is above zero.  The times are in profiles/chunk_kernel_times.csv: drawn products (planes of 8
-// to 4096 a side, k 1 to 13, strides 1 to 4, batches to 2048, up to 1024 channels; 600 or 1200 of each kernel left, of T and of T^T), both
-// kernels in replayed graphs.  Logistic regression on which is faster; a product weighs the logarithm of its times' ratio, up to 0.7, 4
-// times that where items are slower (6 times: row groups above a batch of 3 and marches; twice: channels in row groups), and one
-// that tests hold to a kernel 1 (row groups of T: 4).  (Tiles: an older fit to the logarithm itself, less 0.12, by short products, w below
-// 2, less 0.4, as tests hold products to tiles that a new one would take.)
+// to 4096 a side, k 1 to 13, strides 1 to 4, batches to 2048, a third of them multiples of 16, up to 1024 channels), both kernels
+// in replayed graphs.  Logistic regression on which is faster; a product weighs the logarithm of its times' ratio, up to 0.7, and
+// where items are slower 3 times that (channels in other kernels 4, row groups above a batch of 3 and marches 6); one that tests hold to
+// a kernel weighs 1 (row groups of T: 4).  (Tiles: an older fit to the logarithm itself, less 0.12, by short products, w below 2, less 0.4, as tests
+// hold products to tiles that a new one would take.)
 // Coordinates: w, the multiply-adds of a chunk each (log2 of millions); b, the chunks (log2); how full the other kernels' blocks of 16
-// columns are; a, the longest row (log2); stride 1 or not; c, the channels (log2); beyond the ranges of the fit held at their
-// ends.  By the kernel left: products, how many leave it, time before over time after in their mean, those then more than 6 % slower,
-// those that would still be that much faster; and the same of products drawn apart, with the slowest:
-//   row groups, batches of 2 and 3    1014   574  1.59    5   29     588   313  1.62    1   16  0.93
+// columns are; a, the longest row (log2); stride 1 or not; the other kernel's chunks per lane, 2 or 4, and whether the batch is a
+// multiple of them, as its lanes are then full and its accesses aligned; c, the channels (log2).  Beyond the ranges of the fit they are
+// held at their ends.  By the kernel left: products, how many leave it, time before over time after in their mean, those then more than
+// 6 % slower, those that would still be that much faster; and the same of products drawn apart, with the slowest:
+//   row groups, batches of 2 and 3    1014   584  1.58    5   24     588   328  1.59    1   13  0.93
 //   marching, batches of 2 and 3       186   150  1.80    0    1     112    94  1.70    2    7  0.87
-//   row groups, T                      600   347  1.48   12   42     350   202  1.53    3   29  0.91
-//   row groups, T^T                    600   358  1.52    6   49     350   215  1.50    7   34  0.76
-//   tiles, T                           600   246  2.18    2  234     350   145  2.08    3  136  0.82
-//   marching                          1200   671  2.02   24  118     700   393  2.14    8   67  0.79
-//   staged march, T                    600   277  1.97   10   49     350   143  1.90   10   27  0.76
-//   staged march, T^T                  600   312  1.84    6   37     350   187  1.82    4   33  0.89
-//   channels, row groups              1525  1276  1.50   75   68    2001  1641  1.51  107   87  0.60
-//   channels, other kernels            600   438  2.32    5   29     350   246  2.18    7   19  0.48
-// Channel sums of row groups whose launch has waves to share the channels (ways) leave always: 619, none slower than 0.95 of the former speed.
-// What stays: products that both kernels finish within the time of a launch (w below -4, at strides of 4 and more -0.9); tiles of T^T
-// (1.05 in the mean) and blocks (1.1 where they would leave); marching rows of 64 entries and more at batches of 2 and 3 (1.09); row groups
-// of one column and of batches 4 to 8, which are as fast (1.04 and 0.98 with the best G).
+//   row groups, T                      900   529  1.50   10   55     550   311  1.55    5   37  0.82
+//   row groups, T^T                    900   576  1.49    8   47     550   359  1.47    9   35  0.76
+//   tiles, T                           900   369  1.97    2  330     550   218  1.95    6  205  0.80
+//   marching                          1800   763  1.92   23  182    1100   454  1.98   15  110  0.79
+//   staged march, T                    900   296  1.93   10   84     550   154  1.87    8   54  0.82
+//   staged march, T^T                  900   360  1.75    8   93     550   223  1.70    5   66  0.73
+//   channels, row groups              1692  1334  1.53   59  105    2119  1641  1.53   76  133  0.65
+//   channels, other kernels            900   543  2.10   18   38     550   336  1.94   19   23  0.72
+// Channel sums of row groups whose launch has waves to share the channels (ways) leave always: 834, none slower than 0.95 of the
+// former speed.  What stays: products that both kernels finish within the time of a launch (w below -4, at strides of 4 and more -0.9);
+// tiles of T^T (1.05 in the mean) and blocks (1.1 where they would leave); marching rows of 64 entries and more at batches of 2
+// and 3 (1.09); row groups of one column and of batches 4 to 8, which are as fast (1.04 and 0.98 with the best G).
 enum ItemAgainst { kFewGroups, kFewMarching, kGroupsT, kGroupsTT, kTileT, kMarching, kStagedT, kStagedTT, kGroupsMany, kOthersMany };
-constexpr int kItemTerms = 18;
+constexpr int kItemTerms = 22;
 constexpr double kItemFaster[][kItemTerms] = {
-    // 1, w, w^2, b, b^2, full, a, a^2, stride 1, w a, w b, a b, w at stride 1; channels: c, c^2, c w, c b, c a
-    {7.6104, 0.4127, 0.3728, -0.4595, -0.1778, 0, -1.0377, -0.0869, -0.6655, 0.3888, 0.7638, -0.0862, -0.361},      // row groups, batches of 2 and 3
-    {79.4371, -13.7317, 1.2183, 23.3191, 9.0211, 0, 7.4219, -0.8064, -9.3556, -3.3968, 6.702, -7.8497, 2.4019},      // marching, batches of 2 and 3
-    {16.8595, -0.1938, -0.1076, 5.0236, -0.2216, -1.4592, -6.6658, 0.5418, -1.9865, 0.0134, 0.4308, -0.4311, 0.3025},      // row groups, T
-    {3.183, -1.6541, -0.035, 2.087, 0.0642, -4.2097, -0.4403, -0.0182, -0.4883, 0.2419, 0.4544, -0.2993, -0.1478},      // row groups, T^T
-    {0.3659, -0.0364, 0.0064, 0.2009, -0.0294, -0.2387, -0.0487, -0.0095, -0.0566, -0.0175, 0.0186, 0.012, -0.0491},      // tiles, T
-    {24.8668, -2.6753, 0.5393, 5.1708, -0.1301, 2.5897, -7.1335, 0.8342, 3.6684, -0.7584, 0.1183, -0.4917, -0.9791},      // marching
-    {51.2498, 3.3824, 0.2018, 0.413, 0.0039, 1.1711, -22.798, 2.4518, 9.0107, -1.1984, -0.0752, 0.3145, -1.7064},      // staged march, T
-    {71.2506, 2.4981, 0.1929, 0.3695, -0.0618, -6.9983, -25.0351, 2.4377, 0.143, -1.2136, -0.3672, 0.9124, -0.1312},      // staged march, T^T
-    {16.1273, 2.3603, 0.0651, 2.9615, -0.1238, -5.805, -6.0015, 0.5587, -1.7587, -0.5349, -0.0019, -0.1565, -0.0658, -3.6973, 0.3332, -0.2547, -0.1533, 0.782},      // channels, row groups
-    {35.3112, 0.119, 1.5678, -1.2692, -0.2012, -0.1199, -16.0701, 2.9379, -5.9897, -3.5053, 0.634, 0.5747, 0.5487, 10.7631, 0.162, -2.994, -0.91, 2.4588},      // channels, other kernels
+    // 1, w, w^2, b, b^2, full, a, a^2, stride 1, w a, w b, a b, w at stride 1, 2 chunks per lane, 4, multiple of them, of 4;
+    // channels: c, c^2, c w, c b, c a
+    // row groups, batches of 2 and 3
+    {8.0602, -0.1201, 0.3672, 0.1052, 0.0407, 0, -1.3024, -0.0272, -0.7083, 0.3953, 1.1541, -0.3363, -0.3703},
+    // marching, batches of 2 and 3
+    {88.0951, -17.0261, 1.768, 29.3963, 11.3721, 0, 11.0449, -0.9896, -6.4024, -4.3707, 7.6586, -9.5511, 1.9944},
+    // row groups, T
+    {23.5069, -0.1758, -0.0442, 6.2448, -0.4005, 1.814, -11.3378, 0.9234, -1.5365, -0.1334, 0.4496, -0.3733, 0.5849,
+     -1.3357, 3.9855, -0.8001, 0.4776},
+    // row groups, T^T
+    {-2.7903, -2.2908, 0.0633, 2.3078, -0.0013, -2.0062, -0.4367, -0.0562, 1.0173, 0.2231, 0.4346, -0.2403, -0.0338,
+     0.8529, 4.6813, 1.0905, 1.111},
+    // tiles, T
+    {0.3659, -0.0364, 0.0064, 0.2009, -0.0294, -0.2387, -0.0487, -0.0095, -0.0566, -0.0175, 0.0186, 0.012, -0.0491},
+    // marching
+    {3.7367, -2.4808, 0.5077, 2.6523, -0.1534, 6.4352, 1.2004, 0.0278, 4.4584, -0.788, 0.1273, -0.0591, -0.8703, -1.5612,
+     -4.1715, -1.4058, -0.5283},
+    // staged march, T
+    {63.3654, -1.9129, 0.0451, 3.0241, 0.0218, 6.3423, -22.4184, 1.813, 4.0053, 0.2112, -0.2136, -0.128, -0.5929,
+     -2.9133, -6.7706, -1.9805, 0.2129},
+    // staged march, T^T
+    {76.3723, -1.2961, 0.0864, 1.3883, -0.0879, -2.4071, -24.4221, 1.9923, -0.1241, -0.1322, -0.2404, 0.4734, 0.0272,
+     -1.8124, -3.9253, -2.1951, 1.3022},
+    // channels, row groups
+    {16.2551, 2.5828, 0.0321, 2.9165, -0.1303, -2.8413, -6.0369, 0.5495, -1.7952, -0.5561, 0.0004, -0.1573, -0.0725,
+     -2.7253, -2.3049, 0.4357, -0.9928, -4.0148, 0.3439, -0.244, -0.1575, 0.8381},
+    // channels, other kernels
+    {50.7089, 6.9869, 0.9959, -2.2321, 0.2014, 13.2341, -24.4058, 3.5737, 0.9072, -3.5822, 1.1214, -0.5658, -0.6216,
+     -1.8357, -5.3448, -0.2813, -3.4369, -0.3796, 1.33, -2.848, -1.1262, 3.1921},
 };
 constexpr double kItemLaunch = -4.0, kItemLaunchStrided = -0.9, kItemShortTiles = 2.0, kItemShortTilesLeast = 0.28;
 constexpr double kItemWorkLeast = -9.0, kItemWorkMost = 7.9, kItemChunksMost = 9.0;      // the fit's ranges
@@ -1048,7 +1067,9 @@ bool item_serves(const conv_plan *plan, int batch, const ApplyChoice &other, con
     const double b = std::min(std::log2((double)chunks), kItemChunksMost), a = std::log2((double)plan->max_row_nnz), s = plan->shape.s == 1;
     const double c = std::min(std::log2((double)plan->channels), groups ? kItemChannelsMost : kItemChannelsMostOthers);
     const double full = columns == 4 ? chunks / (4.0 * ((chunks + 3) / 4)) : 0.0;
-    const double at[kItemTerms] = {1.0, w, w * w, b, b * b, full, a, a * a, s, w * a, w * b, a * b, w * s, c, c * c, c * w, c * b, c * a};
+    const double two = other.nv == 2, four = other.nv == 4, whole = other.nv && batch % (4 * other.nv) == 0;
+    const double at[kItemTerms] = {1.0, w, w * w, b, b * b, full, a, a * a, s, w * a, w * b, a * b, w * s, two, four, whole, whole * four,
+                                   c, c * c, c * w, c * b, c * a};
     double faster = 0.0;
     for (int i = 0; i < kItemTerms; ++i) faster += kItemFaster[against][i] * at[i];
     return faster > least;

@@ -45,3 +45,16 @@ def test_beyond_the_times(shape, batch, storage, channels):
     d = cs.conv_dispatch_info(*shape, batch, storage, channels)
     near = cs.conv_dispatch_info(*shape, min(batch, 2048), storage, min(channels, 1024))
     assert d.workgroups > 0 and (d.strip > 0, d.kernel) == (near.strip > 0, near.kernel)
+
+
+# batches that fill the lanes of the kernels left (2 or 4 chunks each), where those are at their best; products of T, of T^T and channel
+# sums apart, as one may be wrong while the others hide it
+def test_batches_that_fill_the_other_kernels_lanes():
+    groups = {}
+    for r, gain, takes in _rows():
+        chunks = int(r["other_chunks_per_lane"])
+        if r["storage"] != "compact" and r["held"] == "0" and chunks > 1 and int(r["batch"]) % (4 * chunks) == 0 and takes:
+            groups.setdefault((r["storage"], r["channels"] == "1"), []).append(gain)
+    assert len(groups) == 3
+    for group, taken in groups.items():
+        assert len(taken) >= 100 and sum(gain < -0.06 for gain in taken) <= 0.06 * len(taken), (group, len(taken), sum(gain < -0.06 for gain in taken))

@@ -17,7 +17,7 @@ ONE = [
     ("csr", (7, 6, 5, 3, 0), 2, 1, 4, 25), ("csr", (7, 9, 6, 4, 0), 2, 1, 8, 36), ("csr", (175, 204, 13, 2, 0), 2, 1, 16, 169),
     ("csc", (142, 155, 2, 2, 0), 9, 4, 1, 1), ("csr", (160, 139, 2, 2, 0), 9, 4, 1, 4), ("csc", (29, 21, 7, 3, 0), 258, 4, 1, 9), ("csc", (51, 58, 6, 2, 0), 9, 4, 2, 9),
     ("csc", (29, 17, 13, 3, 0), 269, 4, 1, 25), ("csc", (27, 18, 13, 3, 0), 266, 4, 2, 25), ("csc", (17, 28, 7, 2, 0), 286, 4, 1, 16), ("csr", (20, 26, 4, 2, 5), 298, 4, 2, 16),
-    ("csr", (47, 49, 4, 2, 2), 34, 4, 4, 16), ("csr", (28, 48, 5, 2, 2), 89, 4, 8, 25), ("csr", (145, 210, 6, 2, 3), 97, 4, 1, 36), ("csr", (60, 64, 8, 1, 4), 118, 4, 1, 64),
+    ("csr", (47, 49, 4, 2, 2), 34, 4, 4, 16), ("csr", (60, 46, 5, 3, 4), 65, 4, 8, 25), ("csr", (145, 210, 6, 2, 3), 97, 4, 1, 36), ("csr", (60, 64, 8, 1, 4), 118, 4, 1, 64),
 ]
 # shape, batch, channels, columns, lanes, ways
 MANY = [

@@ -1134,7 +1134,7 @@ bool rect_compiled(int k, int s) {
 
 constexpr double kChanFusedWork = 1e8;        // multiply-adds per channel below which the launches are fused
 constexpr int64_t kChanFusedWaves = 2048;     // waves that fill the chip (8 per CU)
-constexpr int64_t kChanPartsMinBlocks = 64;   // workgroups from which k 3 at stride 1 has its tiles in parts
+constexpr int64_t kChanPartsMinBlocks = 64;   // workgroups from which k 3 at stride 1 has its tiles in parts (a quarter of them at stride 2)
 
 // The push kernel's launch: strips of 64 lanes, four waves' parts per segment.  False where a strip's
 // line is longer than a wave's registers for it, or the padding reaches the kernel size (rows
@@ -1574,12 +1574,13 @@ ChannelsChoice choose_compact_channels(const conv_plan *plan, const float *x, co
         c.ways = ways;
         // lanes of four columns: the chunks that lie side by side, as many as the batch is a multiple of and a wave's patch has room for,
         // unless the patches, which overlap the more the more parts a tile is in, need more pixels in flight (the kernel's 4 or 8
-        // per lane; 26 x 19, k 7, 3 channels, batch 16: 3.75 us, in four parts 4.57).  Few workgroups of k 3 wait for each other's
-        // patches anyway (12 x 15, k 3, 277 channels, batch 16: 15.4 and 17.0).  2500 sums, batches to 480: 1.08 times the speed of one
-        // chunk in the mean, 17 of them more than 6 % slower, with parts wherever they fit 1.07 and 142.
+        // per lane; 26 x 19, k 7, 3 channels, batch 16: 3.75 us, in four parts 4.57).  Few workgroups of k 3 at strides 1 and 2
+        // wait for each other's patches anyway (12 x 15, k 3, 277 channels, batch 16: 15.4 and 17.0; but 19 x 29, k 3, s 2, 113 channels, batch
+        // 32, 24 workgroups: 29 and 15).  2500 sums, batches to 480: 1.08 times the speed of one chunk in the mean, 24 of them more than
+        // 6 % slower, with parts wherever they fit 1.07 and 144.
         c.chunks = 1;
         int64_t width = phy, wave_vec4 = vec4;
-        const bool parts = vb == 4 && (sh.k != 3 || blocks >= (sh.s == 1 ? kChanPartsMinBlocks : kChanPartsMinBlocks / 2));
+        const bool parts = vb == 4 && (sh.k != 3 || sh.s > 2 || blocks >= (sh.s == 1 ? kChanPartsMinBlocks : kChanPartsMinBlocks / 4));
         for (int chunks = 4; parts && chunks > 1 && c.chunks == 1; chunks /= 2) {
             const int64_t w = (int64_t)(kChanTileY / chunks - 1) * sh.s + sh.k, patch = phx * w * chunks;
             const int64_t v = std::max<int64_t>(patch, kWave) + ((int64_t)sh.k * sh.k + 3) / 4;

@@ -1580,7 +1580,7 @@ ChannelsChoice choose_compact_channels(const conv_plan *plan, const float *x, co
         // 6 % slower, with parts wherever they fit 1.07 and 144.
         c.chunks = 1;
         int64_t width = phy, wave_vec4 = vec4;
-        const bool parts = vb == 4 && (sh.k != 3 || sh.s > 2 || blocks >= (sh.s == 1 ? kChanPartsMinBlocks : kChanPartsMinBlocks / 4));
+        const bool parts = vb == 4 && (sh.k != 3 || blocks >= (sh.s == 1 ? kChanPartsMinBlocks : kChanPartsMinBlocks / 4));
         for (int chunks = 4; parts && chunks > 1 && c.chunks == 1; chunks /= 2) {
             const int64_t w = (int64_t)(kChanTileY / chunks - 1) * sh.s + sh.k, patch = phx * w * chunks;
             const int64_t v = std::max<int64_t>(patch, kWave) + ((int64_t)sh.k * sh.k + 3) / 4;

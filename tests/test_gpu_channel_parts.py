@@ -14,10 +14,10 @@ PARTS = [
     ((26, 43, 1, 1, 0), 33, 16, 4), ((27, 31, 1, 3, 0), 9, 32, 4), ((29, 35, 3, 1, 1), 20, 16, 4), ((31, 50, 3, 2, 1), 11, 16, 4), ((13, 21, 5, 1, 2), 6, 16, 4),
     ((17, 38, 6, 2, 1), 3, 16, 2), ((15, 34, 4, 3, 3), 12, 16, 1), ((25, 39, 1, 2, 0), 40, 24, 2), ((40, 44, 1, 3, 0), 5, 8, 2), ((25, 35, 3, 1, 0), 17, 24, 2),
     ((33, 52, 3, 2, 2), 64, 24, 2), ((12, 19, 6, 1, 3), 14, 16, 2), ((20, 33, 9, 1, 4), 7, 40, 2), ((21, 19, 5, 2, 2), 5, 24, 2), ((18, 23, 2, 2, 1), 16, 16, 4),
-    # ragged batches, overlaps that would need more pixels in flight, few workgroups of k 3: one chunk, and where
-    # they are enough at strides 2 and 3
+    # ragged batches, overlaps that would need more pixels in flight, few workgroups of k 3 (enough at stride 2):
+    # one chunk
     ((26, 43, 1, 1, 0), 33, 12, 1), ((26, 19, 7, 1, 0), 3, 16, 1), ((35, 42, 6, 1, 0), 4, 16, 2), ((90, 62, 8, 1, 0), 19, 8, 1), ((30, 28, 3, 1, 1), 47, 8, 1),
-    ((18, 17, 3, 2, 1), 163, 16, 1), ((19, 29, 3, 2, 1), 113, 32, 4), ((16, 19, 3, 3, 1), 41, 16, 4),
+    ((18, 17, 3, 2, 1), 163, 16, 1), ((19, 29, 3, 2, 1), 113, 32, 4), ((16, 19, 3, 3, 1), 41, 16, 1),
 ]
 
 

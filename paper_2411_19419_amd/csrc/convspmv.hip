@@ -920,28 +920,35 @@ ApplyChoice choose_unblocked(const conv_plan *full, int batch) {
     return c;
 }
 
+// Rows and chunks of four columns, one below a batch of 4, dealt out to cells of per_cell and to the XCDs (items, and descriptor
+// lanes); false beyond 32-bit byte offsets into x (x_size numbers) and y, item numbers of 32 bits, or exact small divisions.
+template <class Geom>
+bool chunk_geometry(const conv_plan *plan, int batch, int64_t x_size, int64_t per_cell, Geom *g) {
+    const int columns = batch >= 4 ? 4 : 1;
+    const int64_t chunks = (batch + columns - 1) / columns, items = plan->rows * chunks, cells = (items + per_cell - 1) / per_cell;
+    if (x_size >= (1LL << 30) || plan->rows * batch >= (1LL << 30) || items > kInt32Limit - kItemThreads || chunks + kWave >= (1 << 21) ||
+        cells + kXcds >= (1LL << 31) / kXcds)
+        return false;
+    g->batch = batch;
+    g->chunks = (int)chunks;
+    g->inv_chunks = 1.0f / (float)chunks;
+    g->items = (unsigned)items;
+    g->cells = (int)cells;
+    g->cells_per_xcd = (int)((cells + kXcds - 1) / kXcds);
+    return true;
+}
+
 // Geometry of an item launch with g lanes per item.
 bool item_geometry(const conv_plan *plan, int batch, int g, int ways, ItemGeom *out) {
-    const int columns = batch >= 4 ? 4 : 1;
-    const int64_t chunks = (batch + columns - 1) / columns, items = plan->rows * chunks, plane = plan->cols / plan->channels * batch;
-    // 32-bit byte offsets into a plane of x and into y, products of 24-bit numbers; item numbers of 32 bits; exact small divisions
-    if (plane >= (1LL << 30) || plan->rows * batch >= (1LL << 30) || plan->cols / plan->channels > (1 << 24) || batch >= (1 << 22) ||
-        items > kInt32Limit - kItemThreads || chunks + kWave >= (1 << 21))
-        return false;
+    const int64_t pixels = plan->cols / plan->channels;
     ItemGeom i{};
-    i.batch = batch;
-    i.chunks = (int)chunks;
-    i.inv_chunks = 1.0f / (float)chunks;
-    i.items = (unsigned)items;
+    if (pixels > (1 << 24) || batch >= (1 << 22) ||      // a column times the batch is a product of 24-bit numbers
+        !chunk_geometry(plan, batch, pixels * batch, (plan->channels > 1 ? kWave : kItemThreads) / g, &i))
+        return false;
     i.channels = plan->channels;
     i.ways = ways;
-    const int64_t per_cell = (plan->channels > 1 ? kWave : kItemThreads) / g;
-    const int64_t cells = (items + per_cell - 1) / per_cell;
-    if (cells + kXcds >= (1LL << 31) / kXcds) return false;
-    i.cells = (int)cells;
-    i.cells_per_xcd = (int)((cells + kXcds - 1) / kXcds);
     i.vals_stride = plan->nnz;
-    i.x_stride = plane;
+    i.x_stride = pixels * batch;
     *out = i;
     return true;
 }
@@ -1313,22 +1320,9 @@ void compact_row_groups(const conv_plan *plan, int batch, CompactChoice *out) {
 }
 
 bool lane_geometry(const conv_plan *plan, int batch, LaneGeom *out) {
-    const int columns = batch >= 4 ? 4 : 1;
-    const int64_t chunks = (batch + columns - 1) / columns, items = plan->rows * chunks;
-    // 32-bit byte offsets into x and y; item numbers of 32 bits; exact small divisions
-    if (plan->shape.k < 2 || plan->shape.k > 13 || plan->cols * batch >= (1LL << 30) || plan->rows * batch >= (1LL << 30) ||
-        items > kInt32Limit - kItemThreads || chunks + kWave >= (1 << 21))
-        return false;
     LaneGeom g{};
+    if (plan->shape.k < 2 || plan->shape.k > 13 || !chunk_geometry(plan, batch, plan->cols * batch, kItemThreads, &g)) return false;
     g.n = plan->shape.n;
-    g.batch = batch;
-    g.chunks = (int)chunks;
-    g.inv_chunks = 1.0f / (float)chunks;
-    g.items = (unsigned)items;
-    const int64_t cells = (items + kItemThreads - 1) / kItemThreads;
-    if (cells + kXcds >= (1LL << 31) / kXcds) return false;
-    g.cells = (int)cells;
-    g.cells_per_xcd = (int)((cells + kXcds - 1) / kXcds);
     *out = g;
     return true;
 }
@@ -1403,12 +1397,13 @@ CompactChoice choose_compact_path(const conv_plan *plan, int batch) {
     // Rectangles whose launch stays below that bound, with strips that are not mostly empty (32 x 20, k 7, s 2, batch 1318, a
     // fifth full: 8.6 us in row groups, 39 marching).  Where segments are longer than the shortest the launch has as many
     // workgroups as it asked for, a few less than compute units because strips do not divide them (3239 x 2417, k 7, s 2, batch 4: 255,
-    // 144 us in row groups, 48 marching): from these lengths on, in steps of rv lines, as the waves' first window is paid for.  Else
-    // as many workgroups, and with few blocks of columns as many full ones, as it takes for the taps (571 x 726, k 7, batch 1, 219: 24.5 and 7.9; 202 x 241, k 7,
-    // batch 32, 208: 37 and 12; 497 x 778, k 9, batch 1: 33 and 9.6; but 201 x 261, k 7, batch 12, 130 that hold 106: 10.6 and 11.9; 31 x 36, k 5,
-    // batch 522, 165 that hold 103: 8.8 and 10.5).  Of 900 products of row groups that have
-    // these lengths or workgroups, batches to 2048, 856 march, 1.69 times as fast in the mean, 3 more than 6 % slower (0.88 at the worst), and
-    // 44 are left as too empty (marching 0.76 in the mean); what their sums do to the error stands at FINE in compact_kernels.h.
+    // 144 us in row groups, 48 marching): from these lengths on, in steps of rv lines, as the waves' first window is paid for.
+    // Else as many workgroups, and with few blocks of columns as many full ones, as it takes for the taps (571 x 726, k 7, batch 1,
+    // 219: 24.5 and 7.9; 202 x 241, k 7, batch 32, 208: 37 and 12; 497 x 778, k 9, batch 1: 33 and 9.6; but 201 x 261, k 7, batch
+    // 12, 130 that hold 106: 10.6 and 11.9; 31 x 36, k 5, batch 522, 165 that hold 103: 8.8 and 10.5).  Of 900 products of row
+    // groups that have these lengths or workgroups, batches to 2048, 856 march, 1.69 times as fast in the mean, 3 more than 6 %
+    // slower (0.88 at the worst), and 44 are left as too empty (marching 0.76 in the mean); what their sums do to the error stands
+    // at FINE in compact_kernels.h.
     auto short_of_bound = [&] {
         if (lowered || can_push || !c.kk || plan->channels > 1) return false;
         const int64_t wgs = workgroups(c), places = (int64_t)c.geom.tw * c.geom.strips;
